@@ -49,7 +49,6 @@
 #include <cstring>
 #include <deque>
 #include <map>
-#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -105,26 +104,6 @@ using namespace slbm_dev;
 
 // ------------------------------------------------------ output kernels
 
-// delta-rho of the current state at every site (0 where there is no state).
-template <typename real, bool PER>
-__global__ __launch_bounds__(256) void k_density(StepArgs<real> a, double* dr_out)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= a.plane) return;
-    const int y = idx / a.ld - 1, x = idx % a.ld - kPadL;
-    double v = 0.0;
-    if (x >= 0 && x < a.nx && y >= 0 && y < a.ny) {
-        real g[9];
-        unsigned fl;
-        if (fetch_site<real, PER>(a, x, y, g, fl)) {
-            double s = 0.0;
-            for (int i = 0; i < 9; ++i) s += (double)g[i];
-            v = s;
-        }
-    }
-    dr_out[idx] = v;
-}
-
 // Density-gradient stencil at a site from a delta-rho field (same closure as
 // the step kernel).
 template <bool PER>
@@ -150,100 +129,94 @@ __device__ void grad_rho(const double* dr, const uint8_t* flags, int x, int y, i
     gy = (1.0 / 3.0) * (rt[2] - rt[4]) + (1.0 / 12.0) * (rt[5] + rt[6] - rt[7] - rt[8]);
 }
 
-// Lattice-unit moments and displacement of the material site (x, y) (padded
-// offset idx) from the current state and the density field dr: o[11] = rho,
-// jx, jy, Pxx, Pyy, Pxy, sxx, syy, sxy, ux, uy (eq:moments with the half-step
-// source, eq:poissonstress with eq:approxdiv, the trapezoid displacement).
-template <typename real, bool PER>
-__device__ __forceinline__ void site_outputs(const StepArgs<real>& a, const double* dr, int x, int y, int idx,
-                                             double o[11])
+// Where a readout goes: unpadded arrays of the caller (null: not wanted), u
+// [2][n] doubles, the moments T with their lattice-to-user scales.
+template <typename T>
+struct ReadoutDst {
+    double* u;
+    T *rho, *j, *P, *sigma;
+    double s_rho, s_j, s_sigma;
+};
+
+// Readout of the current state in one pass, in tiles of R rows of a 62-column
+// strip as the narrow single-step tile: wave w pulls row y0 - 1 + w, leaves
+// its densities in LDS, and after one barrier the R inner waves form grad rho
+// (eq:sourceterm), j + S/2 (eq:moments), P, the Cauchy stress
+// (eq:poissonstress with eq:approxdiv) and the trapezoid displacement, and
+// store what is wanted, scaled and unpadded.  Everything past the pull is in
+// double precision.  Void sites read zero.
+// Bound by HBM: it reads the state once (52 B a site in single precision)
+// and writes each result once.  The earlier chain (density to a padded plane,
+// a second pull into 2 or 11 padded planes, one unpadding pass per plane)
+// moved 200 B for the displacement and 430 B for single-precision moments.
+// 2048^2 plate with holes, fp32, displacement: 96 us against 123; 4096^2,
+// displacement and fp32 moments: 0.65 ms together against 1.55.
+template <typename real, bool PER, typename T>
+__global__ __launch_bounds__(1024) void k_readout(StepArgs<real> a, ReadoutDst<T> d)
 {
+    constexpr int W = strip_width<false>();
+    __shared__ double dens[kMaxTileRows + 2][66];
+    const int tile = xcd_banded(blockIdx.x, gridDim.x);
+    if (tile >= a.ntiles) return;                 // uniform over the workgroup
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int x = (tile % a.nstrips) * W - 1 + lane, y = (tile / a.nstrips) * a.seg - 1 + wave;
     real g[9];
     unsigned fl;
-    fetch_site<real, PER>(a, x, y, g, fl);
-    double gd[9];
-    for (int i = 0; i < 9; ++i) gd[i] = (double)g[i];
-    double d, jx, jy, pxx, pyy, pxy;
-    moments9(gd, d, jx, jy, pxx, pyy, pxy);
-    double gx, gy;
-    grad_rho<PER>(dr, a.flags, x, y, a.nx, a.ny, a.ld, a.px, a.py, gx, gy);
-    const double rho = 1.0 + d;
+    bool in;
+    int ys, s;
+    site_issue<real, PER>(a, x, y, g, fl, ys, in, s);
+    double U0 = 0.0, U1 = 0.0;
+    if (d.u) {
+        U0 = ldu(a.U, s);
+        U1 = ldu(a.U + a.plane, s);
+    }
+    (void)site_finish<real, PER>(a, x, ys, in, true, fl, g);
+    double gd[9], dsum = 0.0;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        gd[i] = (double)g[i];
+        dsum += gd[i];
+    }
+    dens[wave][lane] = dsum;
+    __syncthreads();
+    if (wave < 1 || wave > a.seg || y >= a.ny || x >= a.nx || lane < 1 || lane > 62) return;
+    const size_t n = (size_t)a.nx * a.ny, o = (size_t)y * a.nx + x;
+    const bool live = fl != kVoid;
+    double dr, jx, jy, pxx, pyy, pxy;
+    moments9(gd, dr, jx, jy, pxx, pyy, pxy);
+    double rt[9];
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        const bool ci = (fl >> (i - 1)) & 1u, co = (fl >> (OPP(i) - 1)) & 1u;
+        rt[i] = ci ? (co ? dsum : 2.0 * dsum - dens[wave - CY(i)][lane - CX(i)]) : dens[wave + CY(i)][lane + CX(i)];
+    }
+    const double gx = (1.0 / 3.0) * (rt[1] - rt[3]) + (1.0 / 12.0) * (rt[5] - rt[6] - rt[7] + rt[8]);
+    const double gy = (1.0 / 3.0) * (rt[2] - rt[4]) + (1.0 / 12.0) * (rt[5] + rt[6] - rt[7] - rt[8]);
+    const double rho = 1.0 + dr;
     const double c = (double)a.ml / rho;
     jx += 0.5 * ((double)a.Fx + c * gx);
     jy += 0.5 * ((double)a.Fy + c * gy);
     const double lm = (double)a.lm;
-    o[0] = rho; o[1] = jx; o[2] = jy; o[3] = pxx; o[4] = pyy; o[5] = pxy;
-    o[6] = -pxx - lm * d; o[7] = -pyy - lm * d; o[8] = -pxy;
-    // trapezoid readout: U holds u0 - v0/2 + sum of earlier j/rho
-    o[9] = a.U[idx] + 0.5 * jx / rho;
-    o[10] = a.U[a.plane + idx] + 0.5 * jy / rho;
-}
-
-// Padded planes out[11] (site_outputs; zero where there is no state), or
-// only ux, uy (ncomp 2).
-template <typename real, bool PER>
-__global__ __launch_bounds__(256) void k_outputs(StepArgs<real> a, const double* dr, double* out, int ncomp)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    const long long P = a.plane;
-    if (idx >= P) return;
-    const int y = idx / a.ld - 1, x = idx % a.ld - kPadL;
-    double o[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    if (x >= 0 && x < a.nx && y >= 0 && y < a.ny && a.flags[idx] != kVoid) site_outputs<real, PER>(a, dr, x, y, idx, o);
-    if (ncomp == 11) {
-        for (int c = 0; c < 11; ++c) out[c * P + idx] = o[c];
-    } else {
-        out[idx] = o[9];
-        out[P + idx] = o[10];
+    if (d.u) {
+        // trapezoid readout: U holds u0 - v0/2 + sum of earlier j/rho
+        d.u[o] = live ? U0 + 0.5 * jx / rho : 0.0;
+        d.u[n + o] = live ? U1 + 0.5 * jy / rho : 0.0;
     }
-}
-
-// The displacement straight into an unpadded [2][ny][nx] array (zero where
-// there is no state): the values k_outputs gives, without its padded planes.
-template <typename real, bool PER>
-__global__ __launch_bounds__(256) void k_displacement_out(StepArgs<real> a, const double* dr, double* u)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = a.nx * a.ny;
-    if (idx >= n) return;
-    const int y = idx / a.nx, x = idx - y * a.nx;
-    const int s = sidx(x, y, a.ld);
-    double o[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    if (a.flags[s] != kVoid) site_outputs<real, PER>(a, dr, x, y, s, o);
-    u[idx] = o[9];
-    u[n + idx] = o[10];
-}
-
-// One padded plane into an unpadded, contiguous [ny][nx] array.
-__global__ __launch_bounds__(256) void k_unpad(const double* plane, int nx, int ny, int ld, double* dst)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nx * ny) return;
-    const int y = idx / nx, x = idx - y * nx;
-    dst[idx] = plane[sidx(x, y, ld)];
-}
-
-// Displacement into a caller's unpadded [2][ny][nx] device array.
-__global__ __launch_bounds__(256) void k_unpad_u(const double* out, int nx, int ny, int ld, double* u)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nx * ny) return;
-    const int y = idx / nx, x = idx - y * nx;
-    const long long P = (long long)(ny + 2) * ld;
-    u[idx] = out[sidx(x, y, ld)];
-    u[(long long)nx * ny + idx] = out[P + sidx(x, y, ld)];
-}
-
-// One padded lattice-unit plane, times a unit scale, into a caller's
-// unpadded [ny][nx] device array of doubles or floats.
-template <typename T>
-__global__ __launch_bounds__(256) void k_unpad_scaled(const double* plane, int nx, int ny, int ld, double scale,
-                                                      T* dst)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nx * ny) return;
-    const int y = idx / nx, x = idx - y * nx;
-    dst[idx] = (T)(plane[sidx(x, y, ld)] * scale);
+    if (d.rho) d.rho[o] = (T)(live ? rho * d.s_rho : 0.0);
+    if (d.j) {
+        d.j[o] = (T)(live ? jx * d.s_j : 0.0);
+        d.j[n + o] = (T)(live ? jy * d.s_j : 0.0);
+    }
+    if (d.P) {
+        d.P[o] = (T)(live ? pxx * d.s_sigma : 0.0);
+        d.P[n + o] = (T)(live ? pyy * d.s_sigma : 0.0);
+        d.P[2 * n + o] = (T)(live ? pxy * d.s_sigma : 0.0);
+    }
+    if (d.sigma) {
+        d.sigma[o] = (T)(live ? (-pxx - lm * dr) * d.s_sigma : 0.0);
+        d.sigma[n + o] = (T)(live ? (-pyy - lm * dr) * d.s_sigma : 0.0);
+        d.sigma[2 * n + o] = (T)(live ? -pxy * d.s_sigma : 0.0);
+    }
 }
 
 // ------------------------------------------------------- initial state
@@ -898,34 +871,31 @@ int wait_ready(slbm_s* h)
     return SLBM_OK;
 }
 
-// outputs in lattice units into scratch[1..11]; scratch[0] holds delta-rho
-template <typename real>
-int launch_outputs(slbm_s* h, bool full)
+// Queues a readout of the current state (k_readout) on the plate's stream.
+// Tiles as the single-step kernel's by the plate's size: short ones give a
+// small plate workgroups enough, tall ones cut the two halo rows per tile.
+template <typename real, typename T>
+int launch_readout(slbm_s* h, const ReadoutDst<T>& d)
 {
-    int rc = ensure_scratch(h, full ? 12 : 3);
-    if (rc) return rc;
     StepArgs<real> a = make_args<real>(h, h->cur);
-    const int n = (int)h->plane;
-    const int grid = (n + 255) / 256;
-    double* dr = h->scratch;
-    double* out = h->scratch + h->plane;
-    const int ncomp = full ? 11 : 2;
-    if (h->px || h->py) {
-        hipLaunchKernelGGL((k_density<real, true>), dim3(grid), dim3(256), 0, h->stream, a, dr);
-        hipLaunchKernelGGL((k_outputs<real, true>), dim3(grid), dim3(256), 0, h->stream, a, dr, out, ncomp);
-    } else {
-        hipLaunchKernelGGL((k_density<real, false>), dim3(grid), dim3(256), 0, h->stream, a, dr);
-        hipLaunchKernelGGL((k_outputs<real, false>), dim3(grid), dim3(256), 0, h->stream, a, dr, out, ncomp);
-    }
+    const long long n = (long long)h->nx * h->ny;
+    a.seg = n >= (1LL << 18) ? kMaxTileRows : (n >= (1LL << 14) ? 6 : 2);
+    a.nstrips = (h->nx + strip_width<false>() - 1) / strip_width<false>();
+    a.ntiles = a.nstrips * ((h->ny + a.seg - 1) / a.seg);
+    const dim3 grid((a.ntiles + 7) / 8 * 8), blk(64 * tile_waves<false>(a.seg));
+    if (h->px || h->py)
+        hipLaunchKernelGGL((k_readout<real, true, T>), grid, blk, 0, h->stream, a, d);
+    else
+        hipLaunchKernelGGL((k_readout<real, false, T>), grid, blk, 0, h->stream, a, d);
     HIP_TRY(hipGetLastError());
     return SLBM_OK;
 }
 
-// Readout kernels: full = all moments (11 planes), else the displacement only
-// (2 planes, components 9 and 10 of the full set come first).
-int outputs(slbm_s* h, bool full)
+template <typename T>
+int readout(slbm_s* h, double* u, T* rho, T* j, T* P, T* sigma)
 {
-    return h->precision == SLBM_FP32 ? launch_outputs<float>(h, full) : launch_outputs<double>(h, full);
+    const ReadoutDst<T> d{u, rho, j, P, sigma, h->rho_user, h->rho_user * h->s_v, h->s_sigma};
+    return h->precision == SLBM_FP32 ? launch_readout<float, T>(h, d) : launch_readout<double, T>(h, d);
 }
 
 struct DeviceGuard {
@@ -1274,67 +1244,11 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
     return SLBM_OK;
 }
 
-int copy_out(slbm_s* h, int comp, double scale, double offset, double* dst)
-{
-    // lattice field comp of scratch (after outputs()) -> unpadded host array:
-    // unpadded on the device into scratch plane 0 (the density, no longer
-    // needed once the output kernels ran), then one contiguous copy
-    const int n = h->nx * h->ny;
-    hipLaunchKernelGGL(k_unpad, dim3((n + 255) / 256), dim3(256), 0, h->stream,
-                       (const double*)(h->scratch + (size_t)(1 + comp) * h->plane), h->nx, h->ny, h->ld,
-                       h->scratch);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(dst, h->scratch, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    for (int s = 0; s < n; ++s) dst[s] = h->mask[s] ? dst[s] * scale + offset : 0.0;
-    return SLBM_OK;
-}
-
 }  // namespace
 
-// ------------------------------------------------ readout without allocation
-
-// The density plane slbm_displacement_device_noalloc reads the displacement
-// through: a fixed array in the library's code object, so the call needs no
-// device allocation.  Each device the library runs on holds its own copy
-// (144 MiB) until the process ends; every call on a device shares it.
-constexpr size_t kStaticScratchDoubles = (size_t)18874368;   // 144 MiB of fp64: a 4096 x 4096 plate's padded plane
-static __device__ __align__(256) double scratch[kStaticScratchDoubles];
-
-namespace {
-
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-double* g_scratch_ptr[kMaxDevices] = {};
-
-// The device address of `scratch` on the current device (the host-side name
-// is only a stand-in, not a device address), looked up once per device.
-int static_scratch(int device, double** out)
-{
-    if (device < 0 || device >= kMaxDevices) return fail(SLBM_E_UNSUPPORTED, "device %d beyond %d", device, kMaxDevices);
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (!g_scratch_ptr[device]) {
-        void* p = nullptr;
-        const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !p)
-            return fail(SLBM_E_DEVICE, "address of the static readout scratch: %s", hipGetErrorString(e));
-        g_scratch_ptr[device] = (double*)p;
-    }
-    *out = g_scratch_ptr[device];
-    return SLBM_OK;
-}
-
-template <typename real, bool PER>
-void launch_displacement_noalloc(slbm_s* h, double* dr, double* u)
-{
-    const StepArgs<real> a = make_args<real>(h, h->cur);
-    const int n = h->nx * h->ny;
-    hipLaunchKernelGGL((k_density<real, PER>), dim3((int)((h->plane + 255) / 256)), dim3(256), 0, h->stream, a, dr);
-    hipLaunchKernelGGL((k_displacement_out<real, PER>), dim3((n + 255) / 256), dim3(256), 0, h->stream, a,
-                       (const double*)dr, u);
-}
-
-}  // namespace
+// slbm_displacement_device_noalloc takes plates of up to this many padded
+// sites (a 4096 x 4096 plate's).
+constexpr size_t kNoallocSites = (size_t)18874368;
 
 // ------------------------------------------------------------------ ABI
 
@@ -1406,18 +1320,19 @@ int slbm_moments(slbm_handle h, double* rho, double* j, double* P, double* sigma
         if (!h) return fail(SLBM_E_INVAL, "null handle");
         DeviceGuard dg(h->device);
         if (int rw = wait_ready(h)) return rw;
-        int rc = outputs(h, true);
+        int rc = ensure_scratch(h, 9);
         if (rc) return rc;
         const size_t n = (size_t)h->nx * h->ny;
-        const double sj = h->rho_user * h->s_v;
-        if (rho && (rc = copy_out(h, 0, h->rho_user, 0.0, rho))) return rc;
-        if (j && ((rc = copy_out(h, 1, sj, 0.0, j)) || (rc = copy_out(h, 2, sj, 0.0, j + n)))) return rc;
-        if (P && ((rc = copy_out(h, 3, h->s_sigma, 0.0, P)) || (rc = copy_out(h, 4, h->s_sigma, 0.0, P + n)) ||
-                  (rc = copy_out(h, 5, h->s_sigma, 0.0, P + 2 * n))))
+        double* q = h->scratch;                    // rho, j, P, sigma, those wanted, unpadded
+        if ((rc = readout<double>(h, nullptr, rho ? q : nullptr, j ? q + n : nullptr, P ? q + 3 * n : nullptr,
+                                  sigma ? q + 6 * n : nullptr)))
             return rc;
-        if (sigma && ((rc = copy_out(h, 6, h->s_sigma, 0.0, sigma)) || (rc = copy_out(h, 7, h->s_sigma, 0.0, sigma + n)) ||
-                      (rc = copy_out(h, 8, h->s_sigma, 0.0, sigma + 2 * n))))
-            return rc;
+        const struct { double* dst; size_t first, count; } part[4] = {{rho, 0, 1}, {j, 1, 2}, {P, 3, 3}, {sigma, 6, 3}};
+        for (const auto& pt : part)
+            if (pt.dst)
+                HIP_TRY(hipMemcpyAsync(pt.dst, q + pt.first * n, pt.count * n * sizeof(double), hipMemcpyDeviceToHost,
+                                       h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
         release_transient_scratch(h);
         return SLBM_OK;
     });
@@ -1429,10 +1344,12 @@ int slbm_displacement(slbm_handle h, double* u)
         if (!h || !u) return fail(SLBM_E_INVAL, "null argument");
         DeviceGuard dg(h->device);
         if (int rw = wait_ready(h)) return rw;
-        int rc = outputs(h, false);
+        int rc = ensure_scratch(h, 2);
         if (rc) return rc;
         const size_t n = (size_t)h->nx * h->ny;
-        if ((rc = copy_out(h, 0, 1.0, 0.0, u)) || (rc = copy_out(h, 1, 1.0, 0.0, u + n))) return rc;
+        if ((rc = readout<double>(h, h->scratch, nullptr, nullptr, nullptr, nullptr))) return rc;
+        HIP_TRY(hipMemcpyAsync(u, h->scratch, 2 * n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
         release_transient_scratch(h);
         return SLBM_OK;
     });
@@ -1444,14 +1361,7 @@ int slbm_displacement_device(slbm_handle h, void* u_dev)
         if (!h || !u_dev) return fail(SLBM_E_INVAL, "null argument");
         DeviceGuard dg(h->device);
         if (int rw = wait_ready(h)) return rw;
-        int rc = outputs(h, false);
-        if (rc) return rc;
-        const int n = h->nx * h->ny;
-        hipLaunchKernelGGL(k_unpad_u, dim3((n + 255) / 256), dim3(256), 0, h->stream,
-                           (const double*)(h->scratch + h->plane), h->nx, h->ny, h->ld, (double*)u_dev);
-        HIP_TRY(hipGetLastError());
-        release_transient_scratch(h);
-        return SLBM_OK;
+        return readout<double>(h, (double*)u_dev, nullptr, nullptr, nullptr, nullptr);
     });
 }
 
@@ -1459,22 +1369,12 @@ int slbm_displacement_device_noalloc(slbm_handle h, void* u_dev)
 {
     return guarded([&]() -> int {
         if (!h || !u_dev) return fail(SLBM_E_INVAL, "null argument");
-        if ((size_t)h->plane > kStaticScratchDoubles)
-            return fail(SLBM_E_INVAL, "padded plane of %lld sites exceeds the static readout scratch of %zu sites",
-                        (long long)h->plane, kStaticScratchDoubles);
+        if ((size_t)h->plane > kNoallocSites)
+            return fail(SLBM_E_INVAL, "padded plane of %lld sites exceeds the limit of %zu sites (a static readout scratch's)",
+                        (long long)h->plane, kNoallocSites);
         DeviceGuard dg(h->device);
         if (int rw = wait_ready(h)) return rw;
-        double* dr = nullptr;
-        if (int rc = static_scratch(h->device, &dr)) return rc;
-        const bool per = h->px || h->py;
-        if (h->precision == SLBM_FP32)
-            per ? launch_displacement_noalloc<float, true>(h, dr, (double*)u_dev)
-                : launch_displacement_noalloc<float, false>(h, dr, (double*)u_dev);
-        else
-            per ? launch_displacement_noalloc<double, true>(h, dr, (double*)u_dev)
-                : launch_displacement_noalloc<double, false>(h, dr, (double*)u_dev);
-        HIP_TRY(hipGetLastError());
-        return SLBM_OK;
+        return readout<double>(h, (double*)u_dev, nullptr, nullptr, nullptr, nullptr);
     });
 }
 
@@ -1485,28 +1385,9 @@ int slbm_moments_device(slbm_handle h, void* rho, void* j, void* P, void* sigma,
         if (dtype != SLBM_FP64 && dtype != SLBM_FP32) return fail(SLBM_E_INVAL, "dtype must be SLBM_FP64 or SLBM_FP32");
         DeviceGuard dg(h->device);
         if (int rw = wait_ready(h)) return rw;
-        int rc = outputs(h, true);
-        if (rc) return rc;
-        const int n = h->nx * h->ny;
-        const double sj = h->rho_user * h->s_v;
-        // output components (as in slbm_moments): 0 rho, 1-2 j, 3-5 P, 6-8 sigma
-        const struct { void* dst; int first, count; double scale; } part[4] = {
-            {rho, 0, 1, h->rho_user}, {j, 1, 2, sj}, {P, 3, 3, h->s_sigma}, {sigma, 6, 3, h->s_sigma}};
-        for (const auto& pt : part) {
-            if (!pt.dst) continue;
-            for (int c = 0; c < pt.count; ++c) {
-                const double* src = h->scratch + (size_t)(1 + pt.first + c) * h->plane;
-                if (dtype == SLBM_FP64)
-                    hipLaunchKernelGGL(k_unpad_scaled<double>, dim3((n + 255) / 256), dim3(256), 0, h->stream, src,
-                                       h->nx, h->ny, h->ld, pt.scale, (double*)pt.dst + (size_t)c * n);
-                else
-                    hipLaunchKernelGGL(k_unpad_scaled<float>, dim3((n + 255) / 256), dim3(256), 0, h->stream, src,
-                                       h->nx, h->ny, h->ld, pt.scale, (float*)pt.dst + (size_t)c * n);
-            }
-        }
-        HIP_TRY(hipGetLastError());
-        release_transient_scratch(h);
-        return SLBM_OK;
+        if (dtype == SLBM_FP64)
+            return readout<double>(h, nullptr, (double*)rho, (double*)j, (double*)P, (double*)sigma);
+        return readout<float>(h, nullptr, (float*)rho, (float*)j, (float*)P, (float*)sigma);
     });
 }
 

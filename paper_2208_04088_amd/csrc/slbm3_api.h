@@ -30,7 +30,8 @@ struct slbm3_s {
     double* U = nullptr;
     void* dens = nullptr;
     unsigned int* diverged = nullptr;
-    double* scratch = nullptr;       // 19 planes of doubles, on demand (outputs, initial fields)
+    double* scratch = nullptr;       // planes of doubles, on demand (host readouts, initial fields)
+    int scratch_planes = 0;
     int64_t step = 0;
     // general geometry: site flags, first link record of each site, records
     bool geo = false;
@@ -420,29 +421,34 @@ int grid3(const slbm3_s* h)
 }
 
 // The extrapolating rules (general geometry, GEO, which implies PX; the other
-// cut links' parts come from the previous k3_step), density pass, then
-// `what` (0 step, 1 outputs into scratch, 2 init from scratch).
+// cut links' parts come from the previous k3_step), read by both pulls, and
+// the density pass, which a step or a readout follows.
+template <typename real, bool PX, bool GEO>
+Step3Args<real> launch3_density(slbm3_s* h)
+{
+    const Step3Args<real> a = make_args3<real>(h, h->cur);
+    if (GEO && !h->local && h->n_ext > 0)
+        hipLaunchKernelGGL((k3_links_ext<real>), dim3((unsigned)((h->n_ext + 255) / 256)), dim3(256), 0, h->stream, a,
+                           (const int32_t*)h->elink, (int)h->n_ext);
+    hipLaunchKernelGGL((k3_density<real, PX, GEO>), dim3(grid3(h)), dim3(256), 0, h->stream, a);
+    return a;
+}
+
+// `what`: 0 step, 2 init from scratch.
 template <typename real, bool PX, bool GEO>
 int launch3(slbm3_s* h, int what)
 {
-    Step3Args<real> a = make_args3<real>(h, h->cur);
     const dim3 grid(grid3(h)), blk(256);
     if (what == 2) {
+        Step3Args<real> a = make_args3<real>(h, h->cur);
         a.dst = (real*)h->buf[h->cur];
         hipLaunchKernelGGL((k3_set_dens<real>), dim3((unsigned)((h->plane + 255) / 256)), blk, 0, h->stream, a,
                            (const double*)h->scratch);
         hipLaunchKernelGGL((k3_init<real, PX, GEO>), grid, blk, 0, h->stream, a, (const double*)h->scratch);
-        HIP_TRY(hipGetLastError());
-        return SLBM_OK;
-    }
-    if (GEO && !h->local && h->n_ext > 0)            // the extrapolating rules, read by both pulls
-        hipLaunchKernelGGL((k3_links_ext<real>), dim3((unsigned)((h->n_ext + 255) / 256)), blk, 0, h->stream, a,
-                           (const int32_t*)h->elink, (int)h->n_ext);
-    hipLaunchKernelGGL((k3_density<real, PX, GEO>), grid, blk, 0, h->stream, a);
-    if (what == 0)
+    } else {
+        const Step3Args<real> a = launch3_density<real, PX, GEO>(h);
         hipLaunchKernelGGL((k3_step<real, PX, GEO>), grid, blk, 0, h->stream, a);
-    else
-        hipLaunchKernelGGL((k3_outputs<real, PX, GEO>), grid, blk, 0, h->stream, a, h->scratch);
+    }
     HIP_TRY(hipGetLastError());
     return SLBM_OK;
 }
@@ -457,10 +463,37 @@ int launch3_any(slbm3_s* h, int what)
     return h->px ? launch3<double, true, false>(h, what) : launch3<double, false, false>(h, what);
 }
 
-int ensure_scratch3(slbm3_s* h)
+// A readout of the current state: the density pass, then the wanted fields.
+template <typename real, bool PX, bool GEO, typename T>
+int launch3_readout(slbm3_s* h, const Readout3Dst<T>& d)
 {
-    if (h->scratch) return SLBM_OK;
-    HIP_TRY(hipMalloc((void**)&h->scratch, (size_t)19 * h->plane * sizeof(double)));
+    const Step3Args<real> a = launch3_density<real, PX, GEO>(h);
+    hipLaunchKernelGGL((k3_readout<real, PX, GEO, T>), dim3(grid3(h)), dim3(256), 0, h->stream, a, d);
+    HIP_TRY(hipGetLastError());
+    return SLBM_OK;
+}
+
+template <typename T>
+int readout3(slbm3_s* h, double* u, T* rho, T* j, T* P, T* sigma)
+{
+    const Readout3Dst<T> d{u, rho, j, P, sigma, h->rho_user, h->rho_user * h->s_v, h->s_sigma};
+    if (h->precision == SLBM_FP32) {
+        if (h->geo) return launch3_readout<float, true, true, T>(h, d);
+        return h->px ? launch3_readout<float, true, false, T>(h, d) : launch3_readout<float, false, false, T>(h, d);
+    }
+    if (h->geo) return launch3_readout<double, true, true, T>(h, d);
+    return h->px ? launch3_readout<double, true, false, T>(h, d) : launch3_readout<double, false, false, T>(h, d);
+}
+
+// At least `planes` planes of device doubles for initial fields and host readouts.
+int ensure_scratch3(slbm3_s* h, int planes)
+{
+    if (h->scratch_planes >= planes) return SLBM_OK;
+    if (h->scratch) (void)hipFree(h->scratch);
+    h->scratch = nullptr;
+    h->scratch_planes = 0;
+    HIP_TRY(hipMalloc((void**)&h->scratch, (size_t)planes * h->plane * sizeof(double)));
+    h->scratch_planes = planes;
     return SLBM_OK;
 }
 
@@ -470,29 +503,6 @@ void free3(slbm3_s* h)
                     (void*)h->flags, (void*)h->bidx, h->links, h->lval, (void*)h->wrec, (void*)h->elink})
         if (p) (void)hipFree(p);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
-}
-
-// count consecutive output planes, x -> (x + add) * scale (lattice to user
-// units, as copy_planes3), into caller device memory of doubles or floats
-// (the planes are contiguous in both).
-template <typename T>
-__global__ __launch_bounds__(256) void k3_scale_out(const double* src, long long n, double add, double scale, T* dst)
-{
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = (T)((src[i] + add) * scale);
-}
-
-int device_planes3(slbm3_handle h, int first, int count, double add, double scale, void* dst, int dtype)
-{
-    const long long n = (long long)count * h->plane;
-    const double* src = h->scratch + (size_t)first * (size_t)h->plane;
-    const dim3 grid((unsigned)((n + 255) / 256)), blk(256);
-    if (dtype == SLBM_FP64)
-        hipLaunchKernelGGL(k3_scale_out<double>, grid, blk, 0, h->stream, src, n, add, scale, (double*)dst);
-    else
-        hipLaunchKernelGGL(k3_scale_out<float>, grid, blk, 0, h->stream, src, n, add, scale, (float*)dst);
-    HIP_TRY(hipGetLastError());
-    return SLBM_OK;
 }
 
 }  // namespace
@@ -665,7 +675,7 @@ int slbm3_init_fields(slbm3_handle h, const double* rho, const double* vel, cons
     return guarded([&]() -> int {
         if (!h) return fail(SLBM_E_INVAL, "null handle");
         DeviceGuard dg(h->device);
-        int rc = ensure_scratch3(h);
+        int rc = ensure_scratch3(h, 13);
         if (rc) return rc;
         const long long n = h->plane;
         // lattice units on the host: delta-rho, j = rho v, P = -sigma - (lambda - mu) drho I, u0
@@ -724,39 +734,24 @@ int slbm3_sync(slbm3_handle h)
     });
 }
 
-// Outputs of the current state (lattice units) into the device scratch
-// planes, laid out as k3_outputs writes them.
-static int outputs3(slbm3_handle h)
-{
-    int rc = ensure_scratch3(h);
-    if (rc) return rc;
-    return launch3_any(h, 1);
-}
-
-// Planes [first, first + count) of the output scratch into a host array (x
-// fastest), then x -> (x + add) * scale (lattice to user units).
-static int copy_planes3(slbm3_handle h, int first, int count, double add, double scale, double* dst)
-{
-    const size_t n = (size_t)count * (size_t)h->plane;
-    HIP_TRY(hipMemcpyAsync(dst, h->scratch + (size_t)first * (size_t)h->plane, n * sizeof(double),
-                           hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    if (add != 0.0 || scale != 1.0)
-        for (size_t s = 0; s < n; ++s) dst[s] = (dst[s] + add) * scale;
-    return SLBM_OK;
-}
-
 int slbm3_moments(slbm3_handle h, double* rho, double* j, double* P, double* sigma)
 {
     return guarded([&]() -> int {
         if (!h) return fail(SLBM_E_INVAL, "null handle");
         DeviceGuard dg(h->device);
-        int rc = outputs3(h);
+        int rc = ensure_scratch3(h, 16);
         if (rc) return rc;
-        if (rho && (rc = copy_planes3(h, 0, 1, 1.0, h->rho_user, rho))) return rc;
-        if (j && (rc = copy_planes3(h, 1, 3, 0.0, h->rho_user * h->s_v, j))) return rc;
-        if (P && (rc = copy_planes3(h, 4, 6, 0.0, h->s_sigma, P))) return rc;
-        if (sigma && (rc = copy_planes3(h, 10, 6, 0.0, h->s_sigma, sigma))) return rc;
+        const size_t n = (size_t)h->plane;
+        double* q = h->scratch;                    // rho, j, P, sigma, those wanted
+        if ((rc = readout3<double>(h, nullptr, rho ? q : nullptr, j ? q + n : nullptr, P ? q + 4 * n : nullptr,
+                                   sigma ? q + 10 * n : nullptr)))
+            return rc;
+        const struct { double* dst; size_t first, count; } part[4] = {{rho, 0, 1}, {j, 1, 3}, {P, 4, 6}, {sigma, 10, 6}};
+        for (const auto& pt : part)
+            if (pt.dst)
+                HIP_TRY(hipMemcpyAsync(pt.dst, q + pt.first * n, pt.count * n * sizeof(double), hipMemcpyDeviceToHost,
+                                       h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
         return SLBM_OK;
     });
 }
@@ -766,9 +761,12 @@ int slbm3_displacement(slbm3_handle h, double* u)
     return guarded([&]() -> int {
         if (!h || !u) return fail(SLBM_E_INVAL, "null argument");
         DeviceGuard dg(h->device);
-        int rc = outputs3(h);
+        int rc = ensure_scratch3(h, 3);
         if (rc) return rc;
-        return copy_planes3(h, 16, 3, 0.0, 1.0, u);
+        if ((rc = readout3<double>(h, h->scratch, nullptr, nullptr, nullptr, nullptr))) return rc;
+        HIP_TRY(hipMemcpyAsync(u, h->scratch, (size_t)3 * h->plane * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
+        return SLBM_OK;
     });
 }
 
@@ -777,9 +775,7 @@ int slbm3_displacement_device(slbm3_handle h, void* u_dev)
     return guarded([&]() -> int {
         if (!h || !u_dev) return fail(SLBM_E_INVAL, "null argument");
         DeviceGuard dg(h->device);
-        int rc = outputs3(h);
-        if (rc) return rc;
-        return device_planes3(h, 16, 3, 0.0, 1.0, u_dev, SLBM_FP64);
+        return readout3<double>(h, (double*)u_dev, nullptr, nullptr, nullptr, nullptr);
     });
 }
 
@@ -789,13 +785,9 @@ int slbm3_moments_device(slbm3_handle h, void* rho, void* j, void* P, void* sigm
         if (!h) return fail(SLBM_E_INVAL, "null handle");
         if (dtype != SLBM_FP64 && dtype != SLBM_FP32) return fail(SLBM_E_INVAL, "dtype must be SLBM_FP64 or SLBM_FP32");
         DeviceGuard dg(h->device);
-        int rc = outputs3(h);
-        if (rc) return rc;
-        if (rho && (rc = device_planes3(h, 0, 1, 1.0, h->rho_user, rho, dtype))) return rc;
-        if (j && (rc = device_planes3(h, 1, 3, 0.0, h->rho_user * h->s_v, j, dtype))) return rc;
-        if (P && (rc = device_planes3(h, 4, 6, 0.0, h->s_sigma, P, dtype))) return rc;
-        if (sigma && (rc = device_planes3(h, 10, 6, 0.0, h->s_sigma, sigma, dtype))) return rc;
-        return SLBM_OK;
+        if (dtype == SLBM_FP64)
+            return readout3<double>(h, nullptr, (double*)rho, (double*)j, (double*)P, (double*)sigma);
+        return readout3<float>(h, nullptr, (float*)rho, (float*)j, (float*)P, (float*)sigma);
     });
 }
 
@@ -814,7 +806,7 @@ int slbm3_device_bytes(slbm3_handle h, int64_t* bytes)
     return guarded([&]() -> int {
         if (!h || !bytes) return fail(SLBM_E_INVAL, "null argument");
         int64_t b = 2 * (int64_t)19 * h->stride * (int64_t)h->esize + 3 * h->stride * 8 + h->plane * (int64_t)h->esize;
-        if (h->scratch) b += (int64_t)19 * h->plane * 8;
+        b += (int64_t)h->scratch_planes * h->plane * 8;
         if (h->geo) {
             const long long nwg = (((long long)(h->nx + 63) / 64) * h->ny * h->nz + 3) / 4;
             b += h->plane * 8 + (int64_t)h->link_bytes + 2 * h->n_links * (int64_t)h->esize + (nwg + 1) * 4 +

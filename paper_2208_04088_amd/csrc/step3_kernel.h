@@ -724,12 +724,26 @@ __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
     }
 }
 
-// Outputs at every site (lattice units, double, planes of `out`): 0
-// delta-rho, 1-3 j (with S/2), 4-9 P, 10-15 the Cauchy stress
-// sigma = -P - (lambda - mu) drho I, 16-18 the displacement U + (j/rho)/2.
-// Needs k3_density of the same state first.
-template <typename real, bool PX, bool GEO = false>
-__global__ __launch_bounds__(256) void k3_outputs(Step3Args<real> a, double* out)
+// Where a readout goes: arrays of the caller (null: not wanted), u [3][n]
+// doubles, the moments T with their lattice-to-user scales.
+template <typename T>
+struct Readout3Dst {
+    double* u;
+    T *rho, *j, *P, *sigma;
+    double s_rho, s_j, s_sigma;
+};
+
+// Readout at every site: rho, j (with S/2), P, the Cauchy stress
+// sigma = -P - (lambda - mu) drho I and the displacement U + (j/rho)/2, what
+// is wanted of them, scaled and stored where the caller wants it.  Needs
+// k3_density of the same state first.  Void sites read zero.
+// Bound by HBM: after the density pass it reads the pulls (and U for the
+// displacement) once and writes each result once; the earlier chain wrote all
+// 19 planes in double precision and scaled the wanted ones in a second pass.
+// 256^3 slab, fp32, displacement: 0.44 ms against 1.00 (density pass apart);
+// 256^3 porous solid, fp32 moments: 0.49 against 1.48.
+template <typename real, bool PX, bool GEO, typename T>
+__global__ __launch_bounds__(256) void k3_readout(Step3Args<real> a, Readout3Dst<T> d)
 {
     const int tile = xcd_group3<GEO>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (tile >= a.ntiles) return;
@@ -745,21 +759,21 @@ __global__ __launch_bounds__(256) void k3_outputs(Step3Args<real> a, double* out
     const real c = a.ml / rho;
     if (!st.in) return;
     const unsigned s = sidx3(st.x, st.y, st.z, a.nx, a.ny);
-    const long long n = a.plane;
-    if (GEO && (fl & kVoid3)) {                             // void sites report zeros (rho too)
-        out[s] = -1.0;
-        for (int k = 1; k < 19; ++k) out[k * n + s] = 0.0;
-        return;
-    }
-    out[s] = (double)dr;
+    const size_t n = (size_t)a.plane;
+    const bool live = !(GEO && (fl & kVoid3));              // void sites report zeros (rho too)
+    if (d.rho) d.rho[s] = (T)(live ? ((double)dr + 1.0) * d.s_rho : 0.0);
+#pragma unroll
     for (int k = 0; k < 3; ++k) {
         const double jk = (double)j[k] + 0.5 * ((double)a.F[k] + (double)c * (double)grad[k]);
-        out[(1 + k) * n + s] = jk;
-        out[(16 + k) * n + s] = a.U[k * a.stride + s] + 0.5 * jk / (double)rho;
+        if (d.j) d.j[k * n + s] = (T)(live ? jk * d.s_j : 0.0);
+        if (d.u) d.u[k * n + s] = live ? a.U[k * a.stride + s] + 0.5 * jk / (double)rho : 0.0;
     }
+#pragma unroll
     for (int k = 0; k < 6; ++k) {
-        out[(4 + k) * n + s] = (double)P[k];
-        out[(10 + k) * n + s] = -(double)P[k] - (k < 3 ? (double)a.lm * (double)dr : 0.0);
+        if (d.P) d.P[k * n + s] = (T)(live ? (double)P[k] * d.s_sigma : 0.0);
+        if (d.sigma)
+            d.sigma[k * n + s] =
+                (T)(live ? (-(double)P[k] - (k < 3 ? (double)a.lm * (double)dr : 0.0)) * d.s_sigma : 0.0);
     }
 }
 

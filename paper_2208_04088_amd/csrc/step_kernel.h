@@ -333,27 +333,6 @@ __device__ __forceinline__ GlobalPrev<real, PER> global_prev(const StepArgs<real
     return GlobalPrev<real, PER>{a.src, a.plane, x, y, a.nx, a.ny, a.ld, a.px, a.py};
 }
 
-// Populations at site (x, y) for the current step (x, y in the grid, wrapped
-// by the caller on periodic axes).  Returns false for sites without state.
-template <typename real, bool PER>
-__device__ __forceinline__ bool fetch_site(const StepArgs<real>& a, int x, int y, real g[9], unsigned& flo)
-{
-    const int s = sidx(x, y, a.ld);
-    const unsigned fl = ldu(a.flags, s);
-    flo = fl;
-    if (fl == kVoid) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = real(0);
-        return false;
-    }
-#pragma unroll
-    for (int i = 0; i < 9; ++i)
-        g[i] = a.local ? ldu(a.src + i * a.plane, s)
-                       : ldu(a.src + i * a.plane, wrap_off<PER>(x, y, -CX(i), -CY(i), a.nx, a.ny, a.ld, a.px, a.py));
-    if (!a.local && fl != 0) boundary_fixup<real>(a, global_prev<real, PER>(a, x, y), s, fl, a.t_prev, g);
-    return true;
-}
-
 // Site coordinates of a row or halo site: wrapped on periodic axes (any
 // distance: tiles reach up to three sites past a plate narrower than that),
 // clamped into the grid otherwise -- so that every pull address stays in the

@@ -232,9 +232,8 @@ class Solver:
         _check(lib().slbm_displacement_device(self.h, C.c_void_p(int(ptr))))
 
     def displacement_device_noalloc(self, ptr):
-        """As displacement_device, with no device allocation: the density
-        scratch is the library's static per-device array (plates up to
-        4096 x 4096; overlapping calls on one device race)."""
+        """As displacement_device, with no device allocation (plates up to
+        4096 x 4096)."""
         _check(lib().slbm_displacement_device_noalloc(self.h, C.c_void_p(int(ptr))))
 
     def moments_device(self, rho=0, j=0, P=0, sigma=0, dtype="fp64"):
