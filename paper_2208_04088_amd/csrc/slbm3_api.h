@@ -29,6 +29,9 @@ struct slbm3_s {
     bool local = true;
     double* U = nullptr;
     void* dens = nullptr;
+    void* wall[2] = {nullptr, nullptr};   // the walls' parts (wall_parts3): k3_march reads [wcur], writes the other
+    int wcur = 0;
+    bool wall_fresh = false;              // wall[wcur] belongs to the current state
     unsigned int* diverged = nullptr;
     double* scratch = nullptr;       // planes of doubles, on demand (host readouts, initial fields)
     int scratch_planes = 0;
@@ -85,7 +88,11 @@ Step3Args<real> make_args3(const slbm3_s* h, int src)
         a.wq1[s] = (real)(1.0 + q);
         a.wq[s] = (real)q;
         a.wext[s] = behind && h->norder == 1 && h->wkind[s] == SLBM_NEUMANN ? 1 : 0;
+        a.wskap[s] = h->wkind[s] == SLBM_DIRICHLET ? a.wkap[s] : -a.wkap[s];
+        for (int k = 0; k < 3; ++k) a.wval_next[s][k] = (real)(h->wval[s][k] * ramp(n_next, h->wramp[s]));
     }
+    a.wsrc = (const real*)h->wall[h->wcur];
+    a.wdst = (real*)h->wall[h->wcur ^ 1];
     a.omega = (real)(1.0 / h->tau);
     a.omega_h = (real)(1.0 - 0.5 / h->tau);
     a.ml = (real)(h->muL - h->lamL);
@@ -453,6 +460,78 @@ int launch3(slbm3_s* h, int what)
     return SLBM_OK;
 }
 
+int launch3_any(slbm3_s* h, int what);
+
+// Whether k3_march takes the next step.  Not a state that is read in place
+// (the first step after creation or initial fields), not cut links, not walls
+// whose Neumann data are extrapolated (they read a second site) or that share
+// one site.  And only boxes large enough: below, a workgroup's few planes in
+// series (2.6 us each in single, 5 us in double precision) take longer than
+// the two launches, whose every load is independent.  us per step, two
+// launches and one:
+//   fp32 slab  64^3 21 24   200x60x40 29 34   90x130x70 51 48   96^3 56 47   128^3 133 103   256^3 905 701
+//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 38 40   96^3 40 37   128^3 113 98    256^3 901 689
+//   fp64 slab  40^3 19 20   64^3 35 28        90x130x70 97 90   96^3 108 84  128^3 254 179
+//   fp64 per.  40^3 14 16   64^3 25 22        90x130x70 73 87   96^3 85 80   128^3 223 174   256^3 1682 1259
+bool march3(const slbm3_s* h)
+{
+    if (h->local || h->geo) return false;
+    if (!h->px) {
+        if (h->nx < 2) return false;
+        for (int s = 0; s < 2; ++s)
+            if (h->norder == 1 && h->wkind[s] == SLBM_NEUMANN) return false;
+    }
+    return h->plane >= (h->px ? 850000 : (h->precision == SLBM_FP32 ? 800000 : 250000));
+}
+
+// Planes a k3_march workgroup marches through, for `tiles` tiles of rows over
+// nz planes: a workgroup takes depth + 2 planes' time and a little to start,
+// and the chip runs `slots` of them at once, so the depth that needs the
+// fewest plane times in whole rounds.
+int march_depth(long long tiles, int nz, int slots)
+{
+    int best = 1;
+    long long cost = -1;
+    for (int d = 1; d <= std::min(nz, 64); ++d) {
+        const long long wgs = tiles * ((nz + d - 1) / d), c = (wgs + slots - 1) / slots * (d + 3);
+        if (cost < 0 || c < cost) { cost = c; best = d; }
+    }
+    return best;
+}
+
+template <typename real, bool PX>
+int launch3_march(slbm3_s* h)
+{
+    Step3Args<real> a = make_args3<real>(h, h->cur);
+    a.rows = std::min(kMarchWaves(sizeof(real)) - 2, h->ny);
+    a.nch = (h->nx + 63) / 64;
+    a.nyt = (h->ny + a.rows - 1) / a.rows;
+    a.depth = march_depth((long long)a.nch * a.nyt, h->nz, sizeof(real) == 4 ? 512 : 256);
+    a.mtiles = a.nch * a.nyt * ((h->nz + a.depth - 1) / a.depth);
+    a.xgroup = 8;
+    if (!PX && !h->wall_fresh)
+        hipLaunchKernelGGL((k3_wall_parts<real>), dim3((unsigned)((h->ny * h->nz + 255) / 256), 2), dim3(256), 0,
+                           h->stream, a, (real*)h->wall[h->wcur]);
+    hipLaunchKernelGGL((k3_march<real, PX>), dim3((unsigned)((a.mtiles + 8 * a.xgroup - 1) / (8 * a.xgroup) * (8 * a.xgroup))), dim3(64 * (a.rows + 2)), 0,
+                       h->stream, a);
+    HIP_TRY(hipGetLastError());
+    if (!PX) {
+        h->wcur ^= 1;
+        h->wall_fresh = true;
+    }
+    return SLBM_OK;
+}
+
+int step3(slbm3_s* h)
+{
+    if (!march3(h)) {
+        h->wall_fresh = false;
+        return launch3_any(h, 0);
+    }
+    if (h->precision == SLBM_FP32) return h->px ? launch3_march<float, true>(h) : launch3_march<float, false>(h);
+    return h->px ? launch3_march<double, true>(h) : launch3_march<double, false>(h);
+}
+
 int launch3_any(slbm3_s* h, int what)
 {
     if (h->precision == SLBM_FP32) {
@@ -500,7 +579,8 @@ int ensure_scratch3(slbm3_s* h, int planes)
 void free3(slbm3_s* h)
 {
     for (void* p : {h->buf[0], h->buf[1], (void*)h->U, h->dens, (void*)h->diverged, (void*)h->scratch,
-                    (void*)h->flags, (void*)h->bidx, h->links, h->lval, (void*)h->wrec, (void*)h->elink})
+                    (void*)h->flags, (void*)h->bidx, h->links, h->lval, (void*)h->wrec, (void*)h->elink, h->wall[0],
+                    h->wall[1]})
         if (p) (void)hipFree(p);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
@@ -602,6 +682,8 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
         TRY_OR_BAIL(hipMalloc((void**)&h->U, (size_t)3 * h->stride * sizeof(double)));
         TRY_OR_BAIL(hipMalloc(&h->dens, (size_t)plane * h->esize));
         TRY_OR_BAIL(hipMalloc((void**)&h->diverged, sizeof(unsigned int)));
+        if (!h->px)
+            for (void*& w : h->wall) TRY_OR_BAIL(hipMalloc(&w, (size_t)10 * h->ny * h->nz * h->esize));
         // rest state: g = 0 (f = r), U = 0
         TRY_OR_BAIL(hipMemsetAsync(h->buf[0], 0, pop, h->stream));
         TRY_OR_BAIL(hipMemsetAsync(h->buf[1], 0, pop, h->stream));
@@ -699,6 +781,7 @@ int slbm3_init_fields(slbm3_handle h, const double* rho, const double* vel, cons
         HIP_TRY(hipMemsetAsync(h->diverged, 0, sizeof(unsigned int), h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         h->local = true;
+        h->wall_fresh = false;
         h->step = 0;
         return SLBM_OK;
     });
@@ -711,7 +794,7 @@ int slbm3_step(slbm3_handle h, int64_t nsteps)
         if (nsteps < 0) return fail(SLBM_E_INVAL, "negative step count");
         DeviceGuard dg(h->device);
         for (int64_t k = 0; k < nsteps; ++k) {
-            int rc = launch3_any(h, 0);
+            int rc = step3(h);
             if (rc) return rc;
             h->cur ^= 1;
             h->local = false;
@@ -807,6 +890,7 @@ int slbm3_device_bytes(slbm3_handle h, int64_t* bytes)
         if (!h || !bytes) return fail(SLBM_E_INVAL, "null argument");
         int64_t b = 2 * (int64_t)19 * h->stride * (int64_t)h->esize + 3 * h->stride * 8 + h->plane * (int64_t)h->esize;
         b += (int64_t)h->scratch_planes * h->plane * 8;
+        if (!h->px) b += (int64_t)2 * 10 * h->ny * h->nz * (int64_t)h->esize;
         if (h->geo) {
             const long long nwg = (((long long)(h->nx + 63) / 64) * h->ny * h->nz + 3) / 4;
             b += h->plane * 8 + (int64_t)h->link_bytes + 2 * h->n_links * (int64_t)h->esize + (nwg + 1) * 4 +
@@ -888,6 +972,7 @@ int slbm3_load(slbm3_handle h, const void* buf, size_t bytes)
         HIP_TRY(hipStreamSynchronize(h->stream));
         h->step = hd.step;
         h->local = hd.local != 0;
+        h->wall_fresh = false;
         return SLBM_OK;
     });
 }

@@ -15,8 +15,8 @@
 // State: shifted post-collision populations g = f - r (r the rest state),
 // SoA planes g[i][z][y][x], site offset (z ny + y) nx + x; consecutive planes
 // are `stride` elements apart, a little more than a plane, so that the 19
-// streams of a pull do not all start on the same HBM channel.  One step is two
-// launches: k3_density (delta-rho of the pulled state, needed by the
+// streams of a pull do not all start on the same HBM channel.  A step of a
+// large box without cut links is one launch, k3_march; of any other two: k3_density (delta-rho of the pulled state, needed by the
 // gradient stencil of every neighbour) and k3_step (pull with the rules,
 // moments, source term, collision, U, store; with a general geometry also
 // the next step's rule values at the cut links), and with extrapolating
@@ -115,6 +115,13 @@ struct Step3Args {
     // the groups' time profiles per slot, at the time of the state the pulls
     // read (pf_pull) and of the state the step produces (pf_next)
     real pf_pull[kProfileSlots3], pf_next[kProfileSlots3];
+    // k3_march: its tiles (rows, planes, how many of each, 64-site chunks), the
+    // walls' returned parts it reads and writes (see wall_parts3) and the
+    // walls' values at the time of the state it produces
+    int rows, depth, nyt, nch, mtiles, xgroup;
+    const real* wsrc;
+    real* wdst;
+    real wskap[2], wval_next[2][3];
     real omega, omega_h;       // 1/tau, 1 - 1/(2 tau)
     real ml, lm;               // mu - lambda, lambda - mu (lattice units)
     real F[3];
@@ -244,67 +251,113 @@ __host__ __device__ constexpr double ghost_ep(int k, int c)
 // tau_k per S_a: T puts +S_a/2 on link +a (1, 3, 5) and -S_a/2 on -a (2, 4, 6)
 __host__ __device__ constexpr double ghost_et(int k, int a) { return 0.5 * (ghost3(k, 1 + 2 * a) - ghost3(k, 2 + 2 * a)); }
 
-// Coefficient of one ghost from the site's moments (drho, j with S/2, P),
-// its populations and S.
-template <int k, typename real>
-__device__ __forceinline__ real ghost_coef3(const real g[kQ], real dr, const real j[3], const real P[6],
-                                            const real S[3], real omega, real omega_h)
-{
-    real m = real(0);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        const int n = ghost3(k, i);
-        if (n == 1) m += g[i];
-        else if (n == -1) m -= g[i];
-        else if (n != 0) m += real(n) * g[i];
-    }
-    real e = real(ghost_er(k)) * dr;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-        if (ghost_ej(k, a) != 0.0) e += real(ghost_ej(k, a)) * j[a];
-#pragma unroll
-    for (int c = 0; c < 6; ++c)
-        if (ghost_ep(k, c) != 0.0) e += real(ghost_ep(k, c)) * P[c];
-    real src = real(0);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (ghost_ej(k, a) != 0.0) src += omega_h * (real(ghost_ej(k, a)) * S[a]);
-        if (ghost_et(k, a) != 0.0) src -= real(ghost_et(k, a)) * S[a];
-    }
-    return (omega * (e - m) + src) * real(1.0 / ghost_norm(k));
-}
-
-// Post-collision populations o from g, the moments (j with S/2) and S.
+// delta-rho of a site: its 19 populations added as a binary tree (i with
+// i + 16, then 8, 4, 2, 1 apart), the order in which the lanes of half a wave
+// add them when each holds one (row_sum3).
 template <typename real>
-__device__ __forceinline__ void collide_ghost3(const real g[kQ], real dr, const real j[3], const real P[6],
-                                               const real S[3], real omega, real omega_h, real o[kQ])
+__device__ __forceinline__ real sum3(const real g[kQ])
 {
-    real ak[kGhosts3];
-    ak[0] = ghost_coef3<0>(g, dr, j, P, S, omega, omega_h);
-    ak[1] = ghost_coef3<1>(g, dr, j, P, S, omega, omega_h);
-    ak[2] = ghost_coef3<2>(g, dr, j, P, S, omega, omega_h);
-    ak[3] = ghost_coef3<3>(g, dr, j, P, S, omega, omega_h);
-    ak[4] = ghost_coef3<4>(g, dr, j, P, S, omega, omega_h);
-    ak[5] = ghost_coef3<5>(g, dr, j, P, S, omega, omega_h);
-    ak[6] = ghost_coef3<6>(g, dr, j, P, S, omega, omega_h);
-    ak[7] = ghost_coef3<7>(g, dr, j, P, S, omega, omega_h);
-    ak[8] = ghost_coef3<8>(g, dr, j, P, S, omega, omega_h);
-    const real h[3] = {real(0.5) * S[0], real(0.5) * S[1], real(0.5) * S[2]};
+    real t[16];
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        real d = real(0);
+    for (int i = 0; i < 16; ++i) t[i] = i + 16 < kQ ? g[i] + g[i + 16] : g[i];
 #pragma unroll
-        for (int k = 0; k < kGhosts3; ++k) {
-            const int n = ghost3(k, i);
-            if (n == 1) d += ak[k];
-            else if (n == -1) d -= ak[k];
-            else if (n != 0) d += real(n) * ak[k];
-        }
-        if (i >= 1 && i <= 6) d += (i & 1) ? h[(i - 1) >> 1] : -h[(i - 1) >> 1];
-        o[i] = g[i] + d;
-    }
+    for (int h = 8; h >= 1; h >>= 1)
+#pragma unroll
+        for (int i = 0; i < h; ++i) t[i] = t[i] + t[i + h];
+    return t[0];
 }
 
+// a b + c, rounded once.
+__device__ __forceinline__ float fma3(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma3(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// Moments, source and collision of one site: j on return is with S/2, o the
+// post-collision populations; S = F + c grad.
+//
+// Opposite links i, i + 1 (odd i) enter the even ghosts (epsilon, pi_xx,
+// pi_ww) and P through their sum and the odd ones (q, m) and j through their
+// difference, so each site forms the nine sums and differences once and gives
+// the change back as even +- odd: about 240 operations, where summing each
+// ghost over all 19 populations takes about 700.
+template <typename real>
+__device__ __forceinline__ void collide_pairs3(const real g[kQ], real dr, const real grad[3], real c, const real F[3],
+                                               real omega, real omega_h, real j[3], real o[kQ])
+{
+    real s[9], d[9];
+#pragma unroll
+    for (int p = 0; p < 9; ++p) {
+        s[p] = g[2 * p + 1] + g[2 * p + 2];
+        d[p] = g[2 * p + 1] - g[2 * p + 2];
+    }
+    // links: 0-2 the axes; 3 (1,1,0) 4 (1,-1,0) 5 (1,0,1) 6 (1,0,-1) 7 (0,1,1) 8 (0,1,-1)
+    const real sxy = s[3] + s[4], sxz = s[5] + s[6], syz = s[7] + s[8];
+    const real dxy = d[3] + d[4], exy = d[3] - d[4];         // their x and y parts
+    const real dxz = d[5] + d[6], exz = d[5] - d[6];         // x and z
+    const real dyz = d[7] + d[8], eyz = d[7] - d[8];         // y and z
+    const real bx = dxy + dxz, by = exy + dyz, bz = exz + eyz;
+    real S[3], h[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        S[k] = fma3(c, grad[k], F[k]);
+        h[k] = real(0.5) * S[k];
+    }
+    j[0] = (d[0] + bx) + h[0];
+    j[1] = (d[1] + by) + h[1];
+    j[2] = (d[2] + bz) + h[2];
+    const real Pxx = s[0] + (sxy + sxz), Pyy = s[1] + (sxy + syz), Pzz = s[2] + (sxz + syz);
+    // m_k = n_k.g and a_k N_k = omega (E_k - m_k) + (omega_h Psi_k - tau_k), with
+    // E_k, Psi_k, tau_k of the lattice tables (q: E = ej j, Psi = ej S,
+    // tau = -4 S; m: E = Psi = 0, tau = 0)
+    const real a4 = s[0] + s[1] + s[2], b6 = sxy + sxz + syz;
+    real ak[kGhosts3];
+    {
+        const real m = fma3(real(12), g[0], fma3(real(-4), a4, b6));
+        const real e = fma3(real(ghost_er(0)), dr, real(ghost_ep(0, 0)) * (Pxx + Pyy + Pzz));
+        ak[0] = omega * (e - m) * real(1.0 / ghost_norm(0));
+    }
+    {
+        const real m = fma3(real(-4), s[0], fma3(real(2), s[1] + s[2], (sxy + sxz))) - real(2) * syz;
+        const real e = fma3(real(ghost_ep(4, 0)), Pxx, real(ghost_ep(4, 1)) * (Pyy + Pzz));
+        ak[4] = omega * (e - m) * real(1.0 / ghost_norm(4));
+    }
+    {
+        const real m = fma3(real(2), s[2] - s[1], sxy - sxz);
+        const real e = real(ghost_ep(5, 1)) * (Pyy - Pzz);
+        ak[5] = omega * (e - m) * real(1.0 / ghost_norm(5));
+    }
+    const real bq[3] = {bx, by, bz};
+    const real k_src = omega_h * real(ghost_ej(1, 0)) - real(ghost_et(1, 0));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const real m = fma3(real(-4), d[k], bq[k]);
+        const real e = real(ghost_ej(1, 0)) * j[k];
+        ak[1 + k] = fma3(omega, e - m, k_src * S[k]) * real(1.0 / ghost_norm(1));
+    }
+    const real om_m = -omega * real(1.0 / ghost_norm(6));
+    ak[6] = om_m * (dxy - dxz);
+    ak[7] = om_m * (dyz - exy);
+    ak[8] = om_m * (exz - eyz);
+    // even and odd parts of the change, per pair
+    const real m4a0 = real(-4) * ak[0], a05 = ak[0] + ak[4];
+    const real ev[6] = {fma3(real(-4), ak[4], m4a0), fma3(real(2), ak[4] - ak[5], m4a0), fma3(real(2), ak[4] + ak[5], m4a0),
+                        a05 + ak[5], a05 - ak[5], fma3(real(-2), ak[4], ak[0])};
+    real od[9];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) od[k] = fma3(real(-4), ak[1 + k], h[k]);
+    od[3] = (ak[1] + ak[2]) + (ak[6] - ak[7]);
+    od[4] = (ak[1] - ak[2]) + (ak[6] + ak[7]);
+    od[5] = (ak[1] + ak[3]) - (ak[6] - ak[8]);
+    od[6] = (ak[1] - ak[3]) - (ak[6] + ak[8]);
+    od[7] = (ak[2] + ak[3]) + (ak[7] - ak[8]);
+    od[8] = (ak[2] - ak[3]) + (ak[7] + ak[8]);
+    o[0] = fma3(real(12), ak[0], g[0]);
+#pragma unroll
+    for (int p = 0; p < 9; ++p) {
+        const real e = ev[p < 3 ? p : 3 + (p - 3) / 2];
+        o[2 * p + 1] = g[2 * p + 1] + (e + od[p]);
+        o[2 * p + 2] = g[2 * p + 2] + (e - od[p]);
+    }
+}
 // delta-rho, j and P (xx yy zz xy xz yz) of shifted populations.
 template <typename real>
 __device__ __forceinline__ void moments3(const real g[kQ], real& dr, real j[3], real P[6])
@@ -436,6 +489,89 @@ __device__ __forceinline__ void cut_links3(const Step3Args<real>& a, unsigned s,
         if ((m >> (k - 1)) & 1u) g[opp3(k)] = v[k];
 }
 
+// The walls' parts: link k of the five that leave through a wall returns
+// A_k + s g, g the population that the pull along the leaving direction brings
+// to the site (f_i at x - c_i) and s = kappa (Dirichlet) or -kappa (Neumann);
+// A takes the post-collision state of the site only, so the step that
+// produces the state leaves it behind ([side][5][nz][ny]).
+__host__ __device__ constexpr int wall_pair3(int m) { return m == 0 ? 1 : 5 + 2 * m; }   // 1 7 9 11 13: link with c_x = 1
+
+template <typename real>
+__device__ __forceinline__ void wall_parts3(const Step3Args<real>& a, int side, const real vs[3], const real o[kQ],
+                                            real A[5])
+{
+    real dr, j[3], P[6];
+    moments3(o, dr, j, P);
+    real kap = a.wkap[side], bet = a.wbeta[side], lm = a.lm, v[3] = {vs[0], vs[1], vs[2]};
+    // formed anew at each use: products of these held across k3_march's loop
+    // would spill
+    asm volatile("" : "+s"(kap), "+s"(bet), "+s"(lm), "+s"(v[0]), "+s"(v[1]), "+s"(v[2]));
+    const real n = side == 0 ? real(-1) : real(1);
+    const real Ps[6] = {-(n * v[0]) - lm * dr, P[1], P[2], -(n * v[1]), -(n * v[2]), P[5]};
+#pragma unroll
+    for (int m = 0; m < 5; ++m) {
+        // i leaves, i1 = the pair's link with c_x = 1: c_i = n c_i1
+        const int i1 = wall_pair3(m);
+        const real oi = side == 0 ? o[i1 + 1] : o[i1], ob = side == 0 ? o[i1] : o[i1 + 1];
+        if (a.wkind[side] == kWallDirichlet) {
+            const real cv = n * (v[0] + real(kCY[i1]) * v[1] + real(kCZ[i1]) * v[2]);
+            A[m] = oi - kap * ob - bet * (real(6.0 * w3(i1)) * (real(1) + dr) * cv);
+        } else {
+            real e = real(w3(i1) * (2.5 - 1.5 * c2_3(i1))) * dr;
+            e += real(4.5 * w3(i1) * (2.0 / 3.0)) * Ps[0];
+            e += real(4.5 * w3(i1) * (kCY[i1] * kCY[i1] - 1.0 / 3.0)) * Ps[1];
+            e += real(4.5 * w3(i1) * (kCZ[i1] * kCZ[i1] - 1.0 / 3.0)) * Ps[2];
+            if (kCY[i1]) e += real(9.0 * w3(i1) * kCY[i1]) * Ps[3];
+            if (kCZ[i1]) e += real(9.0 * w3(i1) * kCZ[i1]) * Ps[4];
+            A[m] = -oi - kap * ob + bet * (real(2) * e);
+        }
+    }
+}
+
+// The five populations that a Neumann wall returns with its boundary data
+// extrapolated along the link: eq:abbnoncon, f_ib = -f_i - kappa (f_i(x - c_i)
+// + f_ib) + beta 2 f_eq,i(rho_bd, 0, P*); shifted: g_eq in place of f_eq.  The
+// boundary Poisson stress P* = -sigma* - (lambda - mu) drho_bd I with
+// sigma = -P - (lambda - mu) drho I takes its normal row from the traction,
+// rho_bd and its tangential block as (1 + q) X(x) - q X(x - c_i).
+template <typename real>
+__device__ __forceinline__ void ext_wall3(const Step3Args<real>& a, const Site3& st, int side, const real h[kQ], real dr,
+                                          const real P[6], real g[kQ])
+{
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const real n = side == 0 ? real(-1) : real(1);
+    const real* v = a.wval[side];
+    const real kap = a.wkap[side], bet = a.wbeta[side];
+    const int bx = side == 0 ? st.x + 1 : st.x - 1;         // the next site inward (nx > 1)
+    const real jz[3] = {real(0), real(0), real(0)};
+#pragma unroll
+    for (int i = 1; i < kQ; ++i) {
+        // link i leaves through this wall; its opposite returns
+        if (kCX[i] != (side == 0 ? -1 : 1)) continue;
+        const unsigned sb = sidx3(bx, wrap(st.y - kCY[i], ny), wrap(st.z - kCZ[i], nz), nx, ny);
+        const real hy = a.src[i * a.stride + sb];           // f_i at x - c_i
+        real hb[kQ];
+#pragma unroll
+        for (int k = 0; k < kQ; ++k) hb[k] = a.src[k * a.stride + sb];
+        real dry, jy[3], Py[6];
+        moments3(hb, dry, jy, Py);
+        const real w1 = a.wq1[side], w2 = a.wq[side];
+        const real drb = w1 * dr - w2 * dry;
+        const real Ps[6] = {-(n * v[0]) - a.lm * drb, w1 * P[1] - w2 * Py[1], w1 * P[2] - w2 * Py[2], -(n * v[1]),
+                            -(n * v[2]), w1 * P[5] - w2 * Py[5]};
+        real e;
+        switch (i) {
+#define SLBM3_GEQ(k) case k: e = geq3<k, real>(drb, jz, Ps); break;
+            SLBM3_GEQ(1) SLBM3_GEQ(2) SLBM3_GEQ(3) SLBM3_GEQ(4) SLBM3_GEQ(5) SLBM3_GEQ(6)
+            SLBM3_GEQ(7) SLBM3_GEQ(8) SLBM3_GEQ(9) SLBM3_GEQ(10) SLBM3_GEQ(11) SLBM3_GEQ(12)
+            SLBM3_GEQ(13) SLBM3_GEQ(14) SLBM3_GEQ(15) SLBM3_GEQ(16) SLBM3_GEQ(17) SLBM3_GEQ(18)
+#undef SLBM3_GEQ
+            default: e = real(0);
+        }
+        g[opp3(i)] = -h[i] - kap * (hy + h[opp3(i)]) + bet * (real(2) * e);
+    }
+}
+
 template <typename real, bool PX, bool GEO = false>
 __device__ __forceinline__ void pull3(const Step3Args<real>& a, const Site3& st, real g[kQ], uint32_t& fl)
 {
@@ -483,80 +619,73 @@ __device__ __forceinline__ void pull3(const Step3Args<real>& a, const Site3& st,
         real h[kQ];
 #pragma unroll
         for (int i = 0; i < kQ; ++i) h[i] = a.src[i * a.stride + s];
-        real dr, j[3], P[6];
-        moments3(h, dr, j, P);
-        // both walls when nx == 1
+        real dr = real(0), j[3], P[6];
+        if (a.wext[0] || a.wext[1]) moments3(h, dr, j, P);
+        // both walls when nx == 1: what either returns is formed from the pulls
+        // before any is replaced (kappa = 0 then)
 #pragma unroll
         for (int side = 0; side < 2; ++side) {
             if (side == 0 ? st.x != 0 : st.x != nx - 1) continue;
-            const int kind = a.wkind[side];
-            const real n = side == 0 ? real(-1) : real(1);
-            const real* v = a.wval[side];
-            const real kap = a.wkap[side], bet = a.wbeta[side];
-            // the site behind x along a cut link, x - c_i, is the next site
-            // inward (none in a one-site-wide slab, where kappa = 0)
-            const int bx = nx == 1 ? st.x : (side == 0 ? st.x + 1 : st.x - 1);
-            const real rho = real(1) + dr;
-            const real jz[3] = {real(0), real(0), real(0)};
+            if (a.wext[side]) {
+                ext_wall3(a, st, side, h, dr, P, g);
+                continue;
+            }
+            real A[5];
+            wall_parts3(a, side, a.wval[side], h, A);
 #pragma unroll
-            for (int i = 1; i < kQ; ++i) {
-                // link i leaves through this wall; its opposite returns
-                if (kCX[i] != (side == 0 ? -1 : 1)) continue;
-                const unsigned sb = sidx3(bx, wrap(st.y - kCY[i], ny), wrap(st.z - kCZ[i], nz), nx, ny);
-                const real hy = a.src[i * a.stride + sb];    // f_i at x - c_i
-                real val;
-                if (kind == kWallDirichlet) {
-                    // eq:bbcon / eq:bbnoncon: f_ib = f_i + kappa (f_i(x - c_i) - f_ib)
-                    // - beta 6 w_i c_i.j*, j* = rho(x) v*
-                    const real cv = real(kCX[i]) * v[0] + real(kCY[i]) * v[1] + real(kCZ[i]) * v[2];
-                    val = h[i] + kap * (hy - h[opp3(i)]) - bet * (real(6.0 * w3(i)) * rho * cv);
-                } else {
-                    // eq:abbcon / eq:abbnoncon: f_ib = -f_i - kappa (f_i(x - c_i) + f_ib)
-                    // + beta 2 f_eq,i(rho_bd, 0, P*); shifted: g_eq in place of f_eq.
-                    // Boundary Poisson stress P* = -sigma* - (lambda - mu) drho_bd I with
-                    // sigma = -P - (lambda - mu) drho I: its normal row from the traction,
-                    // its tangential block that of P at the site, or extrapolated along
-                    // the link, (1 + q) X(x) - q X(x - c_i)
-                    real drb = dr, Pb1 = P[1], Pb2 = P[2], Pb5 = P[5];
-                    if (a.wext[side]) {
-                        real hb[kQ];
-#pragma unroll
-                        for (int k = 0; k < kQ; ++k) hb[k] = a.src[k * a.stride + sb];
-                        real dry, jy[3], Py[6];
-                        moments3(hb, dry, jy, Py);
-                        const real w1 = a.wq1[side], w2 = a.wq[side];
-                        drb = w1 * dr - w2 * dry;
-                        Pb1 = w1 * P[1] - w2 * Py[1];
-                        Pb2 = w1 * P[2] - w2 * Py[2];
-                        Pb5 = w1 * P[5] - w2 * Py[5];
-                    }
-                    real Ps[6];
-                    Ps[0] = -(n * v[0]) - a.lm * drb;             // sigma*_xx = n t_x
-                    Ps[1] = Pb1;                                  // tangential block
-                    Ps[2] = Pb2;
-                    Ps[3] = -(n * v[1]);                          // sigma*_xy = n t_y
-                    Ps[4] = -(n * v[2]);                          // sigma*_xz = n t_z
-                    Ps[5] = Pb5;
-                    real e;
-                    switch (i) {
-#define SLBM3_GEQ(k) case k: e = geq3<k, real>(drb, jz, Ps); break;
-                        SLBM3_GEQ(1) SLBM3_GEQ(2) SLBM3_GEQ(3) SLBM3_GEQ(4) SLBM3_GEQ(5) SLBM3_GEQ(6)
-                        SLBM3_GEQ(7) SLBM3_GEQ(8) SLBM3_GEQ(9) SLBM3_GEQ(10) SLBM3_GEQ(11) SLBM3_GEQ(12)
-                        SLBM3_GEQ(13) SLBM3_GEQ(14) SLBM3_GEQ(15) SLBM3_GEQ(16) SLBM3_GEQ(17) SLBM3_GEQ(18)
-#undef SLBM3_GEQ
-                        default: e = real(0);
-                    }
-                    val = -h[i] - kap * (hy + h[opp3(i)]) + bet * (real(2) * e);
-                }
-                g[opp3(i)] = val;
+            for (int m = 0; m < 5; ++m) {
+                const int i1 = wall_pair3(m);               // c_x = 1: returned by side 0, leaves through side 1
+                const real gl = nx == 1 ? real(0) : (side == 0 ? g[i1 + 1] : g[i1]);
+                (side == 0 ? g[i1] : g[i1 + 1]) = A[m] + a.wskap[side] * gl;
             }
         }
     }
 }
 
 // Density gradient of eq:sourceterm, isotropic D3Q19 stencil
-// grad = 3 sum_i w_i c_i rho(x + c_i), from the delta-rho buffer; across a
-// cut link the neighbour is 2 rho(x) - rho(x - c_i) (rho(x) if that is cut too).
+// grad = 3 sum_i w_i c_i rho(x + c_i); across a cut link the neighbour is
+// 2 rho(x) - rho(x - c_i) (rho(x) if that is cut too).  It is added up plane by
+// plane in z, so that k3_march can carry a plane's share to the next one:
+// what plane p gives the gradient of the sites above and below it (sx, sy to
+// the x and y components, tz to z), and in its own plane (gx, gy).
+template <typename real>
+struct PlaneTerms3 {
+    real sx, sy, tz, gx, gy;
+};
+
+// From delta-rho of the 3 x 3 sites around a site (C its own; E, W at x +- 1,
+// N, S at y +- 1).  side: the wall that cuts the site's x links (0 at x = 0, 1
+// at x = nx - 1, -1 none): there the difference to the opposite neighbour
+// doubles the inner one's (less 2 rho(x), which wall_grad3 takes off), and the
+// sum that enters the other axes' terms doubles it too.
+template <typename real>
+__device__ __forceinline__ PlaneTerms3<real> plane_terms3(real C, real E, real W, real N, real S, real NE, real NW, real SE,
+                                                          real SW, int side)
+{
+    real Ed = E, Wd = W, NEd = NE, NWd = NW, SEd = SE, SWd = SW;
+    if (side == 0) { W = E; NW = NE; SW = SE; Wd = -E; NWd = -NE; SWd = -SE; }
+    if (side == 1) { E = W; NE = NW; SE = SW; Ed = -W; NEd = -NW; SEd = -SW; }
+    PlaneTerms3<real> t;
+    t.sx = Ed - Wd;
+    t.sy = N - S;
+    t.tz = fma3(real(1.0 / 6.0), C, real(1.0 / 12.0) * ((E + W) + (N + S)));
+    t.gx = fma3(real(1.0 / 6.0), t.sx, real(1.0 / 12.0) * ((NEd - NWd) + (SEd - SWd)));
+    t.gy = fma3(real(1.0 / 6.0), t.sy, real(1.0 / 12.0) * ((NE - SE) + (NW - SW)));
+    return t;
+}
+// The in-plane part with the share of the plane below, then with that above.
+template <typename real>
+__device__ __forceinline__ real with_share3(real g, real s)
+{
+    return fma3(real(1.0 / 12.0), s, g);
+}
+template <typename real>
+__device__ __forceinline__ real wall_grad3(int side, real dr)
+{
+    return side == 0 ? -dr : (side == 1 ? dr : real(0));
+}
+
+// The gradient from the delta-rho buffer.
 template <typename real, bool PX, bool GEO = false>
 __device__ __forceinline__ void grad3(const Step3Args<real>& a, const Site3& st, real dr, real grad[3],
                                       uint32_t fl = 0u)
@@ -576,17 +705,12 @@ __device__ __forceinline__ void grad3(const Step3Args<real>& a, const Site3& st,
         const int zz = kCZ[i] > 0 ? zp : (kCZ[i] < 0 ? zm : st.z);
         nb[i] = d[sidx3(xx, yy, zz, nx, ny)];
     }
-    if (cutm || cutp) {
-        real sub[kQ];
+    if (cutm && cutp) {                                     // both x neighbours are across a wall
 #pragma unroll
-        for (int i = 1; i < kQ; ++i) {
-            const bool ci = (kCX[i] < 0 && cutm) || (kCX[i] > 0 && cutp);
-            const bool co = (kCX[i] > 0 && cutm) || (kCX[i] < 0 && cutp);
-            sub[i] = ci ? (co ? dr : real(2) * dr - nb[opp3(i)]) : nb[i];
-        }
-#pragma unroll
-        for (int i = 1; i < kQ; ++i) nb[i] = sub[i];
+        for (int i = 1; i < kQ; ++i)
+            if (kCX[i]) nb[i] = dr;
     }
+    const int side = cutm == cutp ? -1 : (cutm ? 0 : 1);
     if (GEO && (fl & kCutMask3) != 0u) {
         real sub[kQ];
 #pragma unroll
@@ -597,13 +721,15 @@ __device__ __forceinline__ void grad3(const Step3Args<real>& a, const Site3& st,
 #pragma unroll
         for (int i = 1; i < kQ; ++i) nb[i] = sub[i];
     }
-    // 3 w_i = 1/6 (axis), 1/12 (diagonals)
-    grad[0] = real(1.0 / 6.0) * (nb[1] - nb[2]) +
-              real(1.0 / 12.0) * ((nb[7] - nb[8]) + (nb[9] - nb[10]) + (nb[11] - nb[12]) + (nb[13] - nb[14]));
-    grad[1] = real(1.0 / 6.0) * (nb[3] - nb[4]) +
-              real(1.0 / 12.0) * ((nb[7] - nb[8]) - (nb[9] - nb[10]) + (nb[15] - nb[16]) + (nb[17] - nb[18]));
-    grad[2] = real(1.0 / 6.0) * (nb[5] - nb[6]) +
-              real(1.0 / 12.0) * ((nb[11] - nb[12]) - (nb[13] - nb[14]) + (nb[15] - nb[16]) - (nb[17] - nb[18]));
+    // planes z - 1, z, z + 1 (only the terms that enter are used)
+    const real o = real(0);
+    const PlaneTerms3<real> lo = plane_terms3(nb[6], nb[13], nb[12], nb[17], nb[16], o, o, o, o, side);
+    const PlaneTerms3<real> in = plane_terms3(dr, nb[1], nb[2], nb[3], nb[4], nb[7], nb[10], nb[9], nb[8], side);
+    const PlaneTerms3<real> hi = plane_terms3(nb[5], nb[11], nb[14], nb[15], nb[18], o, o, o, o, side);
+    grad[0] = with_share3(with_share3(in.gx, lo.sx), hi.sx);
+    if (!PX) grad[0] += wall_grad3(side, dr);
+    grad[1] = with_share3(with_share3(in.gy, lo.sy), hi.sy);
+    grad[2] = hi.tz - lo.tz;
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs.  Each XCD takes groups of
@@ -634,9 +760,7 @@ __global__ __launch_bounds__(256) void k3_density(Step3Args<real> a)
     real g[kQ];
     uint32_t fl;
     pull3<real, PX, GEO>(a, st, g, fl);
-    real dr = real(0);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) dr += g[i];
+    real dr = sum3(g);
     if (GEO && (fl & kVoid3)) dr = real(0);               // void: never read
     if (st.in) a.dens[sidx3(st.x, st.y, st.z, a.nx, a.ny)] = dr;
 }
@@ -664,23 +788,14 @@ __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
     uint32_t fl;
     pull3<real, PX, GEO>(a, st, g, fl);
     const bool live = st.in && !(GEO && (fl & kVoid3));  // void sites stay at rest
-    real dr, j[3], P[6];
-    moments3(g, dr, j, P);
+    const real dr = sum3(g);
     real grad[3];
     grad3<real, PX, GEO>(a, st, dr, grad, fl);
-    const real rho = real(1) + dr;
-    const real ir = recip3(rho);
-    const real c = a.ml * ir;
-    real S[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        S[k] = a.F[k] + c * grad[k];
-        j[k] = j[k] + real(0.5) * S[k];
-    }
+    const real ir = recip3(real(1) + dr);
     const unsigned s = sidx3(st.x, st.y, st.z, a.nx, a.ny);
     // eq:coll in ghost-moment form (exact conserved moments)
-    real o[kQ];
-    collide_ghost3(g, dr, j, P, S, a.omega, a.omega_h, o);
+    real o[kQ], j[3];
+    collide_pairs3(g, dr, grad, a.ml * ir, a.F, a.omega, a.omega_h, j, o);
     const bool bad = !(fabs(dr) + fabs(j[0]) + fabs(j[1]) + fabs(j[2]) < real(kDivergeBound));
     // void sites store the rest state (zeros) rather than nothing: whole
     // lines reach HBM, where a partly written line costs a read-modify-write
@@ -722,6 +837,343 @@ __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
             }
         }
     }
+}
+
+// ------------------------------------------------ one launch per step
+//
+// k3_march takes the density pass and the step in one launch: a workgroup
+// owns `rows` rows of a 64-site chunk and marches through `depth` planes.
+// Wave w holds row y0 - 1 + w (the first and the last only supply density).
+// When the pulls of plane p arrive it adds them up, leaves the density in LDS
+// and the populations in LDS of its own, and sends the loads of plane p + 1
+// off into the same registers; after one barrier the inner waves step plane
+// p - 1 while those are in flight.  So a population is read from memory once
+// per step where the density pass and the step read it twice; the halo rows
+// (2 in 10) and planes (2 in depth + 2) come from L2.
+//
+// Bound by HBM: 256^3 fp32 moves 3.25 GB a step (counters), the 200 B per
+// site it cannot do without, at 4.7 TB/s: 689 us periodic, 701 us with walls,
+// where the two launches move 4.8 GB in 901 and 905 us; fp64 1259 us against
+// 1682.  What it took, 256^3 fp32:
+// - waves of an exact 64-site chunk (62-column strips waste a fifth of a
+//   256-site row), the two halo columns gathered by one more load a wave;
+// - collide_pairs3 (300 vector instructions a site-step, two launches: 1050);
+// - no wait but for the pulls themselves: loads without a branch, a fixed
+//   number of stores behind them, LDS-only barriers, U added in memory
+//   (atomics that return nothing) instead of loaded, and not one spill, whose
+//   reload would wait for every load in flight (slab: 1500 us with 47 spilled
+//   registers, 731 with none);
+// - tiles dealt to the XCDs in groups of 8, so that the chip moves through one
+//   region of the box (groups of 8 to 32 689 us, contiguous bands 722, 1 711);
+// - 8 rows: 6 rows 780 us (their halo, and a last tile of 4 rows), 14 rows 765;
+//   one or two workgroups on a CU make no difference.
+// fp64: 8 waves, what the LDS of a CU holds of their populations (110 KB).
+constexpr int kMarchWaves(int bytes) { return bytes == 4 ? 10 : 8; }     // waves of a workgroup at most
+constexpr int kMarchOcc(int bytes) { return bytes == 4 ? 5 : 2; }        // waves per SIMD it is compiled for
+
+// The parts from a state that no k3_march produced (a loaded one, or one that
+// the two launches advanced).
+template <typename real>
+__global__ __launch_bounds__(256) void k3_wall_parts(Step3Args<real> a, real* out)
+{
+    const int n = a.ny * a.nz, side = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;   // r = z ny + y
+    if (r >= n) return;
+    const unsigned s = (unsigned)r * (unsigned)a.nx + (side ? a.nx - 1 : 0);
+    real o[kQ], A[5];
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) o[i] = a.src[i * a.stride + s];
+    wall_parts3(a, side, a.wval[side], o, A);
+#pragma unroll
+    for (int m = 0; m < 5; ++m) out[(long long)(side * 5 + m) * n + r] = A[m];
+}
+
+template <typename T>
+using gptr3 = __attribute__((address_space(1))) T*;
+
+// Walks the planes of a population or displacement buffer: the base stays in
+// scalar registers (the empty asm also keeps the compiler from holding all 19
+// bases across the loop, more than it has), the byte offset in the plane in
+// one vector register (below 2^32: at most 2^29 sites).
+struct PlaneWalk {
+    gptr3<char> base;
+    unsigned long long step;
+    template <typename T>
+    __device__ __forceinline__ PlaneWalk(const T* p, long long stride)
+        : base((gptr3<char>)p), step((unsigned long long)stride * sizeof(T))
+    {
+        asm volatile("" : "+s"(base));
+    }
+    __device__ __forceinline__ void next()
+    {
+        base += step;
+        asm("" : "+s"(base));
+    }
+    template <typename T>
+    __device__ __forceinline__ void store(unsigned off, T v) const { *(gptr3<T>)(base + off) = v; }
+    // += in memory (one rounded sum, as a load, an add and a store)
+    __device__ __forceinline__ void add(unsigned off, double v) const
+    {
+        (void)__builtin_amdgcn_global_atomic_fadd_f64((gptr3<double>)(base + off), v);
+    }
+};
+
+// Barrier over LDS only: loads from global memory stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Adds what the 32 lanes of each half-wave hold in sum3's order (lanes from
+// kQ on hold zero).
+template <int N>
+__device__ __forceinline__ float row_ror(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, false));
+}
+template <int N>
+__device__ __forceinline__ double row_ror(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x120 + N, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + N, 0xF, 0xF, false);
+    return __longlong_as_double((long long)((unsigned long long)(unsigned)hi << 32 | (unsigned)lo));
+}
+template <typename real>
+__device__ __forceinline__ real half_sum3(real v)
+{
+    v += __shfl_xor(v, 16);
+    v += row_ror<8>(v);
+    v += row_ror<4>(v);
+    v += row_ror<2>(v);
+    v += row_ror<1>(v);
+    return v;
+}
+
+// The population a lane holds of its halo column (lanes from kQ on: none,
+// they repeat population 0), its c + 1 per axis (2 bits each), and whether it
+// is one that the x = nx - 1 wall returns to the right column.
+__device__ __forceinline__ int halo_dir3(int lane) { return (lane & 31) < kQ ? (lane & 31) : 0; }
+__host__ __device__ constexpr uint64_t halo_bits3(int axis, int sign)
+{
+    uint64_t b = 0;
+    for (int i = 0; i < kQ; ++i) b |= (uint64_t)((axis == 0 ? kCX[i] : (axis == 1 ? kCY[i] : kCZ[i])) == sign) << i;
+    return b;
+}
+__device__ __forceinline__ int halo_c3(int i)
+{
+    constexpr uint32_t xp = (uint32_t)halo_bits3(0, 1), xn = (uint32_t)halo_bits3(0, -1), yp = (uint32_t)halo_bits3(1, 1),
+                       yn = (uint32_t)halo_bits3(1, -1), zp = (uint32_t)halo_bits3(2, 1), zn = (uint32_t)halo_bits3(2, -1);
+    const int cx = 1 + (int)((xp >> i) & 1u) - (int)((xn >> i) & 1u), cy = 1 + (int)((yp >> i) & 1u) - (int)((yn >> i) & 1u),
+              cz = 1 + (int)((zp >> i) & 1u) - (int)((zn >> i) & 1u);
+    return cx | cy << 2 | cz << 4;
+}
+__device__ __forceinline__ bool halo_ret3(int lane)
+{
+    constexpr uint32_t xn = (uint32_t)halo_bits3(0, -1);
+    return lane >= 32 && ((xn >> (lane & 31)) & 1u);
+}
+
+// Pulled populations of one plane: a row's, and the lane's share of the two
+// halo columns (lane i: population i of column x0 - 1, lane 32 + i of column
+// x0 + 64).
+template <typename real>
+struct Plane3 {
+    real g[kQ];
+    real halo;
+};
+
+template <typename real, bool PX>
+__global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(real))) void k3_march(Step3Args<real> a)
+{
+    constexpr int NW = kMarchWaves(sizeof(real));
+    __shared__ real dens[2][NW][68];
+    // a lane's own of the plane before: populations, and of grad its in-plane
+    // part with the share of the plane below (x, y), minus that share (z), and
+    // its own share of its neighbours' (x, y, z)
+    __shared__ real park[NW][kQ + 6][64];
+    const int bx = blockIdx.x & 7, bl = blockIdx.x >> 3;
+    const int t = (bl / a.xgroup * 8 + bx) * a.xgroup + bl % a.xgroup;
+    if (t >= a.mtiles) return;                              // uniform over the workgroup
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const int ch = t % a.nch, yt = (t / a.nch) % a.nyt, seg = t / (a.nch * a.nyt);
+    const int x0 = ch * 64, z0 = seg * a.depth, H = min(a.depth, nz - z0);
+    const int yl = yt * a.rows - 1 + wave;
+    const int y = __builtin_amdgcn_readfirstlane((yl + ny) % ny);
+    const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+    const bool out = wave >= 1 && wave <= a.rows && yl < ny;      // uniform over the wave
+    // lanes past the row's end repeat its last site in everything they load and
+    // store, so that no store below is conditional: then the compiler knows how
+    // many stores follow the loads in flight, and waits for the loads alone
+    const int wd = min(64, nx - x0), col = min(lane, wd - 1), x = x0 + col;
+    const bool first = !PX && x0 == 0, last = !PX && x0 + 64 >= nx;   // uniform
+    const int wall_side = PX ? -1 : (x == 0 ? 0 : (x == nx - 1 ? 1 : -1));
+    const long long nyz = (long long)ny * nz;
+    // the lane's halo population (halo_dir3): where it comes from in its plane
+    unsigned hsrc;
+    {
+        const int hi = halo_dir3(lane), hc = halo_c3(hi);
+        int hx = lane < 32 ? x0 - 1 : x0 + wd;              // the halo column
+        if (PX) hx = hx < 0 ? nx - 1 : (hx >= nx ? 0 : hx);
+        else hx = hx < 0 ? 0 : (hx >= nx ? nx - 1 : hx);
+        int hsx = hx - ((hc & 3) - 1);
+        if (PX) hsx = hsx < 0 ? nx - 1 : (hsx >= nx ? 0 : hsx);
+        else hsx = hsx < 0 ? 0 : (hsx >= nx ? nx - 1 : hsx);
+        const int cy = ((hc >> 2) & 3) - 1;
+        hsrc = (unsigned)(cy > 0 ? ym : (cy < 0 ? yp : y)) * (unsigned)nx + (unsigned)hsx;
+    }
+    // the right halo column is the wall's own when one site follows the chunk
+    const bool hwall = !PX && x0 + 65 == nx;                // uniform
+
+    auto issue = [&](int p, Plane3<real>& q) {
+        const int z = p < 0 ? p + nz : (p >= nz ? p - nz : p), zm = z == 0 ? nz - 1 : z - 1, zp = z == nz - 1 ? 0 : z + 1;
+        // what follows from the lane is formed anew for every plane: held across
+        // the loop it would cost the registers that let two workgroups share a CU
+        int xv = x, lv = lane;
+        asm volatile("" : "+v"(xv), "+v"(lv));
+        const int xm = xv == 0 ? nx - 1 : xv - 1, xp = xv == nx - 1 ? 0 : xv + 1;
+        PlaneWalk w(a.src, a.stride), w0(a.wsrc, nyz), w1(a.wsrc + (PX ? 0 : 5 * nyz), nyz);
+        const unsigned wrow = (unsigned)(z * ny + y) * (unsigned)sizeof(real);
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            const int zz = kCZ[i] > 0 ? zm : (kCZ[i] < 0 ? zp : z), yy = kCY[i] > 0 ? ym : (kCY[i] < 0 ? yp : y);
+            const unsigned r = (unsigned)(zz * ny + yy) * (unsigned)nx;      // uniform
+            // between walls the neighbours of every lane that keeps them are next to
+            // it (a wall site's outer one is the wall's part); a periodic row wraps
+            const unsigned off = (r + (unsigned)(!PX || kCX[i] == 0 ? xv : (kCX[i] > 0 ? xm : xp))) * (unsigned)sizeof(real);
+            const int next = PX ? 0 : -kCX[i] * (int)sizeof(real);
+            if (!PX && kCX[i] != 0 && (kCX[i] > 0 ? first : last)) {         // uniform
+                const bool ret = kCX[i] > 0 ? xv == 0 : xv == nx - 1;
+                gptr3<char> src = ret ? (kCX[i] > 0 ? w0.base : w1.base) + wrow : w.base + off + next;
+                q.g[i] = *(gptr3<const real>)src;
+            } else {
+                q.g[i] = *(gptr3<const real>)(w.base + off + next);
+            }
+            w.next();
+            if (!PX && kCX[i] > 0) w0.next();
+            if (!PX && kCX[i] < 0) w1.next();
+        }
+        const int hi = halo_dir3(lv), cz = (halo_c3(hi) >> 4) - 1;
+        const real* hp = a.src + hi * a.stride + ((unsigned)((cz > 0 ? zm : (cz < 0 ? zp : z)) * ny) * (unsigned)nx + hsrc);
+        if (!PX && hwall && halo_ret3(lv)) {
+            const int hm = hi == 2 ? 0 : (hi - 6) / 2;      // 2 8 10 12 14 -> 0..4
+            hp = a.wsrc + ((5 + hm) * nyz + ((long long)z * ny + y));
+        }
+        q.halo = *(gptr3<const real>)hp;
+    };
+    // plane p (in q) has arrived: the walls' returning populations, its density
+    // into LDS with the halo columns', the populations into `park` (inner
+    // waves), then plane `next` on its way into q
+    auto arrive = [&](Plane3<real>& q, int slot, int next, bool keep) -> real {
+        if (!PX && first) {
+            const real s = x == 0 ? a.wskap[0] : real(0);   // other lanes keep their pulls
+#pragma unroll
+            for (int m = 0; m < 5; ++m) q.g[wall_pair3(m)] += s * q.g[wall_pair3(m) + 1];
+        }
+        if (!PX && last) {
+            const real s = x == nx - 1 ? a.wskap[1] : real(0);
+#pragma unroll
+            for (int m = 0; m < 5; ++m) q.g[wall_pair3(m) + 1] += s * q.g[wall_pair3(m)];
+        }
+        if (!PX && hwall) {
+            const real gl = __shfl(q.halo, (lane - 1) & 63);
+            if (halo_ret3(lane)) q.halo += a.wskap[1] * gl;
+        }
+        const real dr = sum3(q.g);
+        const real hs = half_sum3((lane & 31) < kQ ? q.halo : real(0));
+        if (keep) {
+#pragma unroll
+            for (int i = 0; i < kQ; ++i) park[wave][i][lane] = q.g[i];
+        }
+        issue(next, q);
+        __builtin_amdgcn_sched_barrier(0);
+        dens[slot][wave][1 + col] = dr;
+        if ((lane & 31) == 0) dens[slot][wave][lane ? 1 + wd : 0] = hs;
+        lds_barrier();
+        return dr;
+    };
+
+    Plane3<real> q;
+    issue(z0 - 1, q);
+    if (!out) {
+        // a row of halo: densities only; as many barriers as the others
+        for (int m = 0; m <= H + 1; ++m) arrive(q, m & 1, z0 + min(m, H), false);
+        return;
+    }
+    bool bad = false;
+    auto plane_grad = [&](int slot, real dr) {
+        const real (*d)[68] = dens[slot];
+        return plane_terms3(dr, d[wave][col + 2], d[wave][col], d[wave + 1][col + 1], d[wave - 1][col + 1],
+                            d[wave + 1][col + 2], d[wave + 1][col], d[wave - 1][col + 2], d[wave - 1][col],
+                            !PX && (first || last) ? wall_side : -1);
+    };
+    real (*own)[64] = park[wave];
+    auto carry = [&](const PlaneTerms3<real>& t, real sx1, real sy1, real t1) {
+        own[kQ][lane] = with_share3(t.gx, sx1);
+        own[kQ + 1][lane] = with_share3(t.gy, sy1);
+        own[kQ + 2][lane] = t1;
+        own[kQ + 3][lane] = t.sx;
+        own[kQ + 4][lane] = t.sy;
+        own[kQ + 5][lane] = t.tz;
+    };
+    for (int m = 0; m < 2; ++m) {
+        const PlaneTerms3<real> t = plane_grad(m, arrive(q, m, z0 + m, m == 1));
+        const bool below = m > 0;
+        carry(t, below ? own[kQ + 3][lane] : real(0), below ? own[kQ + 4][lane] : real(0),
+              below ? own[kQ + 5][lane] : real(0));
+    }
+    // plane z0 - 1 + m arrives, plane zc before it is stepped
+    auto advance = [&](int m) {
+        const int zc = z0 + m - 2;
+        const unsigned s = (unsigned)(zc * ny + y) * (unsigned)nx + (unsigned)x;
+        real cur[kQ];
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) cur[i] = park[wave][i][lane];
+        const PlaneTerms3<real> t = plane_grad(m & 1, arrive(q, m & 1, z0 + min(m, H), true));
+        const real dr1 = dens[(m & 1) ^ 1][wave][1 + col];  // the stepped plane's, left there one plane ago
+        real grad[3];
+        grad[0] = with_share3(own[kQ][lane], t.sx);
+        if (!PX && (first || last)) grad[0] += wall_grad3(wall_side, dr1);
+        grad[1] = with_share3(own[kQ + 1][lane], t.sy);
+        grad[2] = t.tz - own[kQ + 2][lane];
+        carry(t, own[kQ + 3][lane], own[kQ + 4][lane], own[kQ + 5][lane]);
+        const real ir = recip3(real(1) + dr1);
+        real o[kQ], j[3];
+        collide_pairs3(cur, dr1, grad, a.ml * ir, a.F, a.omega, a.omega_h, j, o);
+        bad |= !(fabs(dr1) + fabs(j[0]) + fabs(j[1]) + fabs(j[2]) < real(kDivergeBound));
+        PlaneWalk w(a.dst, a.stride);
+#pragma unroll
+        for (int i = 0; i < kQ; ++i) {
+            w.store(s * (unsigned)sizeof(real), o[i]);
+            w.next();
+        }
+        PlaneWalk wu(a.U, a.stride);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (lane < wd) wu.add(s * 8u, (double)(j[k] * ir));
+            wu.next();
+        }
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            if (PX || !(side ? last : first)) continue;     // uniform
+            if (wall_side != side) continue;
+            real A[5];
+            wall_parts3(a, side, a.wval_next[side], o, A);
+            PlaneWalk ww(a.wdst + side * 5 * nyz, nyz);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                ww.store((unsigned)(zc * ny + y) * (unsigned)sizeof(real), A[k]);
+                ww.next();
+            }
+        }
+    };
+    // the first one apart: in the loop the loads in flight always have a
+    // plane's stores behind them
+    advance(2);
+    for (int m = 3; m <= H + 1; ++m) advance(m);
+    if (__any(bad) && lane == 0 && *(volatile unsigned int*)a.diverged == 0u) atomicOr(a.diverged, 1u);
 }
 
 // Where a readout goes: arrays of the caller (null: not wanted), u [3][n]

@@ -1,0 +1,71 @@
+"""The one-launch 3-D step on boxes large enough to take it, ragged against
+its 64-site chunks, its rows and its planes.  The box repeats a small one's
+field periodically in y and z, so the reference steps the small one and every
+repetition must match it."""
+import numpy as np
+import pytest
+
+from oracle.slbm3d import Oracle3D
+from slbm_workloads import box3d as B
+from test_gpu_parity3d import FP32_TOL, FP64_TOL, S3, check  # noqa: F401  (S3: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+DT = np.sqrt(1.0 / (3 * 0.05))
+
+
+def box_of(kind, nx, ny, nz):
+    if kind == "periodic":
+        return B.periodic_box3(nx, ny, nz, lam=0.04, mu=0.05, tau=0.6, force=(1e-6, -2e-6, 0.5e-6))
+    moving = B.Wall3(B.DIRICHLET, (1e-4, -5e-5, 2e-5), q=0.3, profile=B.RAMP, ramp_time=5 * DT)
+    pulled = B.Wall3(B.NEUMANN, (5e-5, 1e-5, -2e-5), q=0.8)
+    walls = (moving, pulled) if kind == "slab" else (pulled, moving)
+    return B.slab3(nx, ny, nz, *walls, lam=0.04, mu=0.05, tau=0.6, force=(1e-6, -2e-6, 0.5e-6))
+
+
+# (kind, nx, repetitions of 9 x 5 in y and z): whole chunks; one site more (its
+# wall is the halo column of the last chunk); a short last chunk; one chunk
+@pytest.mark.parametrize("prec,tol", [("fp64", FP64_TOL), ("fp32", FP32_TOL)])
+@pytest.mark.parametrize("kind,nx,ry,rz", [("slab", 128, 13, 14), ("slab", 65, 15, 22), ("flipped", 131, 11, 15),
+                                           ("slab", 61, 19, 18), ("periodic", 128, 13, 15), ("periodic", 67, 16, 20)])
+def test_large_boxes_match_the_reference(S3, kind, nx, ry, rz, prec, tol):  # noqa: F811
+    ny, nz = 9, 5
+    small, big = box_of(kind, nx, ny, nz), box_of(kind, nx, ny * ry, nz * rz)
+    assert big.n_sites >= 850000
+    vel = B.random_velocity(small, 17, 1e-3)
+    tile = lambda v: np.tile(v, (1, rz, ry, 1))
+    ref = Oracle3D(small, extended=(prec == "fp64"))
+    ref.init_fields(vel=vel)
+    ref.step(7)
+    with S3.Solver3(big, prec) as s:
+        s.init_fields(vel=tile(vel))
+        s.step(4)
+        saved = s.save()
+        s.step(3)
+        s.sync()
+        u, (rho, j, P, sig) = s.displacement(), s.moments()
+        s.load(saved)                                       # the walls' parts are formed anew from the state
+        s.step(3)
+        assert np.array_equal(u, s.displacement())
+    rr, jr, Pr, sr = ref.moments()
+    check((u, (rho, j, P, sig)), (tile(ref.displacement()), (tile(rr[None])[0], tile(jr), tile(Pr), tile(sr))), tol,
+          f"{kind} {nx} {prec}", big)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_one_launch_equals_two(S3, prec):  # noqa: F811
+    """A mask without void takes the two launches: the same state as the
+    periodic box's one launch, to the bit."""
+    box = box_of("periodic", 71, 113, 108)
+    geo = B.Box3(**{**box.__dict__, "mask": np.ones((box.nz, box.ny, box.nx), np.uint8),
+                    "links": np.zeros(0, B.LINK3_DTYPE), "groups": []})
+    vel = B.random_velocity(box, 5, 1e-3)
+    res = []
+    for b in (box, geo):
+        with S3.Solver3(b, prec) as s:
+            s.init_fields(vel=vel)
+            s.step(6)
+            s.sync()
+            res.append((s.displacement(), *s.moments()))
+    for x, y in zip(*res):
+        np.testing.assert_array_equal(x, y)
