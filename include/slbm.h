@@ -199,7 +199,9 @@ int slbm_time(slbm_handle h, int64_t* step, double* t_user);
  * the state is read and written once per two steps (seg_rows + 6 waves per
  * tile, 58 output columns; an odd step count ends with one single step).
  * seg_rows is at most 14 (10 with strip 58); 0 keeps the library's choice.
- * With strip 58 the library also lists, per tile, the plate's cut links in
+ * seg_rows 0 with strip 0, the state after slbm_create, leaves the whole
+ * launch to the library: two steps per launch, rows by the plate's size.
+ * For two steps per launch the library also lists, per tile, the plate's cut links in
  * the tile's reach (slbm_boundary_lists), so that the tile evaluates the
  * section 4 rules of all of them together; it allocates device memory for
  * the lists (SLBM_E_NOMEM if none is left).  SLBM_E_INVAL beyond the limits.

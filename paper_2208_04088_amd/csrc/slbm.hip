@@ -466,8 +466,8 @@ struct slbm_s {
     std::vector<char> link_host;
     std::vector<int32_t> link_site;
     int ngroups = 0;
+    void* recs = nullptr;            // the records, then rec_start in the same block
     int32_t* rec_start = nullptr;
-    void* recs = nullptr;
     int rec_seg = 0;
     bool rec_fit = false;
     int64_t rec_bytes = 0;
@@ -582,32 +582,54 @@ hipError_t dev_alloc(slbm_s* h, void** p, size_t n);
 // Rows per tile of the two-step kernel for a requested number (0: default).
 int seg2_rows(int seg) { return std::max(1, std::min(seg > 0 ? seg : 6, kMaxTileRows2)); }
 
+// Rows per tile when the launch is left to the library, which then takes two
+// steps per launch: the fewest of 2, 4, 6, 8 that leave a workgroup a compute
+// unit (256), where a launch is one tile's latency, else the tallest tiles,
+// whose halo costs least.  us per step at 2 4 6 8 10 rows (one step per launch,
+// the default before, in brackets):
+//   fp32 80^2 3.6 3.9 3.9 4.1 4.3 (7.2)  320^2 7.0 4.5 4.7 4.3 4.5 (9.6)  701x354 9.6 7.1 6.2 6.2 5.5 (9.0)
+//        1024^2 29 18 15 15 13 (22)      2048^2 127 80 66 64 55 (100)
+//   fp64 80^2 4.2 4.4 4.8 5.0 5.3 (8.5)  200^2 7.4 4.5 4.8 5.0 5.3 (10.7) 701x354 19.6 13.5 11.7 10.7 10.1 (16.9)
+//        1024^2 60 36 29 26 25 (36)      2048^2 264 164 133 116 107 (172)
+int default_rows2(const slbm_s* h)
+{
+    const long long strips = (h->nx + kStrip2 - 1) / kStrip2;
+    for (int r = 2; r < kMaxTileRows2; r += 2)
+        if (strips * ((h->ny + r - 1) / r) <= 256) return r;
+    return kMaxTileRows2;
+}
+
+// Whether the launch is the library's choice, and the rows per tile of a
+// launch of two steps (0: the launch is of one step).
+bool launch_is_default(const slbm_s* h) { return !h->two && h->seg == 0 && h->wide < 0; }
+int launch_rows2(const slbm_s* h)
+{
+    return h->two ? seg2_rows(h->seg) : (launch_is_default(h) ? default_rows2(h) : 0);
+}
+
 // Frees a plate's tile lists: at once for a single plate (hipFree waits for
 // the device), for a batch plate back to the batch's arena once the launches
 // and readouts queued so far have completed.
 void drop_tile_records(slbm_s* h)
 {
-    if (h->arena && (h->rec_start || h->recs)) {
+    if (h->arena && h->recs) {
         if (h->batch) {
             hipEvent_t ec = nullptr, es = nullptr;
             if (hipEventCreateWithFlags(&ec, hipEventDisableTiming) == hipSuccess &&
                 hipEventCreateWithFlags(&es, hipEventDisableTiming) == hipSuccess &&
                 hipEventRecord(ec, batch_compute_stream(h->batch)) == hipSuccess &&
                 hipEventRecord(es, h->stream) == hipSuccess) {
-                h->arena->release_after({ec, es}, {h->rec_start, h->recs});
+                h->arena->release_after({ec, es}, {h->recs});
             } else {
                 if (ec) (void)hipEventDestroy(ec);
                 if (es) (void)hipEventDestroy(es);
                 (void)hipDeviceSynchronize();
-                h->arena->release(h->rec_start);
                 h->arena->release(h->recs);
             }
         } else {
-            h->arena->release(h->rec_start);
             h->arena->release(h->recs);
         }
     } else {
-        if (h->rec_start) (void)hipFree(h->rec_start);
         if (h->recs) (void)hipFree(h->recs);
     }
     h->rec_start = nullptr;
@@ -731,8 +753,9 @@ int build_tile_records(slbm_s* h, int seg)
         r.meta = d.k | (d.kind << 4) | (d.behind << 6) | ((d.g1 + 1) << 8) | ((d.g2 + 1) << 16);
         r.pos = lay.pos[k];
     }
-    hipError_t e = dev_alloc(h, (void**)&h->rec_start, start.size() * sizeof(int32_t));
-    if (e == hipSuccess) e = dev_alloc(h, &h->recs, std::max<size_t>(1, total) * sizeof(TileRec<real>));
+    // one block: the records, then the tiles' first records
+    const size_t rb = total * sizeof(TileRec<real>), sb = start.size() * sizeof(int32_t);
+    const hipError_t e = dev_alloc(h, &h->recs, rb + sb);
     if (e != hipSuccess) {
         drop_tile_records(h);
         h->rec_seg = seg;
@@ -741,10 +764,11 @@ int build_tile_records(slbm_s* h, int seg)
         if (e == hipErrorOutOfMemory) return fail(SLBM_E_NOMEM, "no device memory for the tile record lists");
         HIP_TRY(e);
     }
-    HIP_TRY(hipMemcpyAsync(h->rec_start, start.data(), start.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                           h->stream));
-    if (total)
-        HIP_TRY(hipMemcpyAsync(h->recs, rec.data(), total * sizeof(TileRec<real>), hipMemcpyHostToDevice, h->stream));
+    h->rec_start = (int32_t*)((char*)h->recs + rb);
+    std::vector<char> stage(rb + sb);
+    if (rb) std::memcpy(stage.data(), rec.data(), rb);
+    std::memcpy(stage.data() + rb, start.data(), sb);
+    HIP_TRY(hipMemcpyAsync(h->recs, stage.data(), rb + sb, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->rec_fit = true;
     h->rec_bytes = (int64_t)(start.size() * sizeof(int32_t) + total * sizeof(TileRec<real>));
@@ -817,7 +841,7 @@ int launch_step2_raw(slbm_s* h, int seg)
 template <typename real>
 int launch_step2(slbm_s* h)
 {
-    StepArgs<real> a = make_args2<real>(h, h->cur, h->seg);
+    StepArgs<real> a = make_args2<real>(h, h->cur, launch_rows2(h));
     dispatch_step2<real>(h, a);
     HIP_TRY(hipGetLastError());
     h->cur ^= 1;
@@ -923,8 +947,7 @@ hipError_t dev_alloc(slbm_s* h, void** p, size_t n)
 // The plate's own device blocks (not the batch's divergence word or scratch).
 std::vector<void*> plate_blocks(slbm_s* h)
 {
-    std::vector<void*> v = {h->buf[0], h->buf[1], h->U, h->flags, h->bidx, h->links, h->groups, h->rec_start,
-                            h->recs};
+    std::vector<void*> v = {h->buf[0], h->buf[1], h->U, h->flags, h->bidx, h->links, h->groups, h->recs};
     if (!h->ext_flag) v.push_back(h->diverged);
     if (!h->batch) v.push_back(h->scratch);
     return v;
@@ -1028,9 +1051,8 @@ int upload_links(slbm_s* h, const std::vector<slbm_link>& L, const std::vector<u
         const hipError_t e = dev_alloc(h, &h->links, d.size() * sizeof(LinkDev<real>));
         if (e == hipErrorOutOfMemory) return fail(SLBM_E_NOMEM, "no device memory for the link records");
         HIP_TRY(e);
-        HIP_TRY(hipMemcpyAsync(h->links, d.data(), d.size() * sizeof(LinkDev<real>), hipMemcpyHostToDevice,
-                               h->stream));
-        HIP_TRY(hipStreamSynchronize(h->stream));
+        // from the copy the handle keeps: the caller synchronises later
+        HIP_TRY(hipMemcpyAsync(h->links, h->link_host.data(), h->link_host.size(), hipMemcpyHostToDevice, h->stream));
     }
     return SLBM_OK;
 }
@@ -1167,7 +1189,12 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
         return fail(SLBM_E_INVAL, "device %d out of range", p->device);
     }
     DeviceGuard dg(h->device);
-    auto bail = [&](int rc) { free_all(h); delete h; return rc; };
+    auto bail = [&](int rc) {
+        if (h->stream) (void)hipStreamSynchronize(h->stream);      // copies queued below read this function's arrays
+        free_all(h);
+        delete h;
+        return rc;
+    };
 #define TRY_OR_BAIL(expr)                                                               \
     do {                                                                                \
         hipError_t e_ = (expr);                                                         \
@@ -1195,37 +1222,30 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
     } else {
         TRY_OR_BAIL(dev_alloc(h, (void**)&h->diverged, sizeof(unsigned int)));
     }
-    {
-        std::vector<uint8_t> fl((size_t)h->plane, (uint8_t)kVoid);
-        std::vector<int32_t> bi((size_t)h->plane, -1);
-        for (int s = 0; s < n; ++s) {
-            if (!mat[s]) continue;
-            const size_t d = (size_t)sidx(s % nx, s / nx, h->ld);
-            fl[d] = cut[s];
-        }
-        for (size_t i = 0; i < L.size(); ++i) {
-            const int s = L[i].site;
-            const size_t d = (size_t)sidx(s % nx, s / nx, h->ld);
-            if (bi[d] < 0) bi[d] = (int32_t)i;
-        }
-        // queued on the plate's stream (for batch plates the batch's side
-        // stream, so that the upload does not wait for running steps)
-        TRY_OR_BAIL(hipMemcpyAsync(h->flags, fl.data(), fl.size(), hipMemcpyHostToDevice, h->stream));
-        TRY_OR_BAIL(hipMemcpyAsync(h->bidx, bi.data(), bi.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                                   h->stream));
-        TRY_OR_BAIL(hipStreamSynchronize(h->stream));
+    // what is uploaded stays alive until the one synchronisation at the end (or
+    // in bail); queued on the plate's stream (for batch plates the batch's side
+    // stream, so that the upload does not wait for running steps)
+    std::vector<uint8_t> fl((size_t)h->plane, (uint8_t)kVoid);
+    std::vector<int32_t> bi((size_t)h->plane, -1);
+    for (int s = 0; s < n; ++s) {
+        if (!mat[s]) continue;
+        const size_t d = (size_t)sidx(s % nx, s / nx, h->ld);
+        fl[d] = cut[s];
     }
-    {
-        std::vector<GroupDev> gd(std::max(1, p->n_groups));
-        for (int g = 0; g < p->n_groups; ++g) {
-            gd[g].profile = p->groups[g].profile;
-            gd[g].ramp_steps = p->groups[g].profile == SLBM_PROFILE_RAMP ? p->groups[g].ramp_time / h->dt_user : 1.0;
-        }
-        TRY_OR_BAIL(dev_alloc(h, (void**)&h->groups, gd.size() * sizeof(GroupDev)));
-        TRY_OR_BAIL(hipMemcpyAsync(h->groups, gd.data(), gd.size() * sizeof(GroupDev), hipMemcpyHostToDevice,
-                                   h->stream));
-        TRY_OR_BAIL(hipStreamSynchronize(h->stream));
+    for (size_t i = 0; i < L.size(); ++i) {
+        const int s = L[i].site;
+        const size_t d = (size_t)sidx(s % nx, s / nx, h->ld);
+        if (bi[d] < 0) bi[d] = (int32_t)i;
     }
+    TRY_OR_BAIL(hipMemcpyAsync(h->flags, fl.data(), fl.size(), hipMemcpyHostToDevice, h->stream));
+    TRY_OR_BAIL(hipMemcpyAsync(h->bidx, bi.data(), bi.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
+    std::vector<GroupDev> gd(std::max(1, p->n_groups));
+    for (int g = 0; g < p->n_groups; ++g) {
+        gd[g].profile = p->groups[g].profile;
+        gd[g].ramp_steps = p->groups[g].profile == SLBM_PROFILE_RAMP ? p->groups[g].ramp_time / h->dt_user : 1.0;
+    }
+    TRY_OR_BAIL(dev_alloc(h, (void**)&h->groups, gd.size() * sizeof(GroupDev)));
+    TRY_OR_BAIL(hipMemcpyAsync(h->groups, gd.data(), gd.size() * sizeof(GroupDev), hipMemcpyHostToDevice, h->stream));
     {
         int rc = h->precision == SLBM_FP32 ? upload_links<float>(h, L, cut, p) : upload_links<double>(h, L, cut, p);
         if (rc) return bail(rc);
@@ -1240,6 +1260,9 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
     h->cur = 0;
     h->step = 0;
     h->local = true;
+    // lists for the library's own launch (a batch has its own; a plate without
+    // room for them takes the rules site by site)
+    if (!arena && tile_records(h, default_rows2(h)) != SLBM_OK) drop_tile_records(h);
     *out = h;
     return SLBM_OK;
 }
@@ -1284,7 +1307,7 @@ int slbm_step(slbm_handle h, int64_t nsteps)
         if (nsteps < 0) return fail(SLBM_E_INVAL, "negative step count");
         DeviceGuard dg(h->device);
         int64_t i = 0;
-        if (h->two) {
+        if (launch_rows2(h)) {
             for (; i + 2 <= nsteps; i += 2) {
                 int rc = h->precision == SLBM_FP32 ? launch_step2<float>(h) : launch_step2<double>(h);
                 if (rc) return rc;
@@ -1469,9 +1492,9 @@ int slbm_set_launch(slbm_handle h, int32_t seg_rows, int32_t strip)
             return fail(SLBM_E_INVAL, "strip must be 0, 58, 62 or 64");
         if (seg_rows > (strip == kStrip2 ? kMaxTileRows2 : kMaxTileRows))
             return fail(SLBM_E_INVAL, "rows per tile above the maximum (14; 10 with two steps per launch)");
-        if (strip == kStrip2) {
+        if (strip == kStrip2 || (strip == 0 && seg_rows == 0)) {
             DeviceGuard dg(h->device);
-            const int rc = tile_records(h, seg_rows);
+            const int rc = tile_records(h, strip == kStrip2 ? seg_rows : default_rows2(h));
             if (rc) return rc;
         }
         h->seg = seg_rows;
