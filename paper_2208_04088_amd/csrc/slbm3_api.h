@@ -29,7 +29,8 @@ struct slbm3_s {
     bool local = true;
     double* U = nullptr;
     void* dens = nullptr;
-    void* wall[2] = {nullptr, nullptr};   // the walls' parts (wall_parts3): k3_march reads [wcur], writes the other
+    // the walls' parts (wall_parts3), one block: k3_march reads [wcur], writes the other
+    void* wall[2] = {nullptr, nullptr};
     int wcur = 0;
     bool wall_fresh = false;              // wall[wcur] belongs to the current state
     unsigned int* diverged = nullptr;
@@ -41,7 +42,11 @@ struct slbm3_s {
     uint32_t* flags = nullptr;
     int32_t* bidx = nullptr;
     void* links = nullptr;
-    void* lval = nullptr;            // per link record: (A, s_kappa) of the rule (k3_step, k3_links_ext)
+    // per link record: (A, s_kappa) of the rule (k3_step, k3_links_ext); k3_march
+    // reads [lcur] and writes the other
+    void* lval[2] = {nullptr, nullptr};
+    int lcur = 0;
+    int32_t* rowrec = nullptr;       // per 64-site chunk of a row: first record
     int32_t* wrec = nullptr;         // per workgroup of k3_step: first record
     int32_t* elink = nullptr;        // the records whose Neumann data are extrapolated
     int64_t n_ext = 0;
@@ -101,7 +106,10 @@ Step3Args<real> make_args3(const slbm3_s* h, int src)
     a.flags = h->flags;
     a.bidx = h->bidx;
     a.links = (const Link3<real>*)h->links;
-    a.lval = (real*)h->lval;
+    a.lval = (real*)h->lval[h->lcur];
+    a.lval_next = (real*)h->lval[h->lcur ^ 1];
+    a.rowrec = h->rowrec;
+    a.nlinks = (int)h->n_links;
     a.wrec = h->wrec;
     return a;
 }
@@ -119,6 +127,7 @@ struct Geo3 {
     std::vector<double> skap;        // per record: kappa (Dirichlet), -kappa (Neumann) or 0 (ext)
     std::vector<int32_t> elink;      // the ext records
     std::vector<int32_t> wrec;       // per workgroup of k3_step: its first record, then the count
+    std::vector<int32_t> rowrec;     // per 64-site chunk of a row: its first record, then the count
     uint64_t hash = 0;               // FNV-1a of the mask and of each cut link's site, direction, q,
                                      // groups and normals, in record order
 };
@@ -388,6 +397,14 @@ int build_geo3(const slbm3_params* p, const slbm3_s* h, Geo3& g)
             g.wrec[(size_t)w] = (int32_t)r;
         }
         g.wrec[(size_t)nwg] = (int32_t)g.recs.size();
+        g.rowrec.resize((size_t)ntiles + 1);
+        r = 0;
+        for (long long t = 0; t < ntiles; ++t) {
+            const long long first = t / chunks * nx + 64 * (t % chunks);
+            while (r < g.recs.size() && g.recs[r].site < first) ++r;
+            g.rowrec[(size_t)t] = (int32_t)r;
+        }
+        g.rowrec[(size_t)ntiles] = (int32_t)g.recs.size();
     }
     return SLBM_OK;
 }
@@ -463,19 +480,29 @@ int launch3(slbm3_s* h, int what)
 int launch3_any(slbm3_s* h, int what);
 
 // Whether k3_march takes the next step.  Not a state that is read in place
-// (the first step after creation or initial fields), not cut links, not walls
-// whose Neumann data are extrapolated (they read a second site) or that share
-// one site.  And only boxes large enough: below, a workgroup's few planes in
+// (the first step after creation or initial fields), not a mask without cut
+// links, not walls whose Neumann data are extrapolated (they read a second
+// site) or that share one site.  And only boxes large enough: below, a workgroup's few planes in
 // series (2.6 us each in single, 5 us in double precision) take longer than
 // the two launches, whose every load is independent.  us per step, two
 // launches and one:
-//   fp32 slab  64^3 21 24   200x60x40 29 34   90x130x70 51 48   96^3 56 47   128^3 133 103   256^3 905 701
-//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 38 40   96^3 40 37   128^3 113 98    256^3 901 689
-//   fp64 slab  40^3 19 20   64^3 35 28        90x130x70 97 90   96^3 108 84  128^3 254 179
-//   fp64 per.  40^3 14 16   64^3 25 22        90x130x70 73 87   96^3 85 80   128^3 223 174   256^3 1682 1259
+//   fp32 slab  64^3 21 24   200x60x40 29 34   90x130x70 51 48   96^3 56 47   128^3 133 100   256^3 905 683
+//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 38 40   96^3 40 37   128^3 113 93    256^3 901 669
+//   fp64 slab  40^3 19 20   64^3 35 28        90x130x70 97 90   96^3 108 79  128^3 254 177
+//   fp64 per.  40^3 14 16   64^3 25 22        90x130x70 73 87   96^3 85 80   128^3 223 174   256^3 1682 1229
+// With cut links the series is longer (6 us a plane), and a row whose last
+// chunk is short pays for all of it (porous solids, n^3):
+//   fp32  100 56 84   120 110 101   128 128 107   130 155 163   150 238 249   160 256 235   180 389 361   256 981 752
+//   fp64  100 125 134  128 243 220   130 294 279   150 420 398   180 662 563   256 1793 1549
 bool march3(const slbm3_s* h)
 {
-    if (h->local || h->geo) return false;
+    if (h->local) return false;
+    if (h->geo) {
+        // a chunk's 64 lanes: how many of 16 hold sites
+        const long long lanes = 16LL * h->nx / (64 * ((h->nx + 63) / 64));
+        if (h->n_links == 0) return false;
+        return h->precision == SLBM_FP32 ? h->plane >= 4000000 || (h->plane >= 1500000 && lanes >= 14) : h->plane >= 2000000;
+    }
     if (!h->px) {
         if (h->nx < 2) return false;
         for (int s = 0; s < 2; ++s)
@@ -487,34 +514,40 @@ bool march3(const slbm3_s* h)
 // Planes a k3_march workgroup marches through, for `tiles` tiles of rows over
 // nz planes: a workgroup takes depth + 2 planes' time and a little to start,
 // and the chip runs `slots` of them at once, so the depth that needs the
-// fewest plane times in whole rounds.
+// fewest plane times in whole rounds (among depths that cost about the same
+// the smaller: the last round ends more evenly; 256^3 slab 685 us at 32, 693 at
+// 64).
 int march_depth(long long tiles, int nz, int slots)
 {
     int best = 1;
     long long cost = -1;
     for (int d = 1; d <= std::min(nz, 64); ++d) {
-        const long long wgs = tiles * ((nz + d - 1) / d), c = (wgs + slots - 1) / slots * (d + 3);
+        const long long wgs = tiles * ((nz + d - 1) / d), c = 6 * ((wgs + slots - 1) / slots * (d + 3)) + d;
         if (cost < 0 || c < cost) { cost = c; best = d; }
     }
     return best;
 }
 
-template <typename real, bool PX>
+template <typename real, bool PX, bool GEO>
 int launch3_march(slbm3_s* h)
 {
     Step3Args<real> a = make_args3<real>(h, h->cur);
     a.rows = std::min(kMarchWaves(sizeof(real)) - 2, h->ny);
     a.nch = (h->nx + 63) / 64;
     a.nyt = (h->ny + a.rows - 1) / a.rows;
-    a.depth = march_depth((long long)a.nch * a.nyt, h->nz, sizeof(real) == 4 ? 512 : 256);
+    a.depth = march_depth((long long)a.nch * a.nyt, h->nz, sizeof(real) == 4 && !GEO ? 512 : 256);
     a.mtiles = a.nch * a.nyt * ((h->nz + a.depth - 1) / a.depth);
-    a.xgroup = 8;
+    a.xgroup = 16;
+    if (GEO && h->n_ext > 0)
+        hipLaunchKernelGGL((k3_links_ext<real>), dim3((unsigned)((h->n_ext + 255) / 256)), dim3(256), 0, h->stream, a,
+                           (const int32_t*)h->elink, (int)h->n_ext);
     if (!PX && !h->wall_fresh)
         hipLaunchKernelGGL((k3_wall_parts<real>), dim3((unsigned)((h->ny * h->nz + 255) / 256), 2), dim3(256), 0,
                            h->stream, a, (real*)h->wall[h->wcur]);
-    hipLaunchKernelGGL((k3_march<real, PX>), dim3((unsigned)((a.mtiles + 8 * a.xgroup - 1) / (8 * a.xgroup) * (8 * a.xgroup))), dim3(64 * (a.rows + 2)), 0,
+    hipLaunchKernelGGL((k3_march<real, PX, GEO>), dim3((unsigned)((a.mtiles + 8 * a.xgroup - 1) / (8 * a.xgroup) * (8 * a.xgroup))), dim3(64 * (a.rows + 2)), 0,
                        h->stream, a);
     HIP_TRY(hipGetLastError());
+    if (GEO) h->lcur ^= 1;
     if (!PX) {
         h->wcur ^= 1;
         h->wall_fresh = true;
@@ -528,8 +561,12 @@ int step3(slbm3_s* h)
         h->wall_fresh = false;
         return launch3_any(h, 0);
     }
-    if (h->precision == SLBM_FP32) return h->px ? launch3_march<float, true>(h) : launch3_march<float, false>(h);
-    return h->px ? launch3_march<double, true>(h) : launch3_march<double, false>(h);
+    if (h->precision == SLBM_FP32) {
+        if (h->geo) return launch3_march<float, true, true>(h);
+        return h->px ? launch3_march<float, true, false>(h) : launch3_march<float, false, false>(h);
+    }
+    if (h->geo) return launch3_march<double, true, true>(h);
+    return h->px ? launch3_march<double, true, false>(h) : launch3_march<double, false, false>(h);
 }
 
 int launch3_any(slbm3_s* h, int what)
@@ -579,8 +616,8 @@ int ensure_scratch3(slbm3_s* h, int planes)
 void free3(slbm3_s* h)
 {
     for (void* p : {h->buf[0], h->buf[1], (void*)h->U, h->dens, (void*)h->diverged, (void*)h->scratch,
-                    (void*)h->flags, (void*)h->bidx, h->links, h->lval, (void*)h->wrec, (void*)h->elink, h->wall[0],
-                    h->wall[1]})
+                    (void*)h->flags, (void*)h->bidx, h->links, h->lval[0],
+                    (void*)h->rowrec, (void*)h->wrec, (void*)h->elink, h->wall[0]})
         if (p) (void)hipFree(p);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
@@ -682,8 +719,11 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
         TRY_OR_BAIL(hipMalloc((void**)&h->U, (size_t)3 * h->stride * sizeof(double)));
         TRY_OR_BAIL(hipMalloc(&h->dens, (size_t)plane * h->esize));
         TRY_OR_BAIL(hipMalloc((void**)&h->diverged, sizeof(unsigned int)));
-        if (!h->px)
-            for (void*& w : h->wall) TRY_OR_BAIL(hipMalloc(&w, (size_t)10 * h->ny * h->nz * h->esize));
+        if (!h->px) {
+            const size_t one = ((size_t)10 * h->ny * h->nz * h->esize + 255) / 256 * 256;
+            TRY_OR_BAIL(hipMalloc(&h->wall[0], 2 * one));
+            h->wall[1] = (char*)h->wall[0] + one;
+        }
         // rest state: g = 0 (f = r), U = 0
         TRY_OR_BAIL(hipMemsetAsync(h->buf[0], 0, pop, h->stream));
         TRY_OR_BAIL(hipMemsetAsync(h->buf[1], 0, pop, h->stream));
@@ -698,6 +738,9 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
                                        hipMemcpyHostToDevice, h->stream));
             TRY_OR_BAIL(hipMalloc((void**)&h->wrec, geo.wrec.size() * sizeof(int32_t)));
             TRY_OR_BAIL(hipMemcpyAsync(h->wrec, geo.wrec.data(), geo.wrec.size() * sizeof(int32_t),
+                                       hipMemcpyHostToDevice, h->stream));
+            TRY_OR_BAIL(hipMalloc((void**)&h->rowrec, geo.rowrec.size() * sizeof(int32_t)));
+            TRY_OR_BAIL(hipMemcpyAsync(h->rowrec, geo.rowrec.data(), geo.rowrec.size() * sizeof(int32_t),
                                        hipMemcpyHostToDevice, h->stream));
             if (!geo.recs.empty()) {
                 if (h->precision == SLBM_FP32) {
@@ -715,17 +758,14 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
                 // (A, s_kappa) per record: the parts come from the steps, s_kappa from here
                 std::vector<double> lv(2 * geo.recs.size(), 0.0);
                 for (size_t r = 0; r < geo.recs.size(); ++r) lv[2 * r + 1] = geo.skap[r];
-                TRY_OR_BAIL(hipMalloc(&h->lval, lv.size() * h->esize));
-                if (h->precision == SLBM_FP32) {
-                    const std::vector<float> lf(lv.begin(), lv.end());
-                    TRY_OR_BAIL(hipMemcpyAsync(h->lval, lf.data(), lf.size() * sizeof(float), hipMemcpyHostToDevice,
-                                               h->stream));
-                    TRY_OR_BAIL(hipStreamSynchronize(h->stream));
-                } else {
-                    TRY_OR_BAIL(hipMemcpyAsync(h->lval, lv.data(), lv.size() * sizeof(double), hipMemcpyHostToDevice,
-                                               h->stream));
-                    TRY_OR_BAIL(hipStreamSynchronize(h->stream));
-                }
+                const std::vector<float> lf(lv.begin(), lv.end());
+                const void* src = h->precision == SLBM_FP32 ? (const void*)lf.data() : (const void*)lv.data();
+                const size_t one = (lv.size() * h->esize + 255) / 256 * 256;
+                TRY_OR_BAIL(hipMalloc(&h->lval[0], 2 * one));
+                h->lval[1] = (char*)h->lval[0] + one;
+                for (void* to : h->lval)
+                    TRY_OR_BAIL(hipMemcpyAsync(to, src, lv.size() * h->esize, hipMemcpyHostToDevice, h->stream));
+                TRY_OR_BAIL(hipStreamSynchronize(h->stream));
                 if (h->n_ext > 0) {
                     TRY_OR_BAIL(hipMalloc((void**)&h->elink, geo.elink.size() * sizeof(int32_t)));
                     TRY_OR_BAIL(hipMemcpyAsync(h->elink, geo.elink.data(), geo.elink.size() * sizeof(int32_t),
@@ -893,7 +933,8 @@ int slbm3_device_bytes(slbm3_handle h, int64_t* bytes)
         if (!h->px) b += (int64_t)2 * 10 * h->ny * h->nz * (int64_t)h->esize;
         if (h->geo) {
             const long long nwg = (((long long)(h->nx + 63) / 64) * h->ny * h->nz + 3) / 4;
-            b += h->plane * 8 + (int64_t)h->link_bytes + 2 * h->n_links * (int64_t)h->esize + (nwg + 1) * 4 +
+            const long long nch = ((long long)(h->nx + 63) / 64) * h->ny * h->nz;
+            b += h->plane * 8 + (int64_t)h->link_bytes + 4 * h->n_links * (int64_t)h->esize + (nwg + nch + 2) * 4 +
                  h->n_ext * 4;
         }
         *bytes = b;
@@ -935,7 +976,7 @@ int slbm3_save(slbm3_handle h, void* buf, size_t* bytes)
         HIP_TRY(hipMemcpyAsync(p + sizeof hd, h->buf[h->cur], pop, hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipMemcpyAsync(p + sizeof hd + pop, h->U, ub, hipMemcpyDeviceToHost, h->stream));
         if (h->n_links > 0)
-            HIP_TRY(hipMemcpyAsync(p + sizeof hd + pop + ub, h->lval, (size_t)2 * h->n_links * h->esize,
+            HIP_TRY(hipMemcpyAsync(p + sizeof hd + pop + ub, h->lval[h->lcur], (size_t)2 * h->n_links * h->esize,
                                    hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         hd.diverged = (int32_t)flag;
@@ -965,7 +1006,7 @@ int slbm3_load(slbm3_handle h, const void* buf, size_t bytes)
         HIP_TRY(hipMemcpyAsync(h->buf[0], p + sizeof hd, pop, hipMemcpyHostToDevice, h->stream));
         HIP_TRY(hipMemcpyAsync(h->U, p + sizeof hd + pop, ub, hipMemcpyHostToDevice, h->stream));
         if (h->n_links > 0)
-            HIP_TRY(hipMemcpyAsync(h->lval, p + sizeof hd + pop + ub, (size_t)2 * h->n_links * h->esize,
+            HIP_TRY(hipMemcpyAsync(h->lval[h->lcur], p + sizeof hd + pop + ub, (size_t)2 * h->n_links * h->esize,
                                    hipMemcpyHostToDevice, h->stream));
         unsigned int flag = (unsigned int)hd.diverged;
         HIP_TRY(hipMemcpyAsync(h->diverged, &flag, sizeof flag, hipMemcpyHostToDevice, h->stream));

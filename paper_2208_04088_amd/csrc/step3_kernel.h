@@ -112,6 +112,8 @@ struct Step3Args {
     const int32_t* bidx;
     const Link3<real>* links;
     real* lval;                // per record: (A, s_kappa), see cut_links3
+    real* lval_next;           // the same, written by k3_march for the next step
+    const int32_t* rowrec;     // per 64-site chunk of a row: its first record (one more: the count)
     const int32_t* wrec;       // per workgroup of k3_step: its first record (one more: the count)
     // the groups' time profiles per slot, at the time of the state the pulls
     // read (pf_pull) and of the state the step produces (pf_next)
@@ -119,7 +121,7 @@ struct Step3Args {
     // k3_march: its tiles (rows, planes, how many of each, 64-site chunks), the
     // walls' returned parts it reads and writes (see wall_parts3) and the
     // walls' values at the time of the state it produces
-    int rows, depth, nyt, nch, mtiles, xgroup;
+    int rows, depth, nyt, nch, mtiles, xgroup, nlinks;
     const real* wsrc;
     real* wdst;
     real wskap[2], wval_next[2][3];
@@ -686,6 +688,32 @@ __device__ __forceinline__ real wall_grad3(int side, real dr)
     return side == 0 ? -dr : (side == 1 ? dr : real(0));
 }
 
+// The gradient from the densities of all 18 neighbours (CUTS: across a cut
+// link of fl the neighbour is extrapolated).
+template <bool CUTS, typename real>
+__device__ __forceinline__ void grad_nb3(real nb[kQ], real dr, uint32_t fl, int side, real grad[3])
+{
+    if (CUTS && (fl & kCutMask3) != 0u) {
+        real sub[kQ];
+#pragma unroll
+        for (int i = 1; i < kQ; ++i) {
+            const bool ci = (fl >> (i - 1)) & 1u, co = (fl >> (opp3(i) - 1)) & 1u;
+            sub[i] = ci ? (co ? dr : real(2) * dr - nb[opp3(i)]) : nb[i];
+        }
+#pragma unroll
+        for (int i = 1; i < kQ; ++i) nb[i] = sub[i];
+    }
+    // planes z - 1, z, z + 1 (only the terms that enter are used)
+    const real o = real(0);
+    const PlaneTerms3<real> lo = plane_terms3(nb[6], nb[13], nb[12], nb[17], nb[16], o, o, o, o, side);
+    const PlaneTerms3<real> in = plane_terms3(dr, nb[1], nb[2], nb[3], nb[4], nb[7], nb[10], nb[9], nb[8], side);
+    const PlaneTerms3<real> hi = plane_terms3(nb[5], nb[11], nb[14], nb[15], nb[18], o, o, o, o, side);
+    grad[0] = with_share3(with_share3(in.gx, lo.sx), hi.sx);
+    if (side >= 0) grad[0] += wall_grad3(side, dr);
+    grad[1] = with_share3(with_share3(in.gy, lo.sy), hi.sy);
+    grad[2] = hi.tz - lo.tz;
+}
+
 // The gradient from the delta-rho buffer.
 template <typename real, bool PX, bool GEO = false>
 __device__ __forceinline__ void grad3(const Step3Args<real>& a, const Site3& st, real dr, real grad[3],
@@ -712,25 +740,7 @@ __device__ __forceinline__ void grad3(const Step3Args<real>& a, const Site3& st,
             if (kCX[i]) nb[i] = dr;
     }
     const int side = cutm == cutp ? -1 : (cutm ? 0 : 1);
-    if (GEO && (fl & kCutMask3) != 0u) {
-        real sub[kQ];
-#pragma unroll
-        for (int i = 1; i < kQ; ++i) {
-            const bool ci = (fl >> (i - 1)) & 1u, co = (fl >> (opp3(i) - 1)) & 1u;
-            sub[i] = ci ? (co ? dr : real(2) * dr - nb[opp3(i)]) : nb[i];
-        }
-#pragma unroll
-        for (int i = 1; i < kQ; ++i) nb[i] = sub[i];
-    }
-    // planes z - 1, z, z + 1 (only the terms that enter are used)
-    const real o = real(0);
-    const PlaneTerms3<real> lo = plane_terms3(nb[6], nb[13], nb[12], nb[17], nb[16], o, o, o, o, side);
-    const PlaneTerms3<real> in = plane_terms3(dr, nb[1], nb[2], nb[3], nb[4], nb[7], nb[10], nb[9], nb[8], side);
-    const PlaneTerms3<real> hi = plane_terms3(nb[5], nb[11], nb[14], nb[15], nb[18], o, o, o, o, side);
-    grad[0] = with_share3(with_share3(in.gx, lo.sx), hi.sx);
-    if (!PX) grad[0] += wall_grad3(side, dr);
-    grad[1] = with_share3(with_share3(in.gy, lo.sy), hi.sy);
-    grad[2] = hi.tz - lo.tz;
+    grad_nb3<GEO>(nb, dr, fl, side, grad);
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs.  Each XCD takes groups of
@@ -852,10 +862,17 @@ __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
 // per step where the density pass and the step read it twice; the halo rows
 // (2 in 10) and planes (2 in depth + 2) come from L2.
 //
+// Cut links (GEO): the (A, s_kappa) of a row's links and of its two halo sites'
+// links come with its pulls (their place in the list follows from the row's
+// first record and the flags, so no load waits for another), and the parts for
+// the next step go to a second buffer, as workgroups that share a halo row
+// still read the first.
+//
 // Bound by HBM: 256^3 fp32 moves 3.25 GB a step (counters), the 200 B per
-// site it cannot do without, at 4.7 TB/s: 689 us periodic, 701 us with walls,
-// where the two launches move 4.8 GB in 901 and 905 us; fp64 1259 us against
-// 1682.  What it took, 256^3 fp32:
+// site it cannot do without, at 4.9 TB/s: 669 us periodic, 683 us with walls,
+// where the two launches move 4.8 GB in 901 and 905 us; fp64 1229 us against
+// 1682; the porous solid 752 against 981 us (its critical path is a cut row's
+// 700 further instructions, between two barriers).  What it took, 256^3 fp32:
 // - waves of an exact 64-site chunk (62-column strips waste a fifth of a
 //   256-site row), the two halo columns gathered by one more load a wave;
 // - collide_pairs3 (300 vector instructions a site-step, two launches: 1050);
@@ -864,13 +881,14 @@ __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
 //   (atomics that return nothing) instead of loaded, and not one spill, whose
 //   reload would wait for every load in flight (slab: 1500 us with 47 spilled
 //   registers, 731 with none);
-// - tiles dealt to the XCDs in groups of 8, so that the chip moves through one
+// - tiles dealt to the XCDs in groups of 16, so that the chip moves through one
 //   region of the box (groups of 8 to 32 689 us, contiguous bands 722, 1 711);
+// - stores past the L2 (689 -> 669 us, porous solid 854 -> 800);
 // - 8 rows: 6 rows 780 us (their halo, and a last tile of 4 rows), 14 rows 765;
 //   one or two workgroups on a CU make no difference.
 // fp64: 8 waves, what the LDS of a CU holds of their populations (110 KB).
 constexpr int kMarchWaves(int bytes) { return bytes == 4 ? 10 : 8; }     // waves of a workgroup at most
-constexpr int kMarchOcc(int bytes) { return bytes == 4 ? 5 : 2; }        // waves per SIMD it is compiled for
+constexpr int kMarchOcc(int bytes, bool geo) { return bytes == 4 ? (geo ? 3 : 5) : 2; }   // waves per SIMD it is compiled for
 
 // The parts from a state that no k3_march produced (a loaded one, or one that
 // the two launches advanced).
@@ -909,8 +927,10 @@ struct PlaneWalk {
         base += step;
         asm("" : "+s"(base));
     }
+    // read again only by the next launch: past the L2, which then holds the rows
+    // that neighbouring workgroups share
     template <typename T>
-    __device__ __forceinline__ void store(unsigned off, T v) const { *(gptr3<T>)(base + off) = v; }
+    __device__ __forceinline__ void store(unsigned off, T v) const { __builtin_nontemporal_store(v, (gptr3<T>)(base + off)); }
     // += in memory (one rounded sum, as a load, an add and a store)
     __device__ __forceinline__ void add(unsigned off, double v) const
     {
@@ -979,17 +999,44 @@ __device__ __forceinline__ bool halo_ret3(int lane)
 // Pulled populations of one plane: a row's, and the lane's share of the two
 // halo columns (lane i: population i of column x0 - 1, lane 32 + i of column
 // x0 + 64).
-template <typename real>
+// GEO: also the flags of the lane's site and of its halo site, and (A, s_kappa)
+// of the first 64 cut links of the wave's sites (lane l: link l) and of the
+// links next to them (lanes 0..17: the 18 before, which end with the left halo
+// site's; lanes 32..49: the 18 after, which begin with the right one's).
+template <typename real, bool GEO>
 struct Plane3 {
     real g[kQ];
     real halo;
 };
+template <typename real>
+struct Plane3<real, true> {
+    real g[kQ];
+    real halo;
+    uint32_t fl, hfl;
+    real la, ls, ha, hs;
+};
+// The records of a row chunk, and where those of its left halo site end and
+// those of its right one begin.
+struct RowRec3 {
+    int r0, r1, left, right;
+};
 
-template <typename real, bool PX>
-__global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(real))) void k3_march(Step3Args<real> a)
+template <typename real, bool PX, bool GEO>
+__global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(real), GEO)) void k3_march(Step3Args<real> a)
 {
     constexpr int NW = kMarchWaves(sizeof(real));
-    __shared__ real dens[2][NW][68];
+    constexpr int RING = GEO ? 4 : 2;                       // GEO: a cut site reads three planes
+    __shared__ real dens[RING][NW][68];
+    __shared__ real pairs[GEO ? NW : 1][GEO ? 64 : 1][2];
+    // GEO, fp32: a cut row's post-collision populations, for its links' parts (in
+    // double precision LDS has no room left; the lanes shuffle them)
+    constexpr bool STAGE = GEO && sizeof(real) == 4;
+    __shared__ real stage[STAGE ? NW : 1][STAGE ? kQ : 1][STAGE ? 64 : 1];
+    __shared__ real profile[kProfileSlots3];                // the groups' factors, indexed by record
+    if (GEO && threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < kProfileSlots3; ++k) profile[k] = a.pf_next[k];
+    }
     // a lane's own of the plane before: populations, and of grad its in-plane
     // part with the share of the plane below (x, y), minus that share (z), and
     // its own share of its neighbours' (x, y, z)
@@ -1028,7 +1075,21 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
     // the right halo column is the wall's own when one site follows the chunk
     const bool hwall = !PX && x0 + 65 == nx;                // uniform
 
-    auto issue = [&](int p, Plane3<real>& q) {
+    // GEO: the records of plane p's row chunk
+    auto row_recs = [&](int p) __attribute__((always_inline)) -> RowRec3 {
+        RowRec3 r{0, 0, 0, 0};
+        if constexpr (GEO) {
+            const int z = p < 0 ? p + nz : (p >= nz ? p - nz : p);
+            // never written by a kernel: scalar loads
+            const auto* rec = (const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.rowrec + (z * ny + y) * a.nch;
+            r.r0 = rec[ch];
+            r.r1 = rec[ch + 1];
+            r.left = rec[ch == 0 ? a.nch : ch];
+            r.right = rec[ch == a.nch - 1 ? 0 : ch + 1];
+        }
+        return r;
+    };
+    auto issue = [&](int p, Plane3<real, GEO>& q, const RowRec3& rr) __attribute__((always_inline)) {
         const int z = p < 0 ? p + nz : (p >= nz ? p - nz : p), zm = z == 0 ? nz - 1 : z - 1, zp = z == nz - 1 ? 0 : z + 1;
         // what follows from the lane is formed anew for every plane: held across
         // the loop it would cost the registers that let two workgroups share a CU
@@ -1063,11 +1124,81 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
             hp = a.wsrc + ((5 + hm) * nyz + ((long long)z * ny + y));
         }
         q.halo = *(gptr3<const real>)hp;
+        if constexpr (GEO) {
+            const unsigned r = (unsigned)(z * ny + y) * (unsigned)nx;
+            q.fl = a.flags[r + (unsigned)xv];
+            const unsigned hx = lv < 32 ? (x0 == 0 ? nx - 1 : x0 - 1) : (x0 + wd >= nx ? 0 : x0 + wd);
+            q.hfl = a.flags[r + hx];
+            // (A, s_kappa): one link a lane, repeating the first where there are fewer
+            const int l = rr.r0 + lv < rr.r1 ? rr.r0 + lv : min(rr.r0, a.nlinks - 1);
+            q.la = a.lval[2 * (long long)l];
+            q.ls = a.lval[2 * (long long)l + 1];
+            int hl = lv < 32 ? rr.left - 18 + min(lv, 17) : rr.right + min(lv - 32, 17);
+            hl = max(0, min(hl, a.nlinks - 1));
+            q.ha = a.lval[2 * (long long)hl];
+            q.hs = a.lval[2 * (long long)hl + 1];
+        }
+    };
+    // GEO: the cut links' returning populations of the row and of its halo sites
+    // (cut_links3's arithmetic), nothing at void sites
+    auto cut_pulls = [&](Plane3<real, GEO>& q, const RowRec3& rr) __attribute__((always_inline)) {
+        if constexpr (GEO) {
+            if (rr.r1 > rr.r0) {                            // uniform
+                pairs[wave][lane][0] = q.la;
+                pairs[wave][lane][1] = q.ls;
+                const uint32_t m = q.fl & kCutMask3;
+                // the links of the lanes before: the bits of every lane's count
+                const uint32_t n = lane < wd ? (uint32_t)__builtin_popcount(m) : 0u;
+                int before = 0;
+#pragma unroll
+                for (int b = 0; b < 5; ++b) {
+                    const unsigned long long v = __ballot((n >> b) & 1u);
+                    before += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(v >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)v, 0u)) << b;
+                }
+                before = __shfl(before, col);
+                const bool many = rr.r1 - rr.r0 > 64;       // uniform
+#pragma unroll
+                for (int p = 0; p < 9; ++p) {
+                    const int k = 2 * p + 1;
+                    const uint32_t b = (m >> (k - 1)) & 3u;
+                    const int l = before + __builtin_popcount(m & ((1u << (k - 1)) - 1u)), l1 = l + (int)(b & 1u);
+                    real A = pairs[wave][l & 63][0], s = pairs[wave][l & 63][1];
+                    real A1 = pairs[wave][l1 & 63][0], s1 = pairs[wave][l1 & 63][1];
+                    if (many) {
+                        const real* v = a.lval + 2 * (long long)(rr.r0 + l);
+                        if ((b & 1u) && l >= 64) { A = v[0]; s = v[1]; }
+                        const real* v1 = a.lval + 2 * (long long)(rr.r0 + l1);
+                        if ((b & 2u) && l1 >= 64) { A1 = v1[0]; s1 = v1[1]; }
+                    }
+                    const real gk = q.g[k], gb = q.g[k + 1];
+                    q.g[k + 1] = (b & 1u) ? A + s * gk : gb;
+                    q.g[k] = (b & 2u) ? A1 + s1 * gb : gk;
+                }
+            }
+            if (__any((q.fl & kVoid3) != 0u)) {
+                const bool v = (q.fl & kVoid3) != 0u;
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) q.g[i] = v ? real(0) : q.g[i];
+            }
+            const uint32_t hm = q.hfl & kCutMask3;
+            if (__any(hm != 0u)) {
+                // lane i (32 + i): population i returned by link k = opp(i)
+                const int i = halo_dir3(lane), k = i == 0 ? 0 : ((i & 1) ? i + 1 : i - 1);
+                const int rank = __builtin_popcount(hm & (k > 0 ? (1u << (k - 1)) - 1u : 0u));
+                const int from = lane < 32 ? 18 - __builtin_popcount(hm) + rank : 32 + rank;
+                const real A = __shfl(q.ha, from & 63), s = __shfl(q.hs, from & 63);
+                const real gk = __shfl(q.halo, (lane & 32) + k);
+                if (k > 0 && ((hm >> (k - 1)) & 1u)) q.halo = A + s * gk;
+            }
+        }
     };
     // plane p (in q) has arrived: the walls' returning populations, its density
     // into LDS with the halo columns', the populations into `park` (inner
     // waves), then plane `next` on its way into q
-    auto arrive = [&](Plane3<real>& q, int slot, int next, bool keep) -> real {
+    auto arrive = [&](Plane3<real, GEO>& q, int slot, int next, bool keep, const RowRec3& rr, const RowRec3& rn) __attribute__((always_inline)) -> real {
+        if constexpr (GEO) {
+            cut_pulls(q, rr);
+        }
         if (!PX && first) {
             const real s = x == 0 ? a.wskap[0] : real(0);   // other lanes keep their pulls
 #pragma unroll
@@ -1088,7 +1219,7 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
 #pragma unroll
             for (int i = 0; i < kQ; ++i) park[wave][i][lane] = q.g[i];
         }
-        issue(next, q);
+        issue(next, q, rn);
         __builtin_amdgcn_sched_barrier(0);
         dens[slot][wave][1 + col] = dr;
         if ((lane & 31) == 0) dens[slot][wave][lane ? 1 + wd : 0] = hs;
@@ -1096,22 +1227,34 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
         return dr;
     };
 
-    Plane3<real> q;
-    issue(z0 - 1, q);
+    Plane3<real, GEO> q;
+    // the records of the plane that arrives, of the one whose loads go out then
+    // and (rs) of the one that arrived before
+    RowRec3 rr = row_recs(z0 - 1), rn = row_recs(z0), rs = rr;
+    issue(z0 - 1, q, rr);
+    auto next_recs = [&](int m) __attribute__((always_inline)) {
+        rs = rr;
+        rr = rn;
+        rn = row_recs(z0 + min(m + 1, H));
+    };
     if (!out) {
         // a row of halo: densities only; as many barriers as the others
-        for (int m = 0; m <= H + 1; ++m) arrive(q, m & 1, z0 + min(m, H), false);
+        for (int m = 0; m <= H + 1; ++m) {
+            arrive(q, m & (RING - 1), z0 + min(m, H), false, rr, rn);
+            next_recs(m);
+        }
         return;
     }
+    uint32_t fl = 0u, flp = 0u;                             // flags of the stepped plane and of the arriving one
     bool bad = false;
-    auto plane_grad = [&](int slot, real dr) {
+    auto plane_grad = [&](int slot, real dr) __attribute__((always_inline)) {
         const real (*d)[68] = dens[slot];
         return plane_terms3(dr, d[wave][col + 2], d[wave][col], d[wave + 1][col + 1], d[wave - 1][col + 1],
                             d[wave + 1][col + 2], d[wave + 1][col], d[wave - 1][col + 2], d[wave - 1][col],
                             !PX && (first || last) ? wall_side : -1);
     };
     real (*own)[64] = park[wave];
-    auto carry = [&](const PlaneTerms3<real>& t, real sx1, real sy1, real t1) {
+    auto carry = [&](const PlaneTerms3<real>& t, real sx1, real sy1, real t1) __attribute__((always_inline)) {
         own[kQ][lane] = with_share3(t.gx, sx1);
         own[kQ + 1][lane] = with_share3(t.gy, sy1);
         own[kQ + 2][lane] = t1;
@@ -1120,40 +1263,68 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
         own[kQ + 5][lane] = t.tz;
     };
     for (int m = 0; m < 2; ++m) {
-        const PlaneTerms3<real> t = plane_grad(m, arrive(q, m, z0 + m, m == 1));
+        if constexpr (GEO) flp = q.fl;
+        const PlaneTerms3<real> t = plane_grad(m, arrive(q, m, z0 + m, m == 1, rr, rn));
+        next_recs(m);
         const bool below = m > 0;
         carry(t, below ? own[kQ + 3][lane] : real(0), below ? own[kQ + 4][lane] : real(0),
               below ? own[kQ + 5][lane] : real(0));
     }
     // plane z0 - 1 + m arrives, plane zc before it is stepped
-    auto advance = [&](int m) {
+    auto advance = [&](int m) __attribute__((always_inline)) {
         const int zc = z0 + m - 2;
         const unsigned s = (unsigned)(zc * ny + y) * (unsigned)nx + (unsigned)x;
         real cur[kQ];
 #pragma unroll
         for (int i = 0; i < kQ; ++i) cur[i] = park[wave][i][lane];
-        const PlaneTerms3<real> t = plane_grad(m & 1, arrive(q, m & 1, z0 + min(m, H), true));
-        const real dr1 = dens[(m & 1) ^ 1][wave][1 + col];  // the stepped plane's, left there one plane ago
+        if constexpr (GEO) {
+            fl = flp;
+            flp = q.fl;
+        }
+        // the stepped row's records, the first 64 now: they arrive while the row
+        // is stepped
+        const int sr0 = rs.r0, sr1 = rs.r1;
+        Link3<real> first64;
+        if constexpr (GEO)
+            if (sr1 > sr0) first64 = a.links[min(sr0 + lane, sr1 - 1)];
+        const int slot = m & (RING - 1);
+        const PlaneTerms3<real> t = plane_grad(slot, arrive(q, slot, z0 + min(m, H), true, rr, rn));
+        next_recs(m);
+        const int slot1 = (m - 1) & (RING - 1);
+        const real dr1 = dens[slot1][wave][1 + col];        // the stepped plane's, left there one plane ago
         real grad[3];
         grad[0] = with_share3(own[kQ][lane], t.sx);
         if (!PX && (first || last)) grad[0] += wall_grad3(wall_side, dr1);
         grad[1] = with_share3(own[kQ + 1][lane], t.sy);
         grad[2] = t.tz - own[kQ + 2][lane];
+        if constexpr (GEO) {
+            if (__any((fl & kCutMask3) != 0u)) {
+                const int slot2 = (m - 2) & (RING - 1);
+                real nb[kQ], gc[3];
+#pragma unroll
+                for (int i = 1; i < kQ; ++i)
+                    nb[i] = dens[kCZ[i] > 0 ? slot : (kCZ[i] < 0 ? slot2 : slot1)][wave + kCY[i]][1 + col + kCX[i]];
+                grad_nb3<true>(nb, dr1, fl, -1, gc);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) grad[k] = (fl & kCutMask3) ? gc[k] : grad[k];
+            }
+        }
         carry(t, own[kQ + 3][lane], own[kQ + 4][lane], own[kQ + 5][lane]);
         const real ir = recip3(real(1) + dr1);
         real o[kQ], j[3];
         collide_pairs3(cur, dr1, grad, a.ml * ir, a.F, a.omega, a.omega_h, j, o);
-        bad |= !(fabs(dr1) + fabs(j[0]) + fabs(j[1]) + fabs(j[2]) < real(kDivergeBound));
+        const bool live = !GEO || !(fl & kVoid3);           // void sites stay at rest
+        bad |= live && !(fabs(dr1) + fabs(j[0]) + fabs(j[1]) + fabs(j[2]) < real(kDivergeBound));
         PlaneWalk w(a.dst, a.stride);
 #pragma unroll
         for (int i = 0; i < kQ; ++i) {
-            w.store(s * (unsigned)sizeof(real), o[i]);
+            w.store(s * (unsigned)sizeof(real), live ? o[i] : real(0));
             w.next();
         }
         PlaneWalk wu(a.U, a.stride);
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            if (lane < wd) wu.add(s * 8u, (double)(j[k] * ir));
+            if (lane < wd && live) wu.add(s * 8u, (double)(j[k] * ir));
             wu.next();
         }
 #pragma unroll
@@ -1167,6 +1338,45 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
             for (int k = 0; k < 5; ++k) {
                 ww.store((unsigned)(zc * ny + y) * (unsigned)sizeof(real), A[k]);
                 ww.next();
+            }
+        }
+        if constexpr (GEO) {
+            // A of the row's cut links for the next step, one link a lane, from the
+            // post-collision populations of its site's lane
+            const unsigned base = (unsigned)(zc * ny + y) * (unsigned)nx + (unsigned)x0;
+            if (STAGE && sr1 > sr0) {
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) stage[wave][i][lane] = o[i];
+            }
+            for (int r = sr0; r < sr1; r += 64) {           // uniform
+                const int l = min(r + lane, sr1 - 1);
+                Link3<real> L = first64;
+                if (r > sr0) L = a.links[l];
+                const int from = (int)((unsigned)L.site - base);
+                const int k = (int)(L.meta & 31u), kb = (int)((L.meta >> 5) & 31u);
+                real h[kQ], hk = real(0), hb = real(0);
+#pragma unroll
+                for (int i = 0; i < kQ; ++i) {
+                    if constexpr (STAGE) {
+                        h[i] = stage[wave][i][from];
+                    } else {
+                        h[i] = __shfl(o[i], from);
+                        if (i == k) hk = h[i];
+                        if (i == kb) hb = h[i];
+                    }
+                }
+                if constexpr (STAGE) {
+                    hk = stage[wave][k][from];
+                    hb = stage[wave][kb][from];
+                }
+                real hd, hj[3], hP[6];
+                moments3(h, hd, hj, hP);
+                const real A = link_part3(L, hk, hb, hd, hd, hP, profile[(L.meta >> 19) & 15u]);
+                const bool ext = (L.meta >> 12) & 1u;       // k3_links_ext's
+                if (r + lane < sr1 && !ext) {
+                    a.lval_next[2 * (long long)l] = A;
+                    a.lval_next[2 * (long long)l + 1] = ((L.meta >> 10) & 3u) == kWallDirichlet ? L.kap : -L.kap;
+                }
             }
         }
     };
