@@ -267,20 +267,22 @@ void batch_launch(slbm_batch_s* b, int parity, int maxk)
         const dim3 blk(64 * (b->rows + 6));
         constexpr int lo = k2_waves<real>(1), hi = k2_waves<real>(kMaxTileRows2);
         const int gs = group_shift(b->group);
+        const TileOrder order =
+            tile_order(parity, grid, state_bytes<real>((long long)b->ntiles * b->rows * kStrip2));
         if (k2_waves<real>(b->rows) == hi) {
             if (b->coop)
                 hipLaunchKernelGGL((k_step2_batch<real, hi, true>), dim3(grid), blk, 0, b->stream, plates, cap, parity,
-                                   b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs);
+                                   b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs, order);
             else
                 hipLaunchKernelGGL((k_step2_batch<real, hi, false>), dim3(grid), blk, 0, b->stream, plates, cap,
-                                   parity, b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs);
+                                   parity, b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs, order);
         } else {
             if (b->coop)
                 hipLaunchKernelGGL((k_step2_batch<real, lo, true>), dim3(grid), blk, 0, b->stream, plates, cap, parity,
-                                   b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs);
+                                   b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs, order);
             else
                 hipLaunchKernelGGL((k_step2_batch<real, lo, false>), dim3(grid), blk, 0, b->stream, plates, cap,
-                                   parity, b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs);
+                                   parity, b->d_tile_plate, b->d_tile_start, b->ntiles, maxk, gs, order);
         }
     } else {
         const dim3 blk(64 * (b->wide ? tile_waves<true>(b->rows) : tile_waves<false>(b->rows)));

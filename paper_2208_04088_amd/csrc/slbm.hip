@@ -782,6 +782,30 @@ int tile_records(slbm_s* h, int seg)
     return h->precision == SLBM_FP32 ? build_tile_records<float>(h, seg) : build_tile_records<double>(h, seg);
 }
 
+template <typename real>
+long long state_bytes(long long sites) { return sites * (long long)(18 * sizeof(real) + 2 * sizeof(double)); }
+
+// How a launch of the two-step kernel goes through `bytes` of state (both
+// buffers and the displacement): each launch backwards through the one before,
+// whose last tiles' results are still in the 256 MB memory-side cache, and
+// with a state larger than that cache the first tiles' results, which would
+// only push out what is read before them, stored past it.  The share that
+// pays falls with the size: at one to two caches half of the tiles, above a
+// quarter; with the state in the cache such stores only lose it.  us per step,
+// 10-row tiles, square plates (forward with plain stores; backwards with
+// none, a quarter, half of the tiles streamed):
+//   fp32  1500 (198 MB) 24.7; 23.8 26.9 29.4   1650 (239 MB) 33.4; 29.4 31.5 34.0   1700 (254 MB) 39.9; 36.7 35.8 36.4
+//         1800 (285 MB) 48.1; 45.3 42.7 41.6   2048 (369 MB) 59.3; 57.7 56.6 53.8   2600 (594 MB) 92.4; 89.3 86.9 86.4
+//         3000 (792 MB) 123.5; 119.4 117.0 119.3   3500 (1.08 GB) 166.3; 165.4 163.3 166.8
+//   fp64  1200 (230 MB) 31.7; 31.4 34.2 36.3   1300 (270 MB) 46.1; 44.2 42.5 42.0   1501 (360 MB) 62.8; 60.8 59.6 57.1
+//         1800 (518 MB) 87.1; 83.6 83.0 83.4   2100 (705 MB) 113.3; 110.9 109.3 109.8
+// 24 mixed plates of a batch (fp32, 64 steps): 7817; 7651 7542 7554.
+TileOrder tile_order(int back, int grid, long long bytes)
+{
+    const long long cache = 250000000;
+    return {back, bytes <= cache ? 0 : (bytes <= 2 * cache ? grid / 2 : grid / 4)};
+}
+
 // Arguments of the two-steps-per-launch kernel: 58-column strips, at most
 // kMaxTileRows2 rows per tile.
 template <typename real>
@@ -799,31 +823,32 @@ StepArgs<real> make_args2(const slbm_s* h, int src, int seg)
 }
 
 template <typename real, bool PER, int W>
-void dispatch_step2_w(const slbm_s* h, const StepArgs<real>& a, int grid, dim3 blk)
+void dispatch_step2_w(const slbm_s* h, const StepArgs<real>& a, const TileOrder& order, int grid, dim3 blk)
 {
     if (a.rec_start)
-        hipLaunchKernelGGL((k_step2<real, PER, W, true>), dim3(grid), blk, 0, h->stream, a);
+        hipLaunchKernelGGL((k_step2<real, PER, W, true>), dim3(grid), blk, 0, h->stream, a, order);
     else
-        hipLaunchKernelGGL((k_step2<real, PER, W, false>), dim3(grid), blk, 0, h->stream, a);
+        hipLaunchKernelGGL((k_step2<real, PER, W, false>), dim3(grid), blk, 0, h->stream, a, order);
 }
 
 template <typename real>
 void dispatch_step2(const slbm_s* h, const StepArgs<real>& a)
 {
     const int grid = grid_for(a);
+    const TileOrder order = tile_order(h->cur, grid, state_bytes<real>(h->plane));
     const dim3 blk(64 * (a.seg + 6));
     constexpr int lo = k2_waves<real>(1), hi = k2_waves<real>(kMaxTileRows2);
     const bool per = h->px || h->py;
     if (k2_waves<real>(a.seg) == hi) {
         if (per)
-            dispatch_step2_w<real, true, hi>(h, a, grid, blk);
+            dispatch_step2_w<real, true, hi>(h, a, order, grid, blk);
         else
-            dispatch_step2_w<real, false, hi>(h, a, grid, blk);
+            dispatch_step2_w<real, false, hi>(h, a, order, grid, blk);
     } else {
         if (per)
-            dispatch_step2_w<real, true, lo>(h, a, grid, blk);
+            dispatch_step2_w<real, true, lo>(h, a, order, grid, blk);
         else
-            dispatch_step2_w<real, false, lo>(h, a, grid, blk);
+            dispatch_step2_w<real, false, lo>(h, a, order, grid, blk);
     }
 }
 

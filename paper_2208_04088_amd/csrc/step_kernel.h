@@ -180,6 +180,11 @@ __device__ __forceinline__ void stu(T* base, unsigned e, T v)     // base unifor
     *(gptr<T>)((gptr<char>)sbase(base) + e * (unsigned)sizeof(T)) = v;
 }
 template <typename T>
+__device__ __forceinline__ void stu_nt(T* base, unsigned e, T v)  // stu, past the caches
+{
+    __builtin_nontemporal_store(v, (gptr<T>)((gptr<char>)sbase(base) + e * (unsigned)sizeof(T)));
+}
+template <typename T>
 __device__ __forceinline__ T ldg(const T* base, unsigned e)       // any base
 {
     return *(const T*)((const char*)base + e * (unsigned)sizeof(T));
@@ -557,6 +562,24 @@ __device__ __forceinline__ int xcd_map(int b, int nb, int shift)
     return shift < 0 ? band : grouped;
 }
 
+// A launch's order through its tiles (see turn) and the leading workgroups
+// whose results pass the caches by.
+struct TileOrder {
+    int back;                  // 1: from the last tile to the first
+    int streamed;
+};
+
+// Workgroup b's place in the launch's order: b itself, or with `back` the
+// workgroups of each XCD from its last to its first (nb is a multiple of 8).
+// Consecutive launches alternate, so that a launch begins where the one before
+// ended, on the part of the state that is still in the 256 MB memory-side
+// cache; tile_order has what that gains.
+__device__ __forceinline__ int turn(int b, int nb, int back)
+{
+    const int x = b & 7, l = b >> 3;
+    return ((back ? (nb >> 3) - 1 - l : l) << 3) + x;
+}
+
 // Densities of the two halo columns of a wide strip in row y (left: column
 // xs - 1, right: xs + 64).  Lanes 0-8 pull the nine populations of the left
 // site, lanes 32-40 those of the right one (one load each), and the sums are
@@ -750,7 +773,7 @@ __device__ __forceinline__ double pick9(const double h[9], int k)
 // reads (second step).  Both compute every rule value from the same inputs
 // with rule_value, so the state is the same to the bit.
 template <typename real, bool PER, bool TWO, bool COOP>
-__device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, TileLds<real, COOP>& lds)
+__device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bool streamed, TileLds<real, COOP>& lds)
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tid = threadIdx.x, nthr = blockDim.x;
@@ -952,11 +975,18 @@ __device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, Ti
                                                lds.dens[wave + 1][lane + 1], o, jx, jy, ir)
                     : collide_core<real, false>(a, g, fl, w, lds.dens[wave + 1][lane], lds.dens[wave + 1][lane - 1],
                                                 lds.dens[wave + 1][lane + 1], o, jx, jy, ir);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) stu(a.dst + i * a.plane, s, o[i]);
         advance_u(ux, uy, jx, jy, ir);
-        stu(a.U, s, ux);
-        stu(a.U + a.plane, s, uy);
+        if (streamed) {                                 // uniform over the workgroup
+#pragma unroll
+            for (int i = 0; i < 9; ++i) stu_nt(a.dst + i * a.plane, s, o[i]);
+            stu_nt(a.U, s, ux);
+            stu_nt(a.U + a.plane, s, uy);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) stu(a.dst + i * a.plane, s, o[i]);
+            stu(a.U, s, ux);
+            stu(a.U + a.plane, s, uy);
+        }
     }
     return bad;
 }
@@ -972,12 +1002,12 @@ constexpr int k2_waves(int rows) { return sizeof(real) == 4 ? (rows > 8 ? 8 : 7)
 // (W = k2_waves(seg)); COOP: the boundary rules tile by tile from the
 // plate's tile record lists.
 template <typename real, bool PER, int W, bool COOP>
-__global__ __launch_bounds__(1024, W) void k_step2(StepArgs<real> a)
+__global__ __launch_bounds__(1024, W) void k_step2(StepArgs<real> a, TileOrder order)
 {
     __shared__ TileLds<real, COOP> lds;
-    const int tile = xcd_map(blockIdx.x, gridDim.x, a.group_shift);
+    const int tile = xcd_map(turn(blockIdx.x, gridDim.x, order.back), gridDim.x, a.group_shift);
     if (tile >= a.ntiles) return;                 // uniform over the workgroup
-    flag_divergence(a.diverged, step_tile2<real, PER, true, COOP>(a, tile, lds));
+    flag_divergence(a.diverged, step_tile2<real, PER, true, COOP>(a, tile, (int)blockIdx.x < order.streamed, lds));
 }
 
 // Per-plate state of the batched step, in device memory so that a captured
@@ -1046,10 +1076,10 @@ template <typename real, int W, bool COOP>
 __global__ __launch_bounds__(1024, W) void k_step2_batch(BatchPlate<real>* __restrict__ plates, int cap, int parity,
                                                       const int* __restrict__ tile_plate,
                                                       const int* __restrict__ tile_start, int ntiles, int maxk,
-                                                      int group_shift)
+                                                      int group_shift, TileOrder order)
 {
     __shared__ TileLds<real, COOP> lds;
-    const int t = xcd_map(blockIdx.x, gridDim.x, group_shift);
+    const int t = xcd_map(turn(blockIdx.x, gridDim.x, order.back), gridDim.x, group_shift);
     if (t >= ntiles) return;                      // uniform over the workgroup
     const int p = tile_plate[t];
     const BatchPlate<real> B = plates[parity * cap + p];
@@ -1057,10 +1087,11 @@ __global__ __launch_bounds__(1024, W) void k_step2_batch(BatchPlate<real>* __res
     // the plate's first tile hands the next launch its state
     if (lt == 0 && threadIdx.x == 0) plates[(parity ^ 1) * cap + p] = batch_next(B, maxk);
     if (!B.active || B.halted) return;
+    const bool streamed = (int)blockIdx.x < order.streamed;
     if (maxk >= 2 && B.remaining >= 2)
-        flag_divergence(B.args.diverged, step_tile2<real, false, true, COOP>(B.args, lt, lds));
+        flag_divergence(B.args.diverged, step_tile2<real, false, true, COOP>(B.args, lt, streamed, lds));
     else
-        flag_divergence(B.args.diverged, step_tile2<real, false, false, COOP>(B.args, lt, lds));
+        flag_divergence(B.args.diverged, step_tile2<real, false, false, COOP>(B.args, lt, streamed, lds));
 }
 
 }  // namespace slbm_dev
