@@ -74,6 +74,14 @@ Step3Args<real> make_args3(const slbm3_s* h, int src)
     a.px = h->px;
     a.local = h->local ? 1 : 0;
     a.ntiles = ((h->nx + 63) / 64) * h->ny * h->nz;
+    // backwards where the second pass would find little of the first one's
+    // state in the caches: not small boxes with cut links, which it lets end on
+    // the rows with the longest work.  us per step, forward and backward:
+    //   fp32 slab   64^3 18.3 18.1   80^3 36.4 34.7   (96^3 and more: k3_march)   fp64 slab  60^3 30.0 29.5
+    //   fp32 porous 100^3 (176 MB) 54.7 53.2   128^3 102.9 102.6   150^3 238 225   180^3 360 351
+    //   fp64 porous  90^3 (240 MB) 73.8 73.2   120^3 206 195
+    //   fp64 solid with a cavity and a crack  45x38x41 16.5 16.8   60^3 (72 MB) 26.7 28.4
+    a.back = !h->geo || h->plane * (long long)((2 * kQ + 1) * sizeof(real) + 24) > 125000000 ? 1 : 0;
     // time profiles at the step of the state the pulls read (the previous
     // step's post-collision state) and of the state this step produces
     const double n_pull = h->step >= 1 ? (double)(h->step - 1) : 0.0, n_next = (double)h->step;

@@ -99,6 +99,7 @@ struct Step3Args {
     int px;                    // periodic in x (else walls)
     int local;                 // src holds the populations at the sites themselves
     int ntiles;                // 64-site row chunks
+    int back;                  // k3_step, k3_readout: from the box's end to its beginning
     int wkind[2];              // walls crossing the first and the last site's x links
     real wval[2][3];           // lattice units: wall velocity (Dirichlet) or traction (Neumann)
     // per wall, from its q: kappa = (1 - 2q)/(1 + 2q), beta = 2/(1 + 2q)
@@ -781,11 +782,14 @@ __device__ __forceinline__ float recip3(float x) { return __builtin_amdgcn_rcpf(
 __device__ __forceinline__ double recip3(double x) { return 1.0 / x; }
 
 // One time step at every site: pull (with the wall rules), moments, source
-// term, eq:coll, U += j/rho, store.
+// term, eq:coll, U += j/rho, store.  With `back` it goes through the box
+// backwards, as does k3_readout: the density pass before it ends on the sites
+// that it begins with, and it ends on those the next density pass reads first,
+// while they are still in the caches (make_args3 has the rule).
 template <typename real, bool PX, bool GEO = false>
 __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
 {
-    const int wg = xcd_group3<GEO>(blockIdx.x);
+    const int wg = xcd_group3<GEO>(turn(blockIdx.x, gridDim.x, a.back));
     int tile = wg * 4 + (threadIdx.x >> 6);
     if (wg * 4 >= a.ntiles) return;                     // uniform over the workgroup
     const bool tvalid = tile < a.ntiles;
@@ -1408,7 +1412,7 @@ struct Readout3Dst {
 template <typename real, bool PX, bool GEO, typename T>
 __global__ __launch_bounds__(256) void k3_readout(Step3Args<real> a, Readout3Dst<T> d)
 {
-    const int tile = xcd_group3<GEO>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int tile = xcd_group3<GEO>(turn(blockIdx.x, gridDim.x, a.back)) * 4 + (threadIdx.x >> 6);
     if (tile >= a.ntiles) return;
     const Site3 st = site_of(tile, threadIdx.x & 63, a.nx, a.ny);
     real g[kQ];
