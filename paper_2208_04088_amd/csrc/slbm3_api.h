@@ -625,7 +625,7 @@ void free3(slbm3_s* h)
 {
     for (void* p : {h->buf[0], h->buf[1], (void*)h->U, h->dens, (void*)h->diverged, (void*)h->scratch,
                     (void*)h->flags, (void*)h->bidx, h->links, h->lval[0],
-                    (void*)h->rowrec, (void*)h->wrec, (void*)h->elink, h->wall[0]})
+                    (void*)h->rowrec, (void*)h->wrec, (void*)h->elink})
         if (p) (void)hipFree(p);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
@@ -725,11 +725,13 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
         TRY_OR_BAIL(hipMalloc(&h->buf[0], pop));
         TRY_OR_BAIL(hipMalloc(&h->buf[1], pop));
         TRY_OR_BAIL(hipMalloc((void**)&h->U, (size_t)3 * h->stride * sizeof(double)));
-        TRY_OR_BAIL(hipMalloc(&h->dens, (size_t)plane * h->esize));
+        // the densities, then (walls) the two sets of returned parts, in one block
+        const size_t dens = ((size_t)plane * h->esize + 255) / 256 * 256;
+        const size_t one = h->px ? 0 : ((size_t)10 * h->ny * h->nz * h->esize + 255) / 256 * 256;
+        TRY_OR_BAIL(hipMalloc(&h->dens, dens + 2 * one));
         TRY_OR_BAIL(hipMalloc((void**)&h->diverged, sizeof(unsigned int)));
         if (!h->px) {
-            const size_t one = ((size_t)10 * h->ny * h->nz * h->esize + 255) / 256 * 256;
-            TRY_OR_BAIL(hipMalloc(&h->wall[0], 2 * one));
+            h->wall[0] = (char*)h->dens + dens;
             h->wall[1] = (char*)h->wall[0] + one;
         }
         // rest state: g = 0 (f = r), U = 0
