@@ -200,7 +200,8 @@ int slbm_time(slbm_handle h, int64_t* step, double* t_user);
  * tile, 58 output columns; an odd step count ends with one single step).
  * seg_rows is at most 14 (10 with strip 58); 0 keeps the library's choice.
  * seg_rows 0 with strip 0, the state after slbm_create, leaves the whole
- * launch to the library: two steps per launch, rows by the plate's size.
+ * launch to the library: two steps per launch, rows by the plate's size, and up
+ * to four per launch on a small plate (at most 256 tiles of 50 columns, 2 rows).
  * For two steps per launch the library also lists, per tile, the plate's cut links in
  * the tile's reach (slbm_boundary_lists), so that the tile evaluates the
  * section 4 rules of all of them together; it allocates device memory for
@@ -256,7 +257,9 @@ int slbm_get_launch(slbm_handle h, int32_t* seg_rows, int32_t* strip, int32_t* x
  * that shape with interleaved XCD groups of 8 and keeps them if they are at
  * least 1 % faster (else bands).  Reports the shape and its time per step in
  * microseconds (any pointer may be NULL); slbm_get_launch gives the XCD
- * group.  Synchronises.  The state and step count are unchanged. */
+ * group.  On a small plate (slbm_set_launch) it also times up to four steps per
+ * launch, which slbm_step then takes if they are faster than that shape; the
+ * time reported is theirs.  Synchronises.  The state and step count are unchanged. */
 int slbm_autotune(slbm_handle h, int32_t* seg_rows, int32_t* strip, double* us_per_step);
 
 /* Checkpoint of the full state of the time stepping of section 3 (the

@@ -471,6 +471,12 @@ struct slbm_s {
     int rec_seg = 0;
     bool rec_fit = false;
     int64_t rec_bytes = 0;
+    // the same for k_step4's tiles (build_four): whether the plate is one for
+    // it and a call of steps takes it, its lists (null: no cut links)
+    bool four_fit = false, four = false;
+    void* recs4 = nullptr;
+    int32_t* rec4_start = nullptr;
+    int64_t rec4_bytes = 0;
     int64_t rec_count = 0;
     int32_t rec_max = 0;
 };
@@ -658,10 +664,10 @@ void axis_images(int c, int n, bool per, int lo, int hi, F&& f)
 
 long long floor_div(long long a, long long b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 
-// Where the cut links sit in the tiles of the two-step kernel (R rows,
-// 58-column strips): a tile's reach is rows y0 - 3 .. y0 + R + 2 and columns
-// xs - 3 .. xs + 60, wave w and lane l at y0 - 3 + w, xs - 3 + l, wrapping on
-// periodic axes.  Every link (site y nx + x) appears in each tile whose reach
+// Where the cut links sit in the tiles of the kernels of several steps (R rows,
+// strips of W = 64 - 2 H columns, H = 3 with two steps): a tile's reach is rows
+// y0 - H .. y0 + R + H - 1 and columns xs - H .. xs + W + H - 1, wave w and lane
+// l at y0 - H + w, xs - H + l, wrapping on periodic axes.  Every link (site y nx + x) appears in each tile whose reach
 // holds its site, once per image of the site there.  start[t] .. start[t + 1]
 // index tile t's records, each a link and a position (w << 8 | l); `most` is
 // the largest count in one tile.  Host only.
@@ -671,24 +677,24 @@ struct TileLayout {
     long long ntiles = 0;
 };
 
-TileLayout tile_layout(int nx, int ny, bool px, bool py, int R, const int32_t* site, int n, int64_t cap)
+TileLayout tile_layout(int nx, int ny, bool px, bool py, int R, int H, const int32_t* site, int n, int64_t cap)
 {
     TileLayout out;
-    const int nstrips = (nx + kStrip2 - 1) / kStrip2, ntr = (ny + R - 1) / R;
+    const int W = 64 - 2 * H, nstrips = (nx + W - 1) / W, ntr = (ny + R - 1) / R;
     out.ntiles = (long long)nstrips * ntr;
     auto each = [&](auto&& f) {
         for (int i = 0; i < n; ++i) {
             const int x = site[i] % nx, y = site[i] / nx;
-            axis_images(y, ny, py, -3, ntr * R + 2, [&](int yh) {
-                const long long tr0 = std::max<long long>(0, -floor_div(-(yh - R - 2), R));
-                const long long tr1 = std::min<long long>(ntr - 1, floor_div(yh + 3, R));
+            axis_images(y, ny, py, -H, ntr * R + H - 1, [&](int yh) {
+                const long long tr0 = std::max<long long>(0, -floor_div(-(yh - R - H + 1), R));
+                const long long tr1 = std::min<long long>(ntr - 1, floor_div(yh + H, R));
                 for (long long tr = tr0; tr <= tr1; ++tr) {
-                    const int w = yh - (int)(tr * R - 3);
-                    axis_images(x, nx, px, -3, nstrips * kStrip2 + 2, [&](int xh) {
-                        const long long s0 = std::max<long long>(0, -floor_div(-(xh - 60), kStrip2));
-                        const long long s1 = std::min<long long>(nstrips - 1, floor_div(xh + 3, kStrip2));
+                    const int w = yh - (int)(tr * R - H);
+                    axis_images(x, nx, px, -H, nstrips * W + H - 1, [&](int xh) {
+                        const long long s0 = std::max<long long>(0, -floor_div(-(xh - W - H + 1), W));
+                        const long long s1 = std::min<long long>(nstrips - 1, floor_div(xh + H, W));
                         for (long long st = s0; st <= s1; ++st)
-                            f(st + tr * nstrips, w, xh - (int)(st * kStrip2 - 3), i);
+                            f(st + tr * nstrips, w, xh - (int)(st * W - H), i);
                     });
                 }
             });
@@ -717,8 +723,34 @@ TileLayout tile_layout(int nx, int ny, bool px, bool py, int R, const int32_t* s
     return out;
 }
 
+// The block a layout's lists take on the device: the records, each with its
+// link's coefficients (TileRec), then the tiles' first records.
+template <typename real>
+std::vector<char> tile_block(const slbm_s* h, const TileLayout& lay)
+{
+    const size_t total = lay.link.size(), rb = total * sizeof(TileRec<real>), sb = lay.start.size() * sizeof(int32_t);
+    const LinkDev<real>* L = reinterpret_cast<const LinkDev<real>*>(h->link_host.data());
+    std::vector<char> block(rb + sb);
+    TileRec<real>* rec = reinterpret_cast<TileRec<real>*>(block.data());
+    for (size_t k = 0; k < total; ++k) {
+        TileRec<real>& r = rec[k];
+        const LinkDev<real>& d = L[lay.link[k]];
+        r.kappa = d.kappa; r.wx = d.wx; r.wy = d.wy; r.D = d.D;
+        for (int j = 0; j < 4; ++j) r.be[j] = d.be[j];
+        for (int j = 0; j < 3; ++j) {
+            r.K1[j] = d.K1[j];
+            r.K2[j] = d.K2[j];
+            r.E3[j] = d.E3[j];
+        }
+        r.meta = d.k | (d.kind << 4) | (d.behind << 6) | ((d.g1 + 1) << 8) | ((d.g2 + 1) << 16);
+        r.pos = lay.pos[k];
+    }
+    std::memcpy(block.data() + rb, lay.start.data(), sb);
+    return block;
+}
+
 // The plate's tile lists on the device for tiles of seg rows: tile_layout's
-// records, each with its link's coefficients (TileRec).  When a tile has more
+// records (tile_block).  When a tile has more
 // than the cooperative kernel takes (or the plate more groups than it
 // tabulates), no lists are kept and the two-step kernel takes the rules site
 // by site.
@@ -733,29 +765,12 @@ int build_tile_records(slbm_s* h, int seg)
     const int R = seg;
     // one record per thread of the tile's workgroup, and what its LDS holds
     const int cap = std::min(kTileRecCap, 64 * (R + 6));
-    const TileLayout lay = tile_layout(h->nx, h->ny, h->px != 0, h->py != 0, R, h->link_site.data(), h->n_links, cap);
+    const TileLayout lay =
+        tile_layout(h->nx, h->ny, h->px != 0, h->py != 0, R, 3, h->link_site.data(), h->n_links, cap);
     if (lay.most > cap) return SLBM_OK;
-    const std::vector<int32_t>& start = lay.start;
-    const int32_t most = lay.most;
+    const std::vector<char> block = tile_block<real>(h, lay);
     const size_t total = lay.link.size();
-    const LinkDev<real>* L = reinterpret_cast<const LinkDev<real>*>(h->link_host.data());
-    std::vector<TileRec<real>> rec(total);
-    for (size_t k = 0; k < total; ++k) {
-        TileRec<real>& r = rec[k];
-        const LinkDev<real>& d = L[lay.link[k]];
-        r.kappa = d.kappa; r.wx = d.wx; r.wy = d.wy; r.D = d.D;
-        for (int j = 0; j < 4; ++j) r.be[j] = d.be[j];
-        for (int j = 0; j < 3; ++j) {
-            r.K1[j] = d.K1[j];
-            r.K2[j] = d.K2[j];
-            r.E3[j] = d.E3[j];
-        }
-        r.meta = d.k | (d.kind << 4) | (d.behind << 6) | ((d.g1 + 1) << 8) | ((d.g2 + 1) << 16);
-        r.pos = lay.pos[k];
-    }
-    // one block: the records, then the tiles' first records
-    const size_t rb = total * sizeof(TileRec<real>), sb = start.size() * sizeof(int32_t);
-    const hipError_t e = dev_alloc(h, &h->recs, rb + sb);
+    const hipError_t e = dev_alloc(h, &h->recs, block.size());
     if (e != hipSuccess) {
         drop_tile_records(h);
         h->rec_seg = seg;
@@ -764,16 +779,48 @@ int build_tile_records(slbm_s* h, int seg)
         if (e == hipErrorOutOfMemory) return fail(SLBM_E_NOMEM, "no device memory for the tile record lists");
         HIP_TRY(e);
     }
-    h->rec_start = (int32_t*)((char*)h->recs + rb);
-    std::vector<char> stage(rb + sb);
-    if (rb) std::memcpy(stage.data(), rec.data(), rb);
-    std::memcpy(stage.data() + rb, start.data(), sb);
-    HIP_TRY(hipMemcpyAsync(h->recs, stage.data(), rb + sb, hipMemcpyHostToDevice, h->stream));
+    h->rec_start = (int32_t*)((char*)h->recs + total * sizeof(TileRec<real>));
+    HIP_TRY(hipMemcpyAsync(h->recs, block.data(), block.size(), hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->rec_fit = true;
-    h->rec_bytes = (int64_t)(start.size() * sizeof(int32_t) + total * sizeof(TileRec<real>));
+    h->rec_bytes = (int64_t)block.size();
     h->rec_count = (int64_t)total;
-    h->rec_max = most;
+    h->rec_max = lay.most;
+    return SLBM_OK;
+}
+
+long long tiles4(const slbm_s* h)
+{
+    return (long long)((h->nx + kStrip4 - 1) / kStrip4) * ((h->ny + kRows4 - 1) / kRows4);
+}
+
+// Whether k_step4 takes the plate's steps, and its lists.  Only while its tiles
+// leave each a compute unit (256): a second round of workgroups costs a second
+// launch's time.  us per step, square plates, four steps and two (best rows):
+//   fp32  32^2 3.06 3.53   80^2 2.96 3.44   128^2 (192 tiles) 2.97 3.54   160^2 (320) 5.27 3.48   256^2 7.33 3.86
+//   fp64  32^2 3.63 4.12   80^2 3.55 3.92   128^2 3.60 4.05               160^2 6.53 4.03         256^2 9.42 4.70
+// A plate with more cut links in a tile than the cooperative kernel takes
+// keeps to two steps.
+template <typename real>
+int build_four(slbm_s* h)
+{
+    if (tiles4(h) > 256 || h->ngroups > kTileGroupCap) return SLBM_OK;
+    if (h->n_links > 0) {
+        const TileLayout lay = tile_layout(h->nx, h->ny, h->px != 0, h->py != 0, kRows4, kHalo4, h->link_site.data(),
+                                           h->n_links, kTileRecCap);
+        if (lay.most > kTileRecCap) return SLBM_OK;
+        const std::vector<char> block = tile_block<real>(h, lay);
+        if (dev_alloc(h, &h->recs4, block.size()) != hipSuccess) {
+            (void)hipGetLastError();
+            h->recs4 = nullptr;
+            return SLBM_OK;                                // no room: two steps per launch
+        }
+        h->rec4_start = (int32_t*)((char*)h->recs4 + lay.link.size() * sizeof(TileRec<real>));
+        h->rec4_bytes = (int64_t)block.size();
+        HIP_TRY(hipMemcpyAsync(h->recs4, block.data(), block.size(), hipMemcpyHostToDevice, h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
+    }
+    h->four_fit = h->four = true;
     return SLBM_OK;
 }
 
@@ -850,6 +897,34 @@ void dispatch_step2(const slbm_s* h, const StepArgs<real>& a)
         else
             dispatch_step2_w<real, false, lo>(h, a, order, grid, blk);
     }
+}
+
+// Up to four steps in one launch; commit = false: an autotuner trial.
+template <typename real>
+int launch_step4(slbm_s* h, int steps, bool commit)
+{
+    StepArgs<real> a = make_args<real>(h, h->cur);
+    if (!commit) a.local = 0;
+    a.seg = kRows4;
+    a.nstrips = (h->nx + kStrip4 - 1) / kStrip4;
+    a.ntiles = (int)tiles4(h);
+    a.rec_start = h->rec4_start;
+    a.recs = (const TileRec<real>*)h->recs4;
+    const dim3 grid(grid_for(a)), blk(64 * (kRows4 + 2 * kHalo4));
+    const bool per = h->px || h->py;
+    if (h->recs4) {
+        if (per) hipLaunchKernelGGL((k_step4<real, true, true>), grid, blk, 0, h->stream, a, steps);
+        else hipLaunchKernelGGL((k_step4<real, false, true>), grid, blk, 0, h->stream, a, steps);
+    } else {
+        if (per) hipLaunchKernelGGL((k_step4<real, true, false>), grid, blk, 0, h->stream, a, steps);
+        else hipLaunchKernelGGL((k_step4<real, false, false>), grid, blk, 0, h->stream, a, steps);
+    }
+    HIP_TRY(hipGetLastError());
+    if (!commit) return SLBM_OK;
+    h->cur ^= 1;
+    h->local = false;
+    h->step += steps;
+    return SLBM_OK;
 }
 
 // Two steps in one launch, not committed (autotuner trials; see launch_step_raw).
@@ -972,7 +1047,7 @@ hipError_t dev_alloc(slbm_s* h, void** p, size_t n)
 // The plate's own device blocks (not the batch's divergence word or scratch).
 std::vector<void*> plate_blocks(slbm_s* h)
 {
-    std::vector<void*> v = {h->buf[0], h->buf[1], h->U, h->flags, h->bidx, h->links, h->groups, h->recs};
+    std::vector<void*> v = {h->buf[0], h->buf[1], h->U, h->flags, h->bidx, h->links, h->groups, h->recs, h->recs4};
     if (!h->ext_flag) v.push_back(h->diverged);
     if (!h->batch) v.push_back(h->scratch);
     return v;
@@ -991,6 +1066,7 @@ void free_all(slbm_s* h)
     h->buf[0] = h->buf[1] = nullptr;
     h->rec_start = nullptr;
     h->recs = nullptr;
+    h->recs4 = nullptr;
     h->rec_fit = false;
     h->U = nullptr;
     h->scratch = nullptr;
@@ -1288,6 +1364,7 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
     // lists for the library's own launch (a batch has its own; a plate without
     // room for them takes the rules site by site)
     if (!arena && tile_records(h, default_rows2(h)) != SLBM_OK) drop_tile_records(h);
+    if (!arena) (void)(h->precision == SLBM_FP32 ? build_four<float>(h) : build_four<double>(h));
     *out = h;
     return SLBM_OK;
 }
@@ -1332,7 +1409,14 @@ int slbm_step(slbm_handle h, int64_t nsteps)
         if (nsteps < 0) return fail(SLBM_E_INVAL, "negative step count");
         DeviceGuard dg(h->device);
         int64_t i = 0;
-        if (launch_rows2(h)) {
+        if (h->four) {
+            while (i < nsteps) {
+                const int k = (int)std::min<int64_t>(kSteps4, nsteps - i);
+                const int rc = h->precision == SLBM_FP32 ? launch_step4<float>(h, k, true) : launch_step4<double>(h, k, true);
+                if (rc) return rc;
+                i += k;
+            }
+        } else if (launch_rows2(h)) {
             for (; i + 2 <= nsteps; i += 2) {
                 int rc = h->precision == SLBM_FP32 ? launch_step2<float>(h) : launch_step2<double>(h);
                 if (rc) return rc;
@@ -1524,6 +1608,7 @@ int slbm_set_launch(slbm_handle h, int32_t seg_rows, int32_t strip)
         }
         h->seg = seg_rows;
         h->two = strip == kStrip2 ? 1 : 0;
+        h->four = h->four_fit && strip == 0 && seg_rows == 0;
         h->wide = (strip == 0 || strip == kStrip2) ? -1 : (strip == 64 ? 1 : 0);
         return SLBM_OK;
     });
@@ -1552,7 +1637,7 @@ int slbm_tile_list_layout(int32_t nx, int32_t ny, int32_t periodic_x, int32_t pe
         for (int i = 0; i < n_links; ++i)
             if (link_sites[i] < 0 || (long long)link_sites[i] >= (long long)nx * ny)
                 return fail(SLBM_E_INVAL, "link %d: site out of the grid", i);
-        const TileLayout lay = tile_layout(nx, ny, periodic_x != 0, periodic_y != 0, rows, link_sites, n_links,
+        const TileLayout lay = tile_layout(nx, ny, periodic_x != 0, periodic_y != 0, rows, 3, link_sites, n_links,
                                            INT64_MAX);
         if (lay.start.empty()) return fail(SLBM_E_UNSUPPORTED, "more than 2^31 - 1 tile records");
         const int64_t total = lay.start[(size_t)lay.ntiles];
@@ -1609,11 +1694,11 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
         HIP_TRY(hipEventCreate(&e0));
         HIP_TRY(hipEventCreate(&e1));
         // time per step of a shape (wv: 0 narrow, 1 wide, 2 two steps per
-        // launch) with the current XCD map: the best of two bursts of
+        // launch, 4 four) with the current XCD map: the best of two bursts of
         // back-to-back launches after a warm one, as steps run; each launch
         // rereads the same state, and U is put back after every burst
         auto time_shape = [&](int c, int wv, double& us) -> int {
-            const int burst = wv == 2 ? 3 : 6;
+            const int burst = wv >= 2 ? 3 : 6, per = wv == 4 ? kSteps4 : (wv == 2 ? 2 : 1);
             if (wv == 2) {
                 const int rc2 = tile_records(h, c);
                 if (rc2) return rc2;
@@ -1622,7 +1707,10 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
             for (int r = 0; r < 3; ++r) {
                 HIP_TRY(hipEventRecord(e0, h->stream));
                 for (int q = 0; q < burst; ++q) {
-                    const int rc2 = wv == 2
+                    const int rc2 = wv == 4
+                        ? (h->precision == SLBM_FP32 ? launch_step4<float>(h, kSteps4, false)
+                                                     : launch_step4<double>(h, kSteps4, false))
+                        : wv == 2
                         ? (h->precision == SLBM_FP32 ? launch_step2_raw<float>(h, c) : launch_step2_raw<double>(h, c))
                         : (h->precision == SLBM_FP32 ? launch_step_raw<float>(h, c, wv) : launch_step_raw<double>(h, c, wv));
                     if (rc2) return rc2;
@@ -1632,7 +1720,7 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
                 HIP_TRY(hipEventSynchronize(e1));
                 float ms = 0;
                 HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-                if (r > 0) t.push_back(ms / (wv == 2 ? 2 * burst : burst));
+                if (r > 0) t.push_back(ms / (per * burst));
             }
             us = 1e3 * *std::min_element(t.begin(), t.end());
             return SLBM_OK;
@@ -1664,6 +1752,13 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
             best_us = us;
         else
             h->group = 0;
+        // four steps per launch, where the plate is one for it
+        h->four = false;
+        if (h->four_fit) {
+            if ((rc = time_shape(kRows4, 4, us))) { h->group = keep_group; return rc; }
+            h->four = us < best_us;
+            best_us = std::min(us, best_us);
+        }
         HIP_TRY(hipMemcpyAsync(h->diverged, flag_saved, sizeof(unsigned int), hipMemcpyDeviceToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         (void)hipEventDestroy(e0);
@@ -1686,7 +1781,7 @@ int slbm_device_bytes(slbm_handle h, int64_t* bytes)
         if (!h || !bytes) return fail(SLBM_E_INVAL, "null argument");
         int64_t b = 2 * (int64_t)9 * h->plane * (int64_t)h->esize + 2 * h->plane * 8 + h->plane * 5;
         b += (int64_t)h->n_links * (h->esize == 4 ? (int64_t)sizeof(LinkDev<float>) : (int64_t)sizeof(LinkDev<double>));
-        b += h->rec_bytes;
+        b += h->rec_bytes + h->rec4_bytes;
         if (h->scratch) b += (int64_t)h->scratch_planes * h->plane * 8;
         *bytes = b;
         return SLBM_OK;

@@ -723,20 +723,20 @@ constexpr int kTileGroupCap = 64;
 // carry the first step's rule values, plane k - 1 of row w those of the cut
 // links k of wave w (rows 0..R+5); they are read before the first step's
 // collision writes post.
-template <typename real, bool COOP>
+template <typename real, bool COOP, int STEPS = 2>
 struct TileLds {
     real post_[kMaxTileRows2 + 4][9][64];
     real dens[kMaxTileRows2 + 6][66];
     __device__ real (*post())[9][64] { return post_; }
 };
-template <typename real>
-struct TileLds<real, true> {
+template <typename real, int STEPS>
+struct TileLds<real, true, STEPS> {
     static constexpr int kWords = (kMaxTileRows2 + 6) * 8 * 64 > (kMaxTileRows2 + 4) * 9 * 64
                                       ? (kMaxTileRows2 + 6) * 8 * 64 : (kMaxTileRows2 + 4) * 9 * 64;
     real buf[kWords];
     real dens[kMaxTileRows2 + 6][66];
     TileRec<real> recs[kTileRecCap];
-    real prof[2][kTileGroupCap];
+    real prof[STEPS][kTileGroupCap];
     __device__ real (*post())[9][64] { return reinterpret_cast<real (*)[9][64]>(buf); }
     __device__ real (*rule1())[8][64] { return reinterpret_cast<real (*)[8][64]>(buf); }
 };
@@ -758,8 +758,10 @@ __device__ __forceinline__ double pick9(const double h[9], int k)
     return __longlong_as_double((long long)v);
 }
 
-// TWO = false: only the first step, stored like a single step (a plate in a
-// batch with one step left).
+// A tile's `steps` steps, at most MOST: the tile widened by H = 2 MOST - 1
+// sites on each side, of which each step uses up two (the first one, by its
+// density stencil alone, one).  One step is stored like a single step (a plate
+// in a batch with one step left).
 //
 // The rules of section 4 at the tile's cut links, two ways.  COOP = false:
 // site by site, each site with cut links pulling, from global memory (first
@@ -770,18 +772,21 @@ __device__ __forceinline__ double pick9(const double h[9], int k)
 // loads, one thread per record gathers the state its rule reads (one round of
 // loads for all records), evaluates it and leaves the value in LDS where the
 // site's lane picks it up (first step) or in the LDS slot the site's pull
-// reads (second step).  Both compute every rule value from the same inputs
+// reads (the others).  Both compute every rule value from the same inputs
 // with rule_value, so the state is the same to the bit.
-template <typename real, bool PER, bool TWO, bool COOP>
-__device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bool streamed, TileLds<real, COOP>& lds)
+template <typename real, bool PER, int MOST, bool COOP>
+__device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, int steps, bool streamed,
+                                           TileLds<real, COOP, MOST>& lds)
 {
+    constexpr int H = 2 * MOST - 1;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int R = a.seg;
     const int strip = tile % a.nstrips;
     const int y0 = (tile / a.nstrips) * R;
-    const int xs = strip * kStrip2 - 3;
-    const int x = xs + lane, y = y0 - 3 + wave;
+    const int xs = strip * (64 - 2 * H) - H;
+    const int x = xs + lane, y = y0 - H + wave;
+    const int top = R + 2 * H - 1;                           // the last wave
     real (*const post)[9][64] = lds.post();
     // first step, from the state buffer
     real g[9];
@@ -789,7 +794,7 @@ __device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bo
     bool in;
     int ys, s;
     site_issue<real, PER>(a, x, y, g, fl, ys, in, s);
-    const bool out_row = wave >= 3 && wave <= R + 2;        // uniform over the wave
+    const bool out_row = wave >= H && wave < R + H;        // uniform over the wave
     double ux = 0.0, uy = 0.0;
     if (out_row) {
         ux = ldu(a.U, s);
@@ -830,18 +835,18 @@ __device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bo
                 }
             }
         }
-        // profiles of the groups at the first and the second step
+        // profiles of the groups at each step
         if (tid < a.ngroups) {
             const GroupDev G = a.groups[tid];
-            lds.prof[0][tid] = profile_of<real>(G, a.t_prev);
-            lds.prof[1][tid] = profile_of<real>(G, a.t_prev + 1);
+#pragma unroll
+            for (int k = 0; k < MOST; ++k) lds.prof[k][tid] = profile_of<real>(G, a.t_prev + k);
         }
         // the state the record's rule reads: the nine populations at its site
         // x and at x - c_k
         real h0[9], hb[9];
         const bool rule1 = rec && !a.local;
         if (rule1) {
-            int rx = xs + (rpos & 255), ry = y0 - 3 + (rpos >> 8);
+            int rx = xs + (rpos & 255), ry = y0 - H + (rpos >> 8);
             bool rin;
             place<PER>(a.nx, a.ny, a.px, a.py, rx, ry, rin);
             const int so = sidx(rx, ry, a.ld);
@@ -881,9 +886,9 @@ __device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bo
     lds.dens[wave][lane] = site_finish<real, PER>(a, x, ys, in, !COOP, fl, g);
     __syncthreads();
     const bool cuts = wave_has_cuts(fl);
-    const bool out = out_row && lane >= 3 && lane <= 60 && y < a.ny && x < a.nx && fl != kVoid;
+    const bool out = out_row && lane >= H && lane <= 63 - H && y < a.ny && x < a.nx && fl != kVoid;
     bool bad = false;
-    if (wave >= 1 && wave <= R + 4) {
+    if (wave >= 1 && wave < top) {
         real o[9];
         if (lane >= 1 && lane <= 62 && fl != kVoid) {
             Window<real> w;
@@ -904,7 +909,7 @@ __device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bo
 #pragma unroll
             for (int i = 0; i < 9; ++i) o[i] = real(0);
         }
-        if constexpr (!TWO) {
+        if (steps == 1) {
             if (out) {
 #pragma unroll
                 for (int i = 0; i < 9; ++i) stu(a.dst + i * a.plane, s, o[i]);
@@ -916,76 +921,108 @@ __device__ __forceinline__ bool step_tile2(const StepArgs<real>& a, int tile, bo
 #pragma unroll
         for (int i = 0; i < 9; ++i) post[wave - 1][i][lane] = o[i];
     }
-    if constexpr (!TWO) return bad;
+    if (steps == 1) return bad;
     __syncthreads();
-    // second step, from the first step's post-collision populations
-    if constexpr (COOP) if (nrec > 0) {
-        // every rule value from the unmodified state first, then each into the
-        // slot its site pulls from (a slot another rule reads -- across a
-        // crack -- is overwritten only after all have read it)
-        real v = real(0);
-        int vr = 0, vi = 0, vl = 0;
-        bool put = false;
-        if (tid < nrec) {
-            const TileRec<real>& L = lds.recs[tid];
-            const int w = L.pos >> 8, l = L.pos & 255;
-            if (w >= 2 && w <= R + 3 && l >= 2 && l <= 61) {
-                const int meta = L.meta, kind = link_kind(L);
-                const int g1 = ((meta >> 8) & 255) - 1, g2 = ((meta >> 16) & 255) - 1;
-                const int k = meta & 15, kb = OPP(k), dx = CX(k), dy = CY(k);
-                const LdsPrev<real> prev{post, w - 1, l};
-                real drx, pxxx, pyyx, pxyx;
-                stored_moments<real>(prev, 0, 0, drx, pxxx, pyyx, pxyx);
-                const real gk = prev(k, 0, 0), gkb = prev(kb, 0, 0);
-                const real gky = ((meta >> 6) & 1) ? prev(k, -dx, -dy) : real(0);
-                real dry = real(0), pxxy = real(0), pyyy = real(0), pxyy = real(0);
-                if (kind != SLBM_DIRICHLET && L.wy != real(0)) stored_moments<real>(prev, -dx, -dy, dry, pxxy, pyyy, pxyy);
-                const real p1 = lds.prof[1][g1];
-                const real p2 = (kind != SLBM_DIRICHLET && g2 >= 0) ? lds.prof[1][g2] : real(0);
-                v = rule_value<real>(a, L, gk, gkb, gky, drx, pxxx, pyyx, pxyx, dry, pxxy, pyyy, pxyy, p1, p2);
-                vr = w - 1 + dy;
-                vi = kb;
-                vl = l + dx;
-                put = true;
+    // the other steps, each from the post-collision populations of the one
+    // before it, on the rows and lanes `e` and more from the workgroup's edges
+    for (int st = 1; st < steps; ++st) {
+        const int e = 2 * st;
+        if constexpr (COOP) if (nrec > 0) {
+            // every rule value from the unmodified state first, then each into the
+            // slot its site pulls from (a slot another rule reads -- across a
+            // crack -- is overwritten only after all have read it)
+            real v = real(0);
+            int vr = 0, vi = 0, vl = 0;
+            bool put = false;
+            if (tid < nrec) {
+                const TileRec<real>& L = lds.recs[tid];
+                const int w = L.pos >> 8, l = L.pos & 255;
+                if (w >= e && w <= top - e && l >= e && l <= 63 - e) {
+                    const int meta = L.meta, kind = link_kind(L);
+                    const int g1 = ((meta >> 8) & 255) - 1, g2 = ((meta >> 16) & 255) - 1;
+                    const int k = meta & 15, kb = OPP(k), dx = CX(k), dy = CY(k);
+                    const LdsPrev<real> prev{post, w - 1, l};
+                    real drx, pxxx, pyyx, pxyx;
+                    stored_moments<real>(prev, 0, 0, drx, pxxx, pyyx, pxyx);
+                    const real gk = prev(k, 0, 0), gkb = prev(kb, 0, 0);
+                    const real gky = ((meta >> 6) & 1) ? prev(k, -dx, -dy) : real(0);
+                    real dry = real(0), pxxy = real(0), pyyy = real(0), pxyy = real(0);
+                    if (kind != SLBM_DIRICHLET && L.wy != real(0)) stored_moments<real>(prev, -dx, -dy, dry, pxxy, pyyy, pxyy);
+                    const real p1 = lds.prof[st][g1];
+                    const real p2 = (kind != SLBM_DIRICHLET && g2 >= 0) ? lds.prof[st][g2] : real(0);
+                    v = rule_value<real>(a, L, gk, gkb, gky, drx, pxxx, pyyx, pxyx, dry, pxxy, pyyy, pxyy, p1, p2);
+                    vr = w - 1 + dy;
+                    vi = kb;
+                    vl = l + dx;
+                    put = true;
+                }
             }
+            __syncthreads();
+            if (put) post[vr][vi][vl] = v;
+            __syncthreads();
+        }
+        if (wave >= e && wave <= top - e) {
+            const int r = wave - 1;
+            const int lc = lane < 2 ? 2 : (lane > 61 ? 61 : lane);   // lanes 0, 1, 62, 63: no site of these steps
+#pragma unroll
+            for (int i = 0; i < 9; ++i) g[i] = post[r - CY(i)][i][lc - CX(i)];
+            const bool live = fl != kVoid;
+            if constexpr (!COOP)
+                if (live && fl != 0) boundary_fixup<real>(a, LdsPrev<real>{post, r, lc}, s, fl, a.t_prev + st, g);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) g[i] = live ? g[i] : real(0);
+            lds.dens[wave][lane] = g[0] + g[1] + g[2] + g[3] + g[4] + g[5] + g[6] + g[7] + g[8];
         }
         __syncthreads();
-        if (put) post[vr][vi][vl] = v;
-        __syncthreads();
-    }
-    if (wave >= 2 && wave <= R + 3) {
-        const int r = wave - 1;
-        const int lc = lane < 2 ? 2 : (lane > 61 ? 61 : lane);   // lanes 0, 1, 62, 63: no second-step site
+        if (MOST > 2 && st + 1 < steps) {
+            if (wave > e && wave < top - e) {
+                real o[9];
+                if (lane >= 1 && lane <= 62 && fl != kVoid) {
+                    Window<real> w;
+                    w.m = lds.dens[wave - 1][lane]; w.m_l = lds.dens[wave - 1][lane - 1]; w.m_r = lds.dens[wave - 1][lane + 1];
+                    w.c_l = lds.dens[wave][lane - 1]; w.c_r = lds.dens[wave][lane + 1];
+                    real jx, jy, ir;
+                    const bool b = cuts ? collide_core<real, true>(a, g, fl, w, lds.dens[wave + 1][lane],
+                                                                   lds.dens[wave + 1][lane - 1], lds.dens[wave + 1][lane + 1],
+                                                                   o, jx, jy, ir)
+                                        : collide_core<real, false>(a, g, fl, w, lds.dens[wave + 1][lane],
+                                                                    lds.dens[wave + 1][lane - 1], lds.dens[wave + 1][lane + 1],
+                                                                    o, jx, jy, ir);
+                    if (out) {
+                        bad |= b;
+                        advance_u(ux, uy, jx, jy, ir);
+                    }
+                } else {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = post[r - CY(i)][i][lc - CX(i)];
-        const bool live = fl != kVoid;
-        if constexpr (!COOP)
-            if (live && fl != 0) boundary_fixup<real>(a, LdsPrev<real>{post, r, lc}, s, fl, a.t_prev + 1, g);
+                    for (int i = 0; i < 9; ++i) o[i] = real(0);
+                }
 #pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = live ? g[i] : real(0);
-        lds.dens[wave][lane] = g[0] + g[1] + g[2] + g[3] + g[4] + g[5] + g[6] + g[7] + g[8];
-    }
-    __syncthreads();
-    if (out) {
-        Window<real> w;
-        w.m = lds.dens[wave - 1][lane]; w.m_l = lds.dens[wave - 1][lane - 1]; w.m_r = lds.dens[wave - 1][lane + 1];
-        w.c_l = lds.dens[wave][lane - 1]; w.c_r = lds.dens[wave][lane + 1];
-        real o[9], jx, jy, ir;
-        bad |= cuts ? collide_core<real, true>(a, g, fl, w, lds.dens[wave + 1][lane], lds.dens[wave + 1][lane - 1],
-                                               lds.dens[wave + 1][lane + 1], o, jx, jy, ir)
-                    : collide_core<real, false>(a, g, fl, w, lds.dens[wave + 1][lane], lds.dens[wave + 1][lane - 1],
-                                                lds.dens[wave + 1][lane + 1], o, jx, jy, ir);
-        advance_u(ux, uy, jx, jy, ir);
-        if (streamed) {                                 // uniform over the workgroup
+                for (int i = 0; i < 9; ++i) post[wave - 1][i][lane] = o[i];
+            }
+            __syncthreads();
+            continue;
+        }
+        if (out) {
+            Window<real> w;
+            w.m = lds.dens[wave - 1][lane]; w.m_l = lds.dens[wave - 1][lane - 1]; w.m_r = lds.dens[wave - 1][lane + 1];
+            w.c_l = lds.dens[wave][lane - 1]; w.c_r = lds.dens[wave][lane + 1];
+            real o[9], jx, jy, ir;
+            bad |= cuts ? collide_core<real, true>(a, g, fl, w, lds.dens[wave + 1][lane], lds.dens[wave + 1][lane - 1],
+                                                   lds.dens[wave + 1][lane + 1], o, jx, jy, ir)
+                        : collide_core<real, false>(a, g, fl, w, lds.dens[wave + 1][lane], lds.dens[wave + 1][lane - 1],
+                                                    lds.dens[wave + 1][lane + 1], o, jx, jy, ir);
+            advance_u(ux, uy, jx, jy, ir);
+            if (streamed) {                                 // uniform over the workgroup
 #pragma unroll
-            for (int i = 0; i < 9; ++i) stu_nt(a.dst + i * a.plane, s, o[i]);
-            stu_nt(a.U, s, ux);
-            stu_nt(a.U + a.plane, s, uy);
-        } else {
+                for (int i = 0; i < 9; ++i) stu_nt(a.dst + i * a.plane, s, o[i]);
+                stu_nt(a.U, s, ux);
+                stu_nt(a.U + a.plane, s, uy);
+            } else {
 #pragma unroll
-            for (int i = 0; i < 9; ++i) stu(a.dst + i * a.plane, s, o[i]);
-            stu(a.U, s, ux);
-            stu(a.U + a.plane, s, uy);
+                for (int i = 0; i < 9; ++i) stu(a.dst + i * a.plane, s, o[i]);
+                stu(a.U, s, ux);
+                stu(a.U + a.plane, s, uy);
+            }
         }
     }
     return bad;
@@ -1007,7 +1044,22 @@ __global__ __launch_bounds__(1024, W) void k_step2(StepArgs<real> a, TileOrder o
     __shared__ TileLds<real, COOP> lds;
     const int tile = xcd_map(turn(blockIdx.x, gridDim.x, order.back), gridDim.x, a.group_shift);
     if (tile >= a.ntiles) return;                 // uniform over the workgroup
-    flag_divergence(a.diverged, step_tile2<real, PER, true, COOP>(a, tile, (int)blockIdx.x < order.streamed, lds));
+    flag_divergence(a.diverged, step_tile2<real, PER, 2, COOP>(a, tile, 2, (int)blockIdx.x < order.streamed, lds));
+}
+
+// Up to four time steps of a small plate: workgroups of kRows4 + 14 waves,
+// 50-column strips.  A launch of a plate of a few tiles is bound by its start,
+// one round of loads and its end (5 to 6 us), whatever it computes, so steps
+// on top are worth most of their sites being halo: 128^2 fp64 14.4 us for four
+// against 8.1 for two.
+constexpr int kSteps4 = 4, kRows4 = 2, kHalo4 = 2 * kSteps4 - 1, kStrip4 = 64 - 2 * kHalo4;
+template <typename real, bool PER, bool COOP>
+__global__ __launch_bounds__(64 * (kRows4 + 2 * kHalo4)) void k_step4(StepArgs<real> a, int steps)
+{
+    __shared__ TileLds<real, COOP, kSteps4> lds;
+    const int tile = xcd_map(blockIdx.x, gridDim.x, a.group_shift);
+    if (tile >= a.ntiles) return;                 // uniform over the workgroup
+    flag_divergence(a.diverged, step_tile2<real, PER, kSteps4, COOP>(a, tile, steps, false, lds));
 }
 
 // Per-plate state of the batched step, in device memory so that a captured
@@ -1089,9 +1141,9 @@ __global__ __launch_bounds__(1024, W) void k_step2_batch(BatchPlate<real>* __res
     if (!B.active || B.halted) return;
     const bool streamed = (int)blockIdx.x < order.streamed;
     if (maxk >= 2 && B.remaining >= 2)
-        flag_divergence(B.args.diverged, step_tile2<real, false, true, COOP>(B.args, lt, streamed, lds));
+        flag_divergence(B.args.diverged, step_tile2<real, false, 2, COOP>(B.args, lt, 2, streamed, lds));
     else
-        flag_divergence(B.args.diverged, step_tile2<real, false, false, COOP>(B.args, lt, streamed, lds));
+        flag_divergence(B.args.diverged, step_tile2<real, false, 2, COOP>(B.args, lt, 1, streamed, lds));
 }
 
 }  // namespace slbm_dev
