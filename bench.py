@@ -190,7 +190,7 @@ def has_ext_links3(box):
 
 
 def measured_traffic3(box, prec):
-    """Calibrated counter bytes per step of the two 3-D kernels
+    """Calibrated counter bytes per step of the 3-D kernels
     (profiles/traffic_<box>_<precision>.json), or None when there is none or
     the kernels changed since."""
     path = os.path.join(ROOT, "profiles", f"traffic_{box.name}_{prec}.json")
@@ -203,7 +203,7 @@ def measured_traffic3(box, prec):
         return None
     shapes = d.get("shapes", {})
     kernels = ("k3_links_ext",) if has_ext_links3(box) else ()
-    kernels += ("k3_density", "k3_step")
+    kernels += ("k3_march",)
     parts = [shapes.get(k) for k in kernels]
     return None if None in parts else sum(p["traffic_bytes_per_launch"] for p in parts)
 
@@ -281,17 +281,17 @@ def time_box3(torch, stream, box, prec, steps, warm):
                    "material_sites": sites,
                    "precision": "fp32 populations and arithmetic, fp64 displacement" if prec == "fp32" else "fp64",
                    "lambda_over_mu": box.lam / box.mu, "tau": box.tau,
-                   "bench_step": "one D3Q19 time step of the whole box (density pass and step kernel; "
+                   "bench_step": "one D3Q19 time step of the whole box (density and step in one launch; "
                                  "with cut links the step also forms the next step's rule values)",
                    "diverged": diverged, "wall_s": round(wall, 4)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic3(box, prec),
-                     "kernel": ("k3_links_ext + " if has_ext_links3(box) else "") + "k3_density + k3_step",
+                     "kernel": ("k3_links_ext + " if has_ext_links3(box) else "") + "k3_march",
                      "bytes_per_site": bps, "bytes_per_step": step_bytes,
-                     "launches_per_step": 3 if has_ext_links3(box) else 2,
+                     "launches_per_step": 2 if has_ext_links3(box) else 1,
                      "avg_step_us": round(t_step * 1e6, 3),
-                     "note": "achieved counts the step's algorithmic bytes over the time of all its launches; "
-                             "the density pass re-reads the pulled populations (traffic: measured bytes per step)"},
+                     "note": "achieved counts the step's algorithmic bytes over the time of all its launches "
+                             "(traffic: measured bytes per step)"},
     }
     s.close()
     return result
@@ -303,8 +303,8 @@ def run_3d(args, torch, dev, stream, n, kind="cube"):
     traction, periodic in y and z; kind "cavities", a porous solid periodic on
     every axis with (n/64)^3 pressurised spherical cavities (cut links of
     every q and normal).  fp32 populations, fp64 displacement, from rest.  One
-    bench step is one time step of the whole box (two launches: density pass,
-    step); the rate counts material sites."""
+    bench step is one time step of the whole box (one launch); the rate counts
+    material sites."""
     from paper_2208_04088_amd import slbm
     steps = args.steps if args.steps_given else 1000
     box, sample = box3_of(kind, n, steps)

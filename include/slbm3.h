@@ -154,7 +154,8 @@ int slbm3_create(const slbm3_params* params, slbm3_handle* out);
 int slbm3_init_fields(slbm3_handle h, const double* rho, const double* vel, const double* sigma,
                       const double* u);
 
-/* Queues nsteps time steps (two launches each). */
+/* Queues nsteps time steps (of one launch each in a large box, else of two, one
+ * more with extrapolated Neumann links). */
 int slbm3_step(slbm3_handle h, int64_t nsteps);
 
 /* Waits for queued work.  SLBM_E_DIVERGED if a step produced a non-finite

@@ -474,6 +474,7 @@ struct slbm_s {
     // the same for k_step4's tiles (build_four): whether the plate is one for
     // it and a call of steps takes it, its lists (null: no cut links)
     bool four_fit = false, four = false;
+    bool recorded = false;           // steps were recorded into a graph
     void* recs4 = nullptr;
     int32_t* rec4_start = nullptr;
     int64_t rec4_bytes = 0;
@@ -1035,6 +1036,17 @@ struct DeviceGuard {
     }
 };
 
+// Whether the stream records a graph.
+bool recording(hipStream_t stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusActive;
+}
+
 // Device memory of a plate: from the batch's arena for batch plates, else
 // hipMalloc.  An exhausted arena reports out-of-memory.
 hipError_t dev_alloc(slbm_s* h, void** p, size_t n)
@@ -1409,15 +1421,22 @@ int slbm_step(slbm_handle h, int64_t nsteps)
         if (nsteps < 0) return fail(SLBM_E_INVAL, "negative step count");
         DeviceGuard dg(h->device);
         int64_t i = 0;
+        // once a graph holds steps of this plate, every call leaves the buffer
+        // that as many single steps leave: the graph's replays begin from it
+        if (!h->recorded && nsteps > 0 && recording(h->stream)) h->recorded = true;
         if (h->four) {
+            int64_t singles = 0;
+            if (h->recorded)
+                while ((singles + (nsteps - singles + kSteps4 - 1) / kSteps4 - nsteps) % 2) ++singles;
             while (i < nsteps) {
-                const int k = (int)std::min<int64_t>(kSteps4, nsteps - i);
+                const int k = i < singles ? 1 : (int)std::min<int64_t>(kSteps4, nsteps - i);
                 const int rc = h->precision == SLBM_FP32 ? launch_step4<float>(h, k, true) : launch_step4<double>(h, k, true);
                 if (rc) return rc;
                 i += k;
             }
         } else if (launch_rows2(h)) {
-            for (; i + 2 <= nsteps; i += 2) {
+            const int64_t pairs = nsteps / 2 - (h->recorded && !h->two ? nsteps / 2 % 2 : 0);
+            for (; i < 2 * pairs; i += 2) {
                 int rc = h->precision == SLBM_FP32 ? launch_step2<float>(h) : launch_step2<double>(h);
                 if (rc) return rc;
             }

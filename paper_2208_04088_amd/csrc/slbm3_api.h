@@ -29,10 +29,9 @@ struct slbm3_s {
     bool local = true;
     double* U = nullptr;
     void* dens = nullptr;
-    // the walls' parts (wall_parts3), one block: k3_march reads [wcur], writes the other
+    // the walls' parts (wall_parts3), one block: k3_march reads [cur], writes the other
     void* wall[2] = {nullptr, nullptr};
-    int wcur = 0;
-    bool wall_fresh = false;              // wall[wcur] belongs to the current state
+    bool wall_fresh = false;              // wall[cur] belongs to the current state
     unsigned int* diverged = nullptr;
     double* scratch = nullptr;       // planes of doubles, on demand (host readouts, initial fields)
     int scratch_planes = 0;
@@ -43,9 +42,8 @@ struct slbm3_s {
     int32_t* bidx = nullptr;
     void* links = nullptr;
     // per link record: (A, s_kappa) of the rule (k3_step, k3_links_ext); k3_march
-    // reads [lcur] and writes the other
+    // reads one and writes the other (lval_at)
     void* lval[2] = {nullptr, nullptr};
-    int lcur = 0;
     int32_t* rowrec = nullptr;       // per 64-site chunk of a row: first record
     int32_t* wrec = nullptr;         // per workgroup of k3_step: first record
     int32_t* elink = nullptr;        // the records whose Neumann data are extrapolated
@@ -58,6 +56,14 @@ struct slbm3_s {
 namespace {
 
 using namespace slbm3_dev;
+
+bool march_box(const slbm3_s* h);
+
+// Which of the two lists of rule values belongs to the current state: with
+// k3_march the one of the state's buffer, so that a state is one place whatever
+// led there (a step from local populations, which reads none, writes in place
+// what the next step reads); without it the first.
+int lval_at(const slbm3_s* h) { return march_box(h) ? h->cur ^ (h->local ? 1 : 0) : 0; }
 
 template <typename real>
 Step3Args<real> make_args3(const slbm3_s* h, int src)
@@ -104,8 +110,8 @@ Step3Args<real> make_args3(const slbm3_s* h, int src)
         a.wskap[s] = h->wkind[s] == SLBM_DIRICHLET ? a.wkap[s] : -a.wkap[s];
         for (int k = 0; k < 3; ++k) a.wval_next[s][k] = (real)(h->wval[s][k] * ramp(n_next, h->wramp[s]));
     }
-    a.wsrc = (const real*)h->wall[h->wcur];
-    a.wdst = (real*)h->wall[h->wcur ^ 1];
+    a.wsrc = (const real*)h->wall[h->cur];
+    a.wdst = (real*)h->wall[h->cur ^ 1];
     a.omega = (real)(1.0 / h->tau);
     a.omega_h = (real)(1.0 - 0.5 / h->tau);
     a.ml = (real)(h->muL - h->lamL);
@@ -114,8 +120,8 @@ Step3Args<real> make_args3(const slbm3_s* h, int src)
     a.flags = h->flags;
     a.bidx = h->bidx;
     a.links = (const Link3<real>*)h->links;
-    a.lval = (real*)h->lval[h->lcur];
-    a.lval_next = (real*)h->lval[h->lcur ^ 1];
+    a.lval = (real*)h->lval[lval_at(h)];
+    a.lval_next = (real*)h->lval[lval_at(h) ^ 1];
     a.rowrec = h->rowrec;
     a.nlinks = (int)h->n_links;
     a.wrec = h->wrec;
@@ -502,9 +508,8 @@ int launch3_any(slbm3_s* h, int what);
 // chunk is short pays for all of it (porous solids, n^3):
 //   fp32  100 56 84   120 110 101   128 128 107   130 155 163   150 238 249   160 256 235   180 389 361   256 981 752
 //   fp64  100 125 134  128 243 220   130 294 279   150 420 398   180 662 563   256 1793 1549
-bool march3(const slbm3_s* h)
+bool march_box(const slbm3_s* h)
 {
-    if (h->local) return false;
     if (h->geo) {
         // a chunk's 64 lanes: how many of 16 hold sites
         const long long lanes = 16LL * h->nx / (64 * ((h->nx + 63) / 64));
@@ -518,6 +523,7 @@ bool march3(const slbm3_s* h)
     }
     return h->plane >= (h->px ? 850000 : (h->precision == SLBM_FP32 ? 800000 : 250000));
 }
+bool march3(const slbm3_s* h) { return !h->local && march_box(h); }
 
 // Planes a k3_march workgroup marches through, for `tiles` tiles of rows over
 // nz planes: a workgroup takes depth + 2 planes' time and a little to start,
@@ -551,15 +557,11 @@ int launch3_march(slbm3_s* h)
                            (const int32_t*)h->elink, (int)h->n_ext);
     if (!PX && !h->wall_fresh)
         hipLaunchKernelGGL((k3_wall_parts<real>), dim3((unsigned)((h->ny * h->nz + 255) / 256), 2), dim3(256), 0,
-                           h->stream, a, (real*)h->wall[h->wcur]);
+                           h->stream, a, (real*)h->wall[h->cur]);
     hipLaunchKernelGGL((k3_march<real, PX, GEO>), dim3((unsigned)((a.mtiles + 8 * a.xgroup - 1) / (8 * a.xgroup) * (8 * a.xgroup))), dim3(64 * (a.rows + 2)), 0,
                        h->stream, a);
     HIP_TRY(hipGetLastError());
-    if (GEO) h->lcur ^= 1;
-    if (!PX) {
-        h->wcur ^= 1;
-        h->wall_fresh = true;
-    }
+    if (!PX) h->wall_fresh = true;
     return SLBM_OK;
 }
 
@@ -843,6 +845,9 @@ int slbm3_step(slbm3_handle h, int64_t nsteps)
         if (!h) return fail(SLBM_E_INVAL, "null handle");
         if (nsteps < 0) return fail(SLBM_E_INVAL, "negative step count");
         DeviceGuard dg(h->device);
+        // a graph forms the walls' parts itself, and leaves none until it has run
+        const bool rec = nsteps > 0 && recording(h->stream);
+        if (rec) h->wall_fresh = false;
         for (int64_t k = 0; k < nsteps; ++k) {
             int rc = step3(h);
             if (rc) return rc;
@@ -850,6 +855,7 @@ int slbm3_step(slbm3_handle h, int64_t nsteps)
             h->local = false;
             h->step += 1;
         }
+        if (rec) h->wall_fresh = false;
         return SLBM_OK;
     });
 }
@@ -986,7 +992,7 @@ int slbm3_save(slbm3_handle h, void* buf, size_t* bytes)
         HIP_TRY(hipMemcpyAsync(p + sizeof hd, h->buf[h->cur], pop, hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipMemcpyAsync(p + sizeof hd + pop, h->U, ub, hipMemcpyDeviceToHost, h->stream));
         if (h->n_links > 0)
-            HIP_TRY(hipMemcpyAsync(p + sizeof hd + pop + ub, h->lval[h->lcur], (size_t)2 * h->n_links * h->esize,
+            HIP_TRY(hipMemcpyAsync(p + sizeof hd + pop + ub, h->lval[lval_at(h)], (size_t)2 * h->n_links * h->esize,
                                    hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         hd.diverged = (int32_t)flag;
@@ -1013,16 +1019,16 @@ int slbm3_load(slbm3_handle h, const void* buf, size_t bytes)
         // the other buffer, which the next step writes, keeps the rest state
         // at void sites from creation
         h->cur = 0;
+        h->local = hd.local != 0;
         HIP_TRY(hipMemcpyAsync(h->buf[0], p + sizeof hd, pop, hipMemcpyHostToDevice, h->stream));
         HIP_TRY(hipMemcpyAsync(h->U, p + sizeof hd + pop, ub, hipMemcpyHostToDevice, h->stream));
         if (h->n_links > 0)
-            HIP_TRY(hipMemcpyAsync(h->lval[h->lcur], p + sizeof hd + pop + ub, (size_t)2 * h->n_links * h->esize,
+            HIP_TRY(hipMemcpyAsync(h->lval[lval_at(h)], p + sizeof hd + pop + ub, (size_t)2 * h->n_links * h->esize,
                                    hipMemcpyHostToDevice, h->stream));
         unsigned int flag = (unsigned int)hd.diverged;
         HIP_TRY(hipMemcpyAsync(h->diverged, &flag, sizeof flag, hipMemcpyHostToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         h->step = hd.step;
-        h->local = hd.local != 0;
         h->wall_fresh = false;
         return SLBM_OK;
     });

@@ -706,7 +706,7 @@ __global__ __launch_bounds__(1024) void k_step(StepArgs<real> a)
 // holds row y0 - 3 + w, lane l column xs - 3 + l -- and its post-collision
 // populations stay in LDS, from where the second step pulls.  Every site's
 // arithmetic is that of two single steps, so the state is bit-identical to
-// theirs.
+// theirs.  k_step4 takes up to four steps the same way.
 constexpr int kMaxTileRows2 = 10;
 constexpr int kStrip2 = 58;
 
