@@ -500,14 +500,14 @@ int launch3_any(slbm3_s* h, int what);
 // series (2.6 us each in single, 5 us in double precision) take longer than
 // the two launches, whose every load is independent.  us per step, two
 // launches and one:
-//   fp32 slab  64^3 21 24   200x60x40 29 34   90x130x70 51 48   96^3 56 47   128^3 133 100   256^3 905 683
-//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 38 40   96^3 40 37   128^3 113 93    256^3 901 669
-//   fp64 slab  40^3 19 20   64^3 35 28        90x130x70 97 90   96^3 108 79  128^3 254 177
-//   fp64 per.  40^3 14 16   64^3 25 22        90x130x70 73 87   96^3 85 80   128^3 223 174   256^3 1682 1229
+//   fp32 slab  64^3 19 24   200x60x40 30 34   90x130x70 48 44   96^3 52 43   128^3 123 99   256^3 897 686
+//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 37 40   96^3 39 35   128^3 110 94   256^3 897 672
+//   fp64 slab  40^3 17 20   64^3 32 25        90x130x70 87 90   96^3 106 77  128^3 228 175
+//   fp64 per.  40^3 13 16   64^3 24 22        90x130x70 73 87   96^3 91 75   128^3 205 169   256^3 1669 1230
 // With cut links the series is longer (6 us a plane), and a row whose last
 // chunk is short pays for all of it (porous solids, n^3):
-//   fp32  100 56 84   120 110 101   128 128 107   130 155 163   150 238 249   160 256 235   180 389 361   256 981 752
-//   fp64  100 125 134  128 243 220   130 294 279   150 420 398   180 662 563   256 1793 1549
+//   fp32  100 55 84   120 108 99   128 122 104   130 151 163   150 225 249   160 241 235   180 374 361   256 964 752
+//   fp64  100 125 134  128 226 219  130 280 294  150 404 420   180 648 563   256 1777 1547
 bool march_box(const slbm3_s* h)
 {
     if (h->geo) {
@@ -558,8 +558,19 @@ int launch3_march(slbm3_s* h)
     if (!PX && !h->wall_fresh)
         hipLaunchKernelGGL((k3_wall_parts<real>), dim3((unsigned)((h->ny * h->nz + 255) / 256), 2), dim3(256), 0,
                            h->stream, a, (real*)h->wall[h->cur]);
-    hipLaunchKernelGGL((k3_march<real, PX, GEO>), dim3((unsigned)((a.mtiles + 8 * a.xgroup - 1) / (8 * a.xgroup) * (8 * a.xgroup))), dim3(64 * (a.rows + 2)), 0,
-                       h->stream, a);
+    const unsigned unit = 8 * a.xgroup;
+    const dim3 grid((a.mtiles + unit - 1) / unit * unit), blk(64 * (a.rows + 2));
+    // stores past the caches once the state (both buffers, U) exceeds the 256 MB
+    // memory-side cache; below, the next launch finds what plain stores left in
+    // it.  Boxes with cut links are above it wherever k3_march takes them.  us per
+    // step of slabs, streamed and plain:
+    //   fp32  96^3 (155 MB) 54 43   112^3 (247 MB) 80 56   116^3 (274 MB) 81 80   128^3 99 102   160^3 196 204
+    //   fp64  64^3 (85 MB) 27 25    90^3 (239 MB) 82 56    90x130x70 (268 MB) 90 93   96^3 77 82   128^3 175 181
+    const bool stream = GEO || h->plane * (long long)(2 * kQ * sizeof(real) + 24) > 250000000;
+    if (stream)
+        hipLaunchKernelGGL((k3_march<real, PX, GEO, true>), grid, blk, 0, h->stream, a);
+    else
+        hipLaunchKernelGGL((k3_march<real, PX, GEO, GEO>), grid, blk, 0, h->stream, a);
     HIP_TRY(hipGetLastError());
     if (!PX) h->wall_fresh = true;
     return SLBM_OK;

@@ -887,7 +887,8 @@ __global__ __launch_bounds__(256) void k3_step(Step3Args<real> a)
 //   registers, 731 with none);
 // - tiles dealt to the XCDs in groups of 16, so that the chip moves through one
 //   region of the box (groups of 8 to 32 689 us, contiguous bands 722, 1 711);
-// - stores past the L2 (689 -> 669 us, porous solid 854 -> 800);
+// - stores past the caches, where the state is larger than they are (689 ->
+//   669 us, porous solid 854 -> 800; launch3_march has the smaller ones);
 // - 8 rows: 6 rows 780 us (their halo, and a last tile of 4 rows), 14 rows 765;
 //   one or two workgroups on a CU make no difference.
 // fp64: 8 waves, what the LDS of a CU holds of their populations (110 KB).
@@ -931,10 +932,13 @@ struct PlaneWalk {
         base += step;
         asm("" : "+s"(base));
     }
-    // read again only by the next launch: past the L2, which then holds the rows
-    // that neighbouring workgroups share
-    template <typename T>
-    __device__ __forceinline__ void store(unsigned off, T v) const { __builtin_nontemporal_store(v, (gptr3<T>)(base + off)); }
+    // what only the next launch reads again; STREAM: past the caches
+    template <bool STREAM, typename T>
+    __device__ __forceinline__ void store(unsigned off, T v) const
+    {
+        if constexpr (STREAM) __builtin_nontemporal_store(v, (gptr3<T>)(base + off));
+        else *(gptr3<T>)(base + off) = v;
+    }
     // += in memory (one rounded sum, as a load, an add and a store)
     __device__ __forceinline__ void add(unsigned off, double v) const
     {
@@ -1025,7 +1029,7 @@ struct RowRec3 {
     int r0, r1, left, right;
 };
 
-template <typename real, bool PX, bool GEO>
+template <typename real, bool PX, bool GEO, bool STREAM>
 __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(real), GEO)) void k3_march(Step3Args<real> a)
 {
     constexpr int NW = kMarchWaves(sizeof(real));
@@ -1322,7 +1326,7 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
         PlaneWalk w(a.dst, a.stride);
 #pragma unroll
         for (int i = 0; i < kQ; ++i) {
-            w.store(s * (unsigned)sizeof(real), live ? o[i] : real(0));
+            w.template store<STREAM>(s * (unsigned)sizeof(real), live ? o[i] : real(0));
             w.next();
         }
         PlaneWalk wu(a.U, a.stride);
@@ -1340,7 +1344,7 @@ __global__ __launch_bounds__(64 * kMarchWaves(sizeof(real)), kMarchOcc(sizeof(re
             PlaneWalk ww(a.wdst + side * 5 * nyz, nyz);
 #pragma unroll
             for (int k = 0; k < 5; ++k) {
-                ww.store((unsigned)(zc * ny + y) * (unsigned)sizeof(real), A[k]);
+                ww.template store<STREAM>((unsigned)(zc * ny + y) * (unsigned)sizeof(real), A[k]);
                 ww.next();
             }
         }

@@ -52,6 +52,28 @@ def test_large_boxes_match_the_reference(S3, kind, nx, ry, rz, prec, tol):  # no
           f"{kind} {nx} {prec}", big)
 
 
+# states on the other side of 250 MB, where the stores change: fp64 below, fp32 above
+@pytest.mark.parametrize("kind,nx,ry,rz,prec,tol", [("slab", 65, 9, 14, "fp64", FP64_TOL), ("flipped", 128, 13, 26, "fp32", FP32_TOL),
+                                                    ("periodic", 129, 13, 23, "fp32", FP32_TOL)])
+def test_both_kinds_of_stores_match_the_reference(S3, kind, nx, ry, rz, prec, tol):  # noqa: F811
+    ny, nz = 9, 5
+    small, big = box_of(kind, nx, ny, nz), box_of(kind, nx, ny * ry, nz * rz)
+    state = big.n_sites * (38 * (8 if prec == "fp64" else 4) + 24)
+    assert big.n_sites >= 250000 and (state < 250e6) == (prec == "fp64")
+    vel = B.random_velocity(small, 19, 1e-3)
+    tile = lambda v: np.tile(v, (1, rz, ry, 1))
+    ref = Oracle3D(small, extended=(prec == "fp64"))
+    ref.init_fields(vel=vel)
+    ref.step(6)
+    with S3.Solver3(big, prec) as s:
+        s.init_fields(vel=tile(vel))
+        s.step(6)
+        s.sync()
+        got = s.displacement(), s.moments()
+    rr, jr, Pr, sr = ref.moments()
+    check(got, (tile(ref.displacement()), (tile(rr[None])[0], tile(jr), tile(Pr), tile(sr))), tol, f"{kind} {nx} {prec}", big)
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_one_launch_equals_two(S3, prec):  # noqa: F811
     """A mask without void takes the two launches: the same state as the
