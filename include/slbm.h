@@ -209,7 +209,8 @@ int slbm_time(slbm_handle h, int64_t* step, double* t_user);
  * Results do not depend on the shape. */
 int slbm_set_launch(slbm_handle h, int32_t seg_rows, int32_t strip);
 
-/* The per-tile cut-link lists of the two-steps-per-launch step (strip 58):
+/* The per-tile cut-link lists of the two-steps-per-launch step (strip 58; on a
+ * small plate whose launch is left to the library, of its four-step tiles):
  * the rows per tile they were built for (0: none, and the step evaluates the
  * boundary rules of section 4 site by site), the records in all lists, and
  * the most in one tile.  Lists are kept only when every tile's fits the

@@ -477,7 +477,8 @@ struct slbm_s {
     bool recorded = false;           // steps were recorded into a graph
     void* recs4 = nullptr;
     int32_t* rec4_start = nullptr;
-    int64_t rec4_bytes = 0;
+    int64_t rec4_bytes = 0, rec4_count = 0;
+    int32_t rec4_max = 0;
     int64_t rec_count = 0;
     int32_t rec_max = 0;
 };
@@ -724,34 +725,33 @@ TileLayout tile_layout(int nx, int ny, bool px, bool py, int R, int H, const int
     return out;
 }
 
-// The block a layout's lists take on the device: the records, each with its
-// link's coefficients (TileRec), then the tiles' first records.
+// A tile's record of a cut link at a position in the tile.
 template <typename real>
-std::vector<char> tile_block(const slbm_s* h, const TileLayout& lay)
+__host__ __device__ inline TileRec<real> tile_rec(const LinkDev<real>& d, int32_t pos)
 {
-    const size_t total = lay.link.size(), rb = total * sizeof(TileRec<real>), sb = lay.start.size() * sizeof(int32_t);
-    const LinkDev<real>* L = reinterpret_cast<const LinkDev<real>*>(h->link_host.data());
-    std::vector<char> block(rb + sb);
-    TileRec<real>* rec = reinterpret_cast<TileRec<real>*>(block.data());
-    for (size_t k = 0; k < total; ++k) {
-        TileRec<real>& r = rec[k];
-        const LinkDev<real>& d = L[lay.link[k]];
-        r.kappa = d.kappa; r.wx = d.wx; r.wy = d.wy; r.D = d.D;
-        for (int j = 0; j < 4; ++j) r.be[j] = d.be[j];
-        for (int j = 0; j < 3; ++j) {
-            r.K1[j] = d.K1[j];
-            r.K2[j] = d.K2[j];
-            r.E3[j] = d.E3[j];
-        }
-        r.meta = d.k | (d.kind << 4) | (d.behind << 6) | ((d.g1 + 1) << 8) | ((d.g2 + 1) << 16);
-        r.pos = lay.pos[k];
+    TileRec<real> r;
+    r.kappa = d.kappa; r.wx = d.wx; r.wy = d.wy; r.D = d.D;
+    for (int j = 0; j < 4; ++j) r.be[j] = d.be[j];
+    for (int j = 0; j < 3; ++j) {
+        r.K1[j] = d.K1[j];
+        r.K2[j] = d.K2[j];
+        r.E3[j] = d.E3[j];
     }
-    std::memcpy(block.data() + rb, lay.start.data(), sb);
-    return block;
+    r.meta = d.k | (d.kind << 4) | (d.behind << 6) | ((d.g1 + 1) << 8) | ((d.g2 + 1) << 16);
+    r.pos = pos;
+    return r;
+}
+
+template <typename real>
+__global__ __launch_bounds__(256) void k_tile_records(const LinkDev<real>* links, const int32_t* link, const int32_t* pos,
+                                                      int n, TileRec<real>* rec)
+{
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k < n) rec[k] = tile_rec<real>(links[link[k]], pos[k]);
 }
 
 // The plate's tile lists on the device for tiles of seg rows: tile_layout's
-// records (tile_block).  When a tile has more
+// records (tile_rec).  When a tile has more
 // than the cooperative kernel takes (or the plate more groups than it
 // tabulates), no lists are kept and the two-step kernel takes the rules site
 // by site.
@@ -769,8 +769,12 @@ int build_tile_records(slbm_s* h, int seg)
     const TileLayout lay =
         tile_layout(h->nx, h->ny, h->px != 0, h->py != 0, R, 3, h->link_site.data(), h->n_links, cap);
     if (lay.most > cap) return SLBM_OK;
-    const std::vector<char> block = tile_block<real>(h, lay);
-    const size_t total = lay.link.size();
+    const size_t total = lay.link.size(), rb = total * sizeof(TileRec<real>), sb = lay.start.size() * sizeof(int32_t);
+    const LinkDev<real>* L = reinterpret_cast<const LinkDev<real>*>(h->link_host.data());
+    std::vector<char> block(rb + sb);
+    for (size_t k = 0; k < total; ++k)
+        reinterpret_cast<TileRec<real>*>(block.data())[k] = tile_rec<real>(L[lay.link[k]], lay.pos[k]);
+    std::memcpy(block.data() + rb, lay.start.data(), sb);
     const hipError_t e = dev_alloc(h, &h->recs, block.size());
     if (e != hipSuccess) {
         drop_tile_records(h);
@@ -780,7 +784,7 @@ int build_tile_records(slbm_s* h, int seg)
         if (e == hipErrorOutOfMemory) return fail(SLBM_E_NOMEM, "no device memory for the tile record lists");
         HIP_TRY(e);
     }
-    h->rec_start = (int32_t*)((char*)h->recs + total * sizeof(TileRec<real>));
+    h->rec_start = (int32_t*)((char*)h->recs + rb);
     HIP_TRY(hipMemcpyAsync(h->recs, block.data(), block.size(), hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     h->rec_fit = true;
@@ -810,15 +814,27 @@ int build_four(slbm_s* h)
         const TileLayout lay = tile_layout(h->nx, h->ny, h->px != 0, h->py != 0, kRows4, kHalo4, h->link_site.data(),
                                            h->n_links, kTileRecCap);
         if (lay.most > kTileRecCap) return SLBM_OK;
-        const std::vector<char> block = tile_block<real>(h, lay);
-        if (dev_alloc(h, &h->recs4, block.size()) != hipSuccess) {
+        // the links and their positions go up, the device forms the records: each
+        // link is in some ten tiles, and creation would take a third longer
+        const size_t total = lay.link.size(), rb = total * sizeof(TileRec<real>), n = lay.start.size();
+        std::vector<int32_t> up(lay.start);
+        up.insert(up.end(), lay.link.begin(), lay.link.end());
+        up.insert(up.end(), lay.pos.begin(), lay.pos.end());
+        const size_t bytes = rb + up.size() * sizeof(int32_t);
+        if (dev_alloc(h, &h->recs4, bytes) != hipSuccess) {
             (void)hipGetLastError();
             h->recs4 = nullptr;
             return SLBM_OK;                                // no room: two steps per launch
         }
-        h->rec4_start = (int32_t*)((char*)h->recs4 + lay.link.size() * sizeof(TileRec<real>));
-        h->rec4_bytes = (int64_t)block.size();
-        HIP_TRY(hipMemcpyAsync(h->recs4, block.data(), block.size(), hipMemcpyHostToDevice, h->stream));
+        h->rec4_start = (int32_t*)((char*)h->recs4 + rb);
+        h->rec4_bytes = (int64_t)bytes;
+        h->rec4_count = (int64_t)total;
+        h->rec4_max = lay.most;
+        HIP_TRY(hipMemcpyAsync(h->rec4_start, up.data(), up.size() * sizeof(int32_t), hipMemcpyHostToDevice, h->stream));
+        hipLaunchKernelGGL((k_tile_records<real>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, h->stream,
+                           (const LinkDev<real>*)h->links, h->rec4_start + n, h->rec4_start + n + total, (int)total,
+                           (TileRec<real>*)h->recs4);
+        HIP_TRY(hipGetLastError());
         HIP_TRY(hipStreamSynchronize(h->stream));
     }
     h->four_fit = h->four = true;
@@ -1375,8 +1391,10 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
     h->local = true;
     // lists for the library's own launch (a batch has its own; a plate without
     // room for them takes the rules site by site)
-    if (!arena && tile_records(h, default_rows2(h)) != SLBM_OK) drop_tile_records(h);
-    if (!arena) (void)(h->precision == SLBM_FP32 ? build_four<float>(h) : build_four<double>(h));
+    if (!arena) {
+        (void)(h->precision == SLBM_FP32 ? build_four<float>(h) : build_four<double>(h));
+        if (!h->four && tile_records(h, default_rows2(h)) != SLBM_OK) drop_tile_records(h);
+    }
     *out = h;
     return SLBM_OK;
 }
@@ -1620,7 +1638,7 @@ int slbm_set_launch(slbm_handle h, int32_t seg_rows, int32_t strip)
             return fail(SLBM_E_INVAL, "strip must be 0, 58, 62 or 64");
         if (seg_rows > (strip == kStrip2 ? kMaxTileRows2 : kMaxTileRows))
             return fail(SLBM_E_INVAL, "rows per tile above the maximum (14; 10 with two steps per launch)");
-        if (strip == kStrip2 || (strip == 0 && seg_rows == 0)) {
+        if (strip == kStrip2 || (strip == 0 && seg_rows == 0 && !h->four_fit)) {
             DeviceGuard dg(h->device);
             const int rc = tile_records(h, strip == kStrip2 ? seg_rows : default_rows2(h));
             if (rc) return rc;
@@ -1675,9 +1693,10 @@ int slbm_boundary_lists(slbm_handle h, int32_t* rows, int64_t* records, int32_t*
 {
     return guarded([&]() -> int {
         if (!h) return fail(SLBM_E_INVAL, "null handle");
-        if (rows) *rows = h->rec_fit ? h->rec_seg : 0;
-        if (records) *records = h->rec_fit ? h->rec_count : 0;
-        if (max_per_tile) *max_per_tile = h->rec_fit ? h->rec_max : 0;
+        const bool four = launch_is_default(h) && h->four;
+        if (rows) *rows = four ? (h->recs4 ? kRows4 : 0) : (h->rec_fit ? h->rec_seg : 0);
+        if (records) *records = four ? h->rec4_count : (h->rec_fit ? h->rec_count : 0);
+        if (max_per_tile) *max_per_tile = four ? h->rec4_max : (h->rec_fit ? h->rec_max : 0);
         return SLBM_OK;
     });
 }
