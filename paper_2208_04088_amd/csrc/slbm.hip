@@ -420,6 +420,17 @@ struct Arena {
 
 struct slbm_batch_s;
 
+// A plate's per-tile cut-link lists on the device for tiles of `seg` rows.
+struct TileLists {
+    void* recs = nullptr;            // the records, then `start` in the same block
+    int32_t* start = nullptr;
+    int seg = 0;
+    bool fit = false;                // every tile's list fits the cooperative kernel
+    bool held = false;               // a recorded graph reads them: kept until the plate goes
+    int64_t bytes = 0, count = 0;
+    int32_t most = 0;
+};
+
 struct slbm_s {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -460,17 +471,13 @@ struct slbm_s {
     int group = 0;                   // workgroups to XCDs: 0 contiguous bands, g > 0 interleaved groups of g
     std::vector<uint8_t> mask;
     // per-tile cut-link records of the two-step kernel (build_tile_records):
-    // the link records as uploaded and each link's site, the lists on the
-    // device for tiles of rec_seg rows, rec_fit when every tile's fits the
-    // cooperative kernel
+    // the link records as uploaded and each link's site, the lists in use, and
+    // those of other rows that graphs hold (at most one per number of rows)
     std::vector<char> link_host;
     std::vector<int32_t> link_site;
     int ngroups = 0;
-    void* recs = nullptr;            // the records, then rec_start in the same block
-    int32_t* rec_start = nullptr;
-    int rec_seg = 0;
-    bool rec_fit = false;
-    int64_t rec_bytes = 0;
+    TileLists rec;
+    std::vector<TileLists> rec_kept;
     // the same for k_step4's tiles (build_four): whether the plate is one for
     // it and a call of steps takes it, its lists (null: no cut links)
     bool four_fit = false, four = false;
@@ -479,8 +486,6 @@ struct slbm_s {
     int32_t* rec4_start = nullptr;
     int64_t rec4_bytes = 0, rec4_count = 0;
     int32_t rec4_max = 0;
-    int64_t rec_count = 0;
-    int32_t rec_max = 0;
 };
 
 namespace {
@@ -615,38 +620,36 @@ int launch_rows2(const slbm_s* h)
     return h->two ? seg2_rows(h->seg) : (launch_is_default(h) ? default_rows2(h) : 0);
 }
 
-// Frees a plate's tile lists: at once for a single plate (hipFree waits for
-// the device), for a batch plate back to the batch's arena once the launches
-// and readouts queued so far have completed.
+// Takes a plate's tile lists out of use.  Lists that a recorded graph reads are
+// put aside until the plate goes (build_tile_records takes them up again).  Any
+// others are freed: at once for a single plate (hipFree waits for the device),
+// for a batch plate back to the batch's arena once the launches and readouts
+// queued so far have completed.
 void drop_tile_records(slbm_s* h)
 {
-    if (h->arena && h->recs) {
+    if (h->rec.held) {
+        h->rec_kept.push_back(h->rec);
+    } else if (h->arena && h->rec.recs) {
         if (h->batch) {
             hipEvent_t ec = nullptr, es = nullptr;
             if (hipEventCreateWithFlags(&ec, hipEventDisableTiming) == hipSuccess &&
                 hipEventCreateWithFlags(&es, hipEventDisableTiming) == hipSuccess &&
                 hipEventRecord(ec, batch_compute_stream(h->batch)) == hipSuccess &&
                 hipEventRecord(es, h->stream) == hipSuccess) {
-                h->arena->release_after({ec, es}, {h->recs});
+                h->arena->release_after({ec, es}, {h->rec.recs});
             } else {
                 if (ec) (void)hipEventDestroy(ec);
                 if (es) (void)hipEventDestroy(es);
                 (void)hipDeviceSynchronize();
-                h->arena->release(h->recs);
+                h->arena->release(h->rec.recs);
             }
         } else {
-            h->arena->release(h->recs);
+            h->arena->release(h->rec.recs);
         }
     } else {
-        if (h->recs) (void)hipFree(h->recs);
+        if (h->rec.recs) (void)hipFree(h->rec.recs);
     }
-    h->rec_start = nullptr;
-    h->recs = nullptr;
-    h->rec_seg = 0;
-    h->rec_fit = false;
-    h->rec_bytes = 0;
-    h->rec_count = 0;
-    h->rec_max = 0;
+    h->rec = TileLists{};
 }
 
 // Coordinates c + m n (any m on a periodic axis, m = 0 otherwise) in [lo, hi]:
@@ -759,9 +762,15 @@ template <typename real>
 int build_tile_records(slbm_s* h, int seg)
 {
     seg = seg2_rows(seg);
-    if (h->rec_seg == seg) return SLBM_OK;
+    if (h->rec.seg == seg) return SLBM_OK;
     drop_tile_records(h);
-    h->rec_seg = seg;
+    for (size_t i = 0; i < h->rec_kept.size(); ++i)
+        if (h->rec_kept[i].seg == seg) {
+            h->rec = h->rec_kept[i];
+            h->rec_kept.erase(h->rec_kept.begin() + (std::ptrdiff_t)i);
+            return SLBM_OK;
+        }
+    h->rec.seg = seg;
     if (h->n_links == 0 || h->ngroups > kTileGroupCap) return SLBM_OK;
     const int R = seg;
     // one record per thread of the tile's workgroup, and what its LDS holds
@@ -775,22 +784,22 @@ int build_tile_records(slbm_s* h, int seg)
     for (size_t k = 0; k < total; ++k)
         reinterpret_cast<TileRec<real>*>(block.data())[k] = tile_rec<real>(L[lay.link[k]], lay.pos[k]);
     std::memcpy(block.data() + rb, lay.start.data(), sb);
-    const hipError_t e = dev_alloc(h, &h->recs, block.size());
+    const hipError_t e = dev_alloc(h, &h->rec.recs, block.size());
     if (e != hipSuccess) {
         drop_tile_records(h);
-        h->rec_seg = seg;
+        h->rec.seg = seg;
         // a batch plate without room in the budget goes without lists
         if (e == hipErrorOutOfMemory && h->arena) return SLBM_OK;
         if (e == hipErrorOutOfMemory) return fail(SLBM_E_NOMEM, "no device memory for the tile record lists");
         HIP_TRY(e);
     }
-    h->rec_start = (int32_t*)((char*)h->recs + rb);
-    HIP_TRY(hipMemcpyAsync(h->recs, block.data(), block.size(), hipMemcpyHostToDevice, h->stream));
+    h->rec.start = (int32_t*)((char*)h->rec.recs + rb);
+    HIP_TRY(hipMemcpyAsync(h->rec.recs, block.data(), block.size(), hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
-    h->rec_fit = true;
-    h->rec_bytes = (int64_t)block.size();
-    h->rec_count = (int64_t)total;
-    h->rec_max = lay.most;
+    h->rec.fit = true;
+    h->rec.bytes = (int64_t)block.size();
+    h->rec.count = (int64_t)total;
+    h->rec.most = lay.most;
     return SLBM_OK;
 }
 
@@ -879,9 +888,9 @@ StepArgs<real> make_args2(const slbm_s* h, int src, int seg)
     a.seg = seg2_rows(seg);
     a.nstrips = (h->nx + kStrip2 - 1) / kStrip2;
     a.ntiles = a.nstrips * ((h->ny + a.seg - 1) / a.seg);
-    if (h->rec_fit && h->rec_seg == a.seg) {
-        a.rec_start = h->rec_start;
-        a.recs = (const TileRec<real>*)h->recs;
+    if (h->rec.fit && h->rec.seg == a.seg) {
+        a.rec_start = h->rec.start;
+        a.recs = (const TileRec<real>*)h->rec.recs;
     }
     return a;
 }
@@ -1075,7 +1084,8 @@ hipError_t dev_alloc(slbm_s* h, void** p, size_t n)
 // The plate's own device blocks (not the batch's divergence word or scratch).
 std::vector<void*> plate_blocks(slbm_s* h)
 {
-    std::vector<void*> v = {h->buf[0], h->buf[1], h->U, h->flags, h->bidx, h->links, h->groups, h->recs, h->recs4};
+    std::vector<void*> v = {h->buf[0], h->buf[1], h->U, h->flags, h->bidx, h->links, h->groups, h->rec.recs, h->recs4};
+    for (const TileLists& l : h->rec_kept) v.push_back(l.recs);
     if (!h->ext_flag) v.push_back(h->diverged);
     if (!h->batch) v.push_back(h->scratch);
     return v;
@@ -1092,10 +1102,9 @@ void free_all(slbm_s* h)
             (void)hipFree(p);
     }
     h->buf[0] = h->buf[1] = nullptr;
-    h->rec_start = nullptr;
-    h->recs = nullptr;
+    h->rec = TileLists{};
+    h->rec_kept.clear();
     h->recs4 = nullptr;
-    h->rec_fit = false;
     h->U = nullptr;
     h->scratch = nullptr;
     if (h->ready) (void)hipEventDestroy(h->ready);
@@ -1441,7 +1450,10 @@ int slbm_step(slbm_handle h, int64_t nsteps)
         int64_t i = 0;
         // once a graph holds steps of this plate, every call leaves the buffer
         // that as many single steps leave: the graph's replays begin from it
-        if (!h->recorded && nsteps > 0 && recording(h->stream)) h->recorded = true;
+        if (nsteps > 0 && recording(h->stream)) {
+            h->recorded = true;
+            h->rec.held = h->rec.recs != nullptr;
+        }
         if (h->four) {
             int64_t singles = 0;
             if (h->recorded)
@@ -1694,9 +1706,9 @@ int slbm_boundary_lists(slbm_handle h, int32_t* rows, int64_t* records, int32_t*
     return guarded([&]() -> int {
         if (!h) return fail(SLBM_E_INVAL, "null handle");
         const bool four = launch_is_default(h) && h->four;
-        if (rows) *rows = four ? (h->recs4 ? kRows4 : 0) : (h->rec_fit ? h->rec_seg : 0);
-        if (records) *records = four ? h->rec4_count : (h->rec_fit ? h->rec_count : 0);
-        if (max_per_tile) *max_per_tile = four ? h->rec4_max : (h->rec_fit ? h->rec_max : 0);
+        if (rows) *rows = four ? (h->recs4 ? kRows4 : 0) : (h->rec.fit ? h->rec.seg : 0);
+        if (records) *records = four ? h->rec4_count : (h->rec.fit ? h->rec.count : 0);
+        if (max_per_tile) *max_per_tile = four ? h->rec4_max : (h->rec.fit ? h->rec.most : 0);
         return SLBM_OK;
     });
 }
@@ -1819,7 +1831,8 @@ int slbm_device_bytes(slbm_handle h, int64_t* bytes)
         if (!h || !bytes) return fail(SLBM_E_INVAL, "null argument");
         int64_t b = 2 * (int64_t)9 * h->plane * (int64_t)h->esize + 2 * h->plane * 8 + h->plane * 5;
         b += (int64_t)h->n_links * (h->esize == 4 ? (int64_t)sizeof(LinkDev<float>) : (int64_t)sizeof(LinkDev<double>));
-        b += h->rec_bytes + h->rec4_bytes;
+        b += h->rec.bytes + h->rec4_bytes;
+        for (const TileLists& l : h->rec_kept) b += l.bytes;
         if (h->scratch) b += (int64_t)h->scratch_planes * h->plane * 8;
         *bytes = b;
         return SLBM_OK;

@@ -1,0 +1,72 @@
+"""Steps recorded into a graph, and the launch changed afterwards: the graph's
+replays still take the steps they were recorded with, whatever set_launch and
+the autotuner did to the plate's tile lists since, bit-equal to eager steps."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from slbm_workloads import geometry as G
+from test_gpu_parity import mixed_plate
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2208_04088_amd import slbm
+    slbm.lib()
+    return torch, slbm
+
+
+def record(torch, stream, call):
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+        call()
+    return g
+
+
+def replay(torch, stream, g):
+    with torch.cuda.stream(stream):
+        g.replay()
+    stream.synchronize()
+
+
+def plate(shape):
+    """Edges, a hole and a crack; no load that changes with time, which a graph
+    would repeat as recorded."""
+    p = mixed_plate(*shape, seed=4, order=1, periodic=False)
+    return dataclasses.replace(p, groups=[dataclasses.replace(g, profile=G.PROFILE_STEP) for g in p.groups])
+
+
+# a plate of two steps per launch from tile lists, and a small one of four
+@pytest.mark.parametrize("shape", [(300, 200), (70, 60)])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_lists_outlive_a_change_of_the_launch(env, shape, prec):
+    torch, slbm = env
+    p = plate(shape)
+    stream = torch.cuda.Stream()
+    with slbm.Solver(p, prec, stream=stream.cuda_stream) as a, slbm.Solver(p, prec, stream=stream.cuda_stream) as b:
+        b.set_launch(6, 62)
+        a.step(4)
+        b.step(4)
+        g = record(torch, stream, lambda: a.step(8))
+        changes = [lambda: a.set_launch(5, 58), a.autotune, lambda: a.set_launch(7, 58), lambda: a.set_launch(0, 0),
+                   lambda: a.set_launch(6, 62)]
+        for k, change in enumerate(changes):
+            change()
+            replay(torch, stream, g)
+            a.step(4)
+            replay(torch, stream, g)
+            b.step(20)
+            assert np.array_equal(a.displacement(), b.displacement()), k
+        # no more are kept than those recorded from, and they are taken up again
+        held = []
+        for _ in range(3):
+            for shape2 in ((5, 58), (7, 58), (0, 0)):
+                a.set_launch(*shape2)
+            held.append(a.device_bytes())
+        assert held[0] == held[1] == held[2]
+        del g
