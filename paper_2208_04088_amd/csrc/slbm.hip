@@ -1465,7 +1465,7 @@ int slbm_step(slbm_handle h, int64_t nsteps)
                 i += k;
             }
         } else if (launch_rows2(h)) {
-            const int64_t pairs = nsteps / 2 - (h->recorded && !h->two ? nsteps / 2 % 2 : 0);
+            const int64_t pairs = nsteps / 2 - (h->recorded ? nsteps / 2 % 2 : 0);
             for (; i < 2 * pairs; i += 2) {
                 int rc = h->precision == SLBM_FP32 ? launch_step2<float>(h) : launch_step2<double>(h);
                 if (rc) return rc;
