@@ -481,7 +481,7 @@ struct slbm_s {
     // the same for k_step4's tiles (build_four): whether the plate is one for
     // it and a call of steps takes it, its lists (null: no cut links)
     bool four_fit = false, four = false;
-    bool recorded = false;           // steps were recorded into a graph
+    bool recorded = false;           // steps or readouts were recorded into a graph
     void* recs4 = nullptr;
     int32_t* rec4_start = nullptr;
     int64_t rec4_bytes = 0, rec4_count = 0;
@@ -1041,10 +1041,13 @@ int launch_readout(slbm_s* h, const ReadoutDst<T>& d)
     return SLBM_OK;
 }
 
+bool recording(hipStream_t stream);
+
 template <typename T>
 int readout(slbm_s* h, double* u, T* rho, T* j, T* P, T* sigma)
 {
     const ReadoutDst<T> d{u, rho, j, P, sigma, h->rho_user, h->rho_user * h->s_v, h->s_sigma};
+    if (!h->recorded && recording(h->stream)) h->recorded = true;      // it reads the buffer of now (slbm_step)
     return h->precision == SLBM_FP32 ? launch_readout<float, T>(h, d) : launch_readout<double, T>(h, d);
 }
 
@@ -1448,8 +1451,8 @@ int slbm_step(slbm_handle h, int64_t nsteps)
         if (nsteps < 0) return fail(SLBM_E_INVAL, "negative step count");
         DeviceGuard dg(h->device);
         int64_t i = 0;
-        // once a graph holds steps of this plate, every call leaves the buffer
-        // that as many single steps leave: the graph's replays begin from it
+        // once a graph holds steps or readouts of this plate, every call leaves the
+        // buffer that as many single steps leave: the graph's replays begin from it
         if (nsteps > 0 && recording(h->stream)) {
             h->recorded = true;
             h->rec.held = h->rec.recs != nullptr;

@@ -98,3 +98,33 @@ def test_two_steps_per_launch_recorded(env, rows, n):
         b.step(5)
         assert np.array_equal(a.displacement(), b.displacement())
         del g
+
+
+# a readout alone in a graph reads the buffer of its recording: eager steps in
+# between leave the state there after every even number, as single steps do
+@pytest.mark.parametrize("shape,launch", [((300, 200), (0, 0)), ((70, 60), (0, 0)), ((300, 200), (6, 58))])
+@pytest.mark.parametrize("n", [2, 4, 6, 8, 10])
+def test_readouts_recorded(env, shape, launch, n):
+    torch, slbm = env
+    p = plate(shape)
+    stream = torch.cuda.Stream()
+    new = lambda k: torch.zeros((k, p.ny, p.nx), dtype=torch.float64, device="cuda")
+    u, v, rho, sig = new(2), new(2), new(1), new(3)
+    torch.cuda.synchronize()
+    with slbm.Solver(p, "fp64", stream=stream.cuda_stream) as a, slbm.Solver(p, "fp64", stream=stream.cuda_stream) as b:
+        b.set_launch(6, 62)
+        a.set_launch(*launch)
+        a.step(3)
+        b.step(3)
+        g = [record(torch, stream, lambda: a.displacement_device(u.data_ptr())),
+             record(torch, stream, lambda: a.displacement_device_noalloc(v.data_ptr())),
+             record(torch, stream, lambda: a.moments_device(rho=rho.data_ptr(), sigma=sig.data_ptr()))]
+        for k in range(2):
+            a.step(n)
+            b.step(n)
+            for one in g:
+                replay(torch, stream, one)
+            m = b.moments()
+            assert np.array_equal(u.cpu().numpy(), b.displacement()) and torch.equal(u, v), k
+            assert np.array_equal(rho.cpu().numpy()[0], m[0]) and np.array_equal(sig.cpu().numpy(), m[3]), k
+        del g, one
