@@ -879,6 +879,21 @@ TileOrder tile_order(int back, int grid, long long bytes)
     return {back, bytes <= cache ? 0 : (bytes <= 2 * cache ? grid / 2 : grid / 4)};
 }
 
+bool recording(hipStream_t stream);
+
+// The lists of the library's own launch of two steps, where they can be had:
+// while the stream records a graph nothing may be allocated, and a plate
+// without room for them takes the rules site by site.
+void default_lists(slbm_s* h)
+{
+    if (recording(h->stream)) return;
+    try {
+        if (tile_records(h, default_rows2(h)) == SLBM_OK) return;
+    } catch (const std::bad_alloc&) {
+    }
+    drop_tile_records(h);
+}
+
 // Arguments of the two-steps-per-launch kernel: 58-column strips, at most
 // kMaxTileRows2 rows per tile.
 template <typename real>
@@ -1405,7 +1420,7 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
     // room for them takes the rules site by site)
     if (!arena) {
         (void)(h->precision == SLBM_FP32 ? build_four<float>(h) : build_four<double>(h));
-        if (!h->four && tile_records(h, default_rows2(h)) != SLBM_OK) drop_tile_records(h);
+        if (!h->four) default_lists(h);
     }
     *out = h;
     return SLBM_OK;
@@ -1653,10 +1668,13 @@ int slbm_set_launch(slbm_handle h, int32_t seg_rows, int32_t strip)
             return fail(SLBM_E_INVAL, "strip must be 0, 58, 62 or 64");
         if (seg_rows > (strip == kStrip2 ? kMaxTileRows2 : kMaxTileRows))
             return fail(SLBM_E_INVAL, "rows per tile above the maximum (14; 10 with two steps per launch)");
-        if (strip == kStrip2 || (strip == 0 && seg_rows == 0 && !h->four_fit)) {
+        if (strip == kStrip2) {
             DeviceGuard dg(h->device);
-            const int rc = tile_records(h, strip == kStrip2 ? seg_rows : default_rows2(h));
+            const int rc = tile_records(h, seg_rows);
             if (rc) return rc;
+        } else if (strip == 0 && seg_rows == 0 && !h->four_fit) {
+            DeviceGuard dg(h->device);
+            default_lists(h);
         }
         h->seg = seg_rows;
         h->two = strip == kStrip2 ? 1 : 0;

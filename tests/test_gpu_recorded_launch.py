@@ -128,3 +128,29 @@ def test_readouts_recorded(env, shape, launch, n):
             assert np.array_equal(u.cpu().numpy(), b.displacement()) and torch.equal(u, v), k
             assert np.array_equal(rho.cpu().numpy()[0], m[0]) and np.array_equal(sig.cpu().numpy(), m[3]), k
         del g, one
+
+
+def test_back_to_the_librarys_launch_while_recording(env):
+    """set_launch(0, 0) needs no device work of its own: it may be called
+    between recorded steps."""
+    torch, slbm = env
+    p = plate((300, 200))
+    stream = torch.cuda.Stream()
+    with slbm.Solver(p, "fp32", stream=stream.cuda_stream) as a, slbm.Solver(p, "fp32", stream=stream.cuda_stream) as b:
+        b.set_launch(6, 62)
+        a.set_launch(10, 58)
+        a.step(3)
+        b.step(3)
+
+        def call():
+            a.set_launch(0, 0)
+            a.step(4)
+
+        g = record(torch, stream, call)
+        for _ in range(2):
+            replay(torch, stream, g)
+            b.step(4)
+        a.step(5)
+        b.step(5)
+        assert np.array_equal(a.displacement(), b.displacement())
+        del g
