@@ -786,6 +786,8 @@ int build_tile_records(slbm_s* h, int seg)
     std::memcpy(block.data() + rb, lay.start.data(), sb);
     const hipError_t e = dev_alloc(h, &h->rec.recs, block.size());
     if (e != hipSuccess) {
+        (void)hipGetLastError();                           // not the next launch's error
+        h->rec.recs = nullptr;
         drop_tile_records(h);
         h->rec.seg = seg;
         // a batch plate without room in the budget goes without lists
