@@ -922,10 +922,10 @@ void dispatch_step2_w(const slbm_s* h, const StepArgs<real>& a, const TileOrder&
 }
 
 template <typename real>
-void dispatch_step2(const slbm_s* h, const StepArgs<real>& a)
+void dispatch_step2(const slbm_s* h, const StepArgs<real>& a, int back)
 {
     const int grid = grid_for(a);
-    const TileOrder order = tile_order(h->cur, grid, state_bytes<real>(h->plane));
+    const TileOrder order = tile_order(back, grid, state_bytes<real>(h->plane));
     const dim3 blk(64 * (a.seg + 6));
     constexpr int lo = k2_waves<real>(1), hi = k2_waves<real>(kMaxTileRows2);
     const bool per = h->px || h->py;
@@ -972,11 +972,11 @@ int launch_step4(slbm_s* h, int steps, bool commit)
 
 // Two steps in one launch, not committed (autotuner trials; see launch_step_raw).
 template <typename real>
-int launch_step2_raw(slbm_s* h, int seg)
+int launch_step2_raw(slbm_s* h, int seg, int back)
 {
     StepArgs<real> a = make_args2<real>(h, h->cur, seg);
     a.local = 0;
-    dispatch_step2<real>(h, a);
+    dispatch_step2<real>(h, a, back);
     HIP_TRY(hipGetLastError());
     return SLBM_OK;
 }
@@ -985,7 +985,7 @@ template <typename real>
 int launch_step2(slbm_s* h)
 {
     StepArgs<real> a = make_args2<real>(h, h->cur, launch_rows2(h));
-    dispatch_step2<real>(h, a);
+    dispatch_step2<real>(h, a, h->cur);
     HIP_TRY(hipGetLastError());
     h->cur ^= 1;
     h->local = false;
@@ -1768,8 +1768,10 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
         HIP_TRY(hipEventCreate(&e1));
         // time per step of a shape (wv: 0 narrow, 1 wide, 2 two steps per
         // launch, 4 four) with the current XCD map: the best of two bursts of
-        // back-to-back launches after a warm one, as steps run; each launch
-        // rereads the same state, and U is put back after every burst
+        // back-to-back launches after a warm one, two-step launches in alternating
+        // directions as they run (tile_order); each launch rereads the same state,
+        // and U is put back after every burst
+        int launches = 0;
         auto time_shape = [&](int c, int wv, double& us) -> int {
             const int burst = wv >= 2 ? 3 : 6, per = wv == 4 ? kSteps4 : (wv == 2 ? 2 : 1);
             if (wv == 2) {
@@ -1784,7 +1786,8 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
                         ? (h->precision == SLBM_FP32 ? launch_step4<float>(h, kSteps4, false)
                                                      : launch_step4<double>(h, kSteps4, false))
                         : wv == 2
-                        ? (h->precision == SLBM_FP32 ? launch_step2_raw<float>(h, c) : launch_step2_raw<double>(h, c))
+                        ? (h->precision == SLBM_FP32 ? launch_step2_raw<float>(h, c, launches++ & 1)
+                                                     : launch_step2_raw<double>(h, c, launches++ & 1))
                         : (h->precision == SLBM_FP32 ? launch_step_raw<float>(h, c, wv) : launch_step_raw<double>(h, c, wv));
                     if (rc2) return rc2;
                 }
