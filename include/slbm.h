@@ -210,7 +210,7 @@ int slbm_time(slbm_handle h, int64_t* step, double* t_user);
 int slbm_set_launch(slbm_handle h, int32_t seg_rows, int32_t strip);
 
 /* The per-tile cut-link lists of the two-steps-per-launch step (strip 58; on a
- * small plate whose launch is left to the library, of its four-step tiles):
+ * small plate that takes up to four steps per launch, of its four-step tiles):
  * the rows per tile they were built for (0: none, and the step evaluates the
  * boundary rules of section 4 site by site), the records in all lists, and
  * the most in one tile.  Lists are kept only when every tile's fits the
@@ -259,8 +259,9 @@ int slbm_get_launch(slbm_handle h, int32_t* seg_rows, int32_t* strip, int32_t* x
  * least 1 % faster (else bands).  Reports the shape and its time per step in
  * microseconds (any pointer may be NULL); slbm_get_launch gives the XCD
  * group.  On a small plate (slbm_set_launch) it also times up to four steps per
- * launch, which slbm_step then takes if they are faster than that shape; the
- * time reported is theirs.  Synchronises.  The state and step count are unchanged. */
+ * launch, which slbm_step then takes if they are faster than that shape (any
+ * call of slbm_set_launch ends that; with rows 0 and strip 0 they are taken
+ * again).  Synchronises.  The state and step count are unchanged. */
 int slbm_autotune(slbm_handle h, int32_t* seg_rows, int32_t* strip, double* us_per_step);
 
 /* Checkpoint of the full state of the time stepping of section 3 (the

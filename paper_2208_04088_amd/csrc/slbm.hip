@@ -1728,7 +1728,7 @@ int slbm_boundary_lists(slbm_handle h, int32_t* rows, int64_t* records, int32_t*
 {
     return guarded([&]() -> int {
         if (!h) return fail(SLBM_E_INVAL, "null handle");
-        const bool four = launch_is_default(h) && h->four;
+        const bool four = h->four;
         if (rows) *rows = four ? (h->recs4 ? kRows4 : 0) : (h->rec.fit ? h->rec.seg : 0);
         if (records) *records = four ? h->rec4_count : (h->rec.fit ? h->rec.count : 0);
         if (max_per_tile) *max_per_tile = four ? h->rec4_max : (h->rec.fit ? h->rec.most : 0);
@@ -1828,19 +1828,17 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
             best_us = us;
         else
             h->group = 0;
-        // four steps per launch, where the plate is one for it
-        h->four = false;
-        if (h->four_fit) {
-            if ((rc = time_shape(kRows4, 4, us))) { h->group = keep_group; return rc; }
-            h->four = us < best_us;
-            best_us = std::min(us, best_us);
-        }
+        // four steps per launch, where the plate is one for it, taken if they are
+        // faster than the best shape, which is set and reported with its own time
+        if (h->four_fit && (rc = time_shape(kRows4, 4, us))) { h->group = keep_group; return rc; }
+        const bool four = h->four_fit && us < best_us;
         HIP_TRY(hipMemcpyAsync(h->diverged, flag_saved, sizeof(unsigned int), hipMemcpyDeviceToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         release_transient_scratch(h);
         if (best_w == 2 && (rc = tile_records(h, best))) return rc;
+        h->four = four;
         h->seg = best;
         h->two = best_w == 2 ? 1 : 0;
         h->wide = best_w == 2 ? -1 : best_w;
