@@ -261,7 +261,8 @@ int slbm_get_launch(slbm_handle h, int32_t* seg_rows, int32_t* strip, int32_t* x
  * group.  On a small plate (slbm_set_launch) it also times up to four steps per
  * launch, which slbm_step then takes if they are faster than that shape (any
  * call of slbm_set_launch ends that; with rows 0 and strip 0 they are taken
- * again).  Synchronises.  The state and step count are unchanged. */
+ * again).  Synchronises.  The state and step count are unchanged; after an
+ * error the launch is too. */
 int slbm_autotune(slbm_handle h, int32_t* seg_rows, int32_t* strip, double* us_per_step);
 
 /* Checkpoint of the full state of the time stepping of section 3 (the

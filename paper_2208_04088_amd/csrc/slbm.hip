@@ -1802,6 +1802,22 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
             return SLBM_OK;
         };
         const int keep_group = h->group;
+        // after a failed trial the plate is as it was: state, launch and lists
+        auto undo = [&](int failed) -> int {
+            const std::string why = g_err;
+            h->group = keep_group;
+            (void)hipMemcpyAsync(h->U, saved, ub, hipMemcpyDeviceToDevice, h->stream);
+            (void)hipMemcpyAsync(h->diverged, flag_saved, sizeof(unsigned int), hipMemcpyDeviceToDevice, h->stream);
+            (void)hipStreamSynchronize(h->stream);
+            (void)hipEventDestroy(e0);
+            (void)hipEventDestroy(e1);
+            if (h->two)
+                (void)tile_records(h, h->seg);
+            else if (launch_is_default(h) && !h->four_fit)
+                default_lists(h);
+            g_err = why;
+            return failed;
+        };
         h->group = 0;
         const int cand[] = {2, 3, 4, 6, 8, 10, 12, 14};
         int best = 0, best_w = 0;
@@ -1810,34 +1826,34 @@ int slbm_autotune(slbm_handle h, int32_t* seg_out, int32_t* strip_out, double* u
         for (int c : cand) {
             if (c > (wv ? max_tile_rows<true>() : max_tile_rows<false>())) break;
             if (c > std::max(2, h->ny)) break;
-            if ((rc = time_shape(c, wv, us))) { h->group = keep_group; return rc; }
+            if ((rc = time_shape(c, wv, us))) return undo(rc);
             if (us < best_us) { best_us = us; best = c; best_w = wv; }
         }
         // two steps per launch
         const int cand2[] = {2, 3, 4, 5, 6, 7, 8, 9, 10};
         for (int c : cand2) {
             if (c > std::max(2, h->ny)) break;
-            if ((rc = time_shape(c, 2, us))) { h->group = keep_group; return rc; }
+            if ((rc = time_shape(c, 2, us))) return undo(rc);
             if (us < best_us) { best_us = us; best = c; best_w = 2; }
         }
         // the best shape with interleaved XCD groups of 8, kept when at least
         // 1 % faster (plates whose boundary tiles cluster)
         h->group = 8;
-        if ((rc = time_shape(best, best_w, us))) { h->group = keep_group; return rc; }
+        if ((rc = time_shape(best, best_w, us))) return undo(rc);
         if (us < 0.99 * best_us)
             best_us = us;
         else
             h->group = 0;
         // four steps per launch, where the plate is one for it, taken if they are
         // faster than the best shape, which is set and reported with its own time
-        if (h->four_fit && (rc = time_shape(kRows4, 4, us))) { h->group = keep_group; return rc; }
+        if (h->four_fit && (rc = time_shape(kRows4, 4, us))) return undo(rc);
         const bool four = h->four_fit && us < best_us;
+        if (best_w == 2 && (rc = tile_records(h, best))) return undo(rc);
         HIP_TRY(hipMemcpyAsync(h->diverged, flag_saved, sizeof(unsigned int), hipMemcpyDeviceToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         release_transient_scratch(h);
-        if (best_w == 2 && (rc = tile_records(h, best))) return rc;
         h->four = four;
         h->seg = best;
         h->two = best_w == 2 ? 1 : 0;

@@ -81,3 +81,29 @@ def test_no_room_for_the_tile_lists():
         assert np.array_equal(s.displacement(), want)
         s.set_launch(0, 0)
         assert s.boundary_lists()[0] == 10
+
+
+def test_no_room_to_autotune():
+    """The trials' larger lists are refused: the error leaves the launch, its
+    lists and the state as they were."""
+    import torch
+    assert torch.cuda.is_available()
+    from paper_2208_04088_amd import slbm
+    p = pinholes(1600)
+    with slbm.Solver(p, "fp64") as s, slbm.Solver(p, "fp64") as ref:
+        ref.set_launch(6, 62)
+        s.step(3)
+        s.autotune()                               # its scratch is there
+        s.set_launch(0, 0)
+        lists = s.boundary_lists()
+        assert lists[0] == 10
+        held = fill(torch, BLOCK)
+        with pytest.raises(slbm.SlbmError) as e:
+            s.autotune()
+        assert e.value.code == -2, e.value
+        assert s.boundary_lists() == lists and s.launch()[:2] == (0, 0)
+        held.clear()
+        torch.cuda.empty_cache()
+        s.step(4)
+        ref.step(7)
+        assert np.array_equal(s.displacement(), ref.displacement())
