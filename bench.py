@@ -189,8 +189,40 @@ def has_ext_links3(box):
     return any(box.groups[g].kind == NEUMANN for g in set(box.links["group"].tolist()))
 
 
-def measured_traffic3(box, prec):
-    """Calibrated counter bytes per step of the 3-D kernels
+def recorded_kernels(lib, stream, call):
+    """Kernels that `call` queues on the HIP stream `stream` (an address): it is
+    recorded, not run, so the handle that it steps is of no use afterwards."""
+    import ctypes as C
+    graph, n = C.c_void_p(), C.c_size_t()
+
+    def check(rc):
+        if rc != 0:
+            raise RuntimeError(f"HIP error {rc} while recording")
+
+    check(lib.hipStreamBeginCapture(C.c_void_p(stream), C.c_int(1)))         # 1: this thread's calls alone
+    try:
+        call()
+    finally:
+        check(lib.hipStreamEndCapture(C.c_void_p(stream), C.byref(graph)))
+    check(lib.hipGraphGetNodes(graph, None, C.byref(n)))
+    check(lib.hipGraphDestroy(graph))
+    return n.value
+
+
+def kernels3(s, stream, box):
+    """Names of the kernels of one step of the box `s` (which ends here): one
+    more recorded step is that many more launches."""
+    from paper_2208_04088_amd import slbm3
+    many, few = (recorded_kernels(slbm3.lib(), stream, lambda: s.step(k)) for k in (6, 4))
+    per = (many - few) // 2
+    ext = ("k3_links_ext",) if has_ext_links3(box) else ()
+    names = ext + (("k3_march",) if per - len(ext) == 1 else ("k3_density", "k3_step"))
+    assert len(names) == per, (names, per)
+    return names
+
+
+def measured_traffic3(box, prec, kernels):
+    """Calibrated counter bytes per step of the 3-D kernels named
     (profiles/traffic_<box>_<precision>.json), or None when there is none or
     the kernels changed since."""
     path = os.path.join(ROOT, "profiles", f"traffic_{box.name}_{prec}.json")
@@ -202,8 +234,6 @@ def measured_traffic3(box, prec):
     if d.get("kernel_fingerprint") != kernel_fingerprint("step3_kernel.h"):
         return None
     shapes = d.get("shapes", {})
-    kernels = ("k3_links_ext",) if has_ext_links3(box) else ()
-    kernels += ("k3_march",)
     parts = [shapes.get(k) for k in kernels]
     return None if None in parts else sum(p["traffic_bytes_per_launch"] for p in parts)
 
@@ -268,6 +298,7 @@ def time_box3(torch, stream, box, prec, steps, warm):
     except slbm3.S.SlbmError:
         diverged = True
     assert diverged or np.isfinite(s.displacement()).all()
+    kernels = kernels3(s, stream.cuda_stream, box)
     sites = box.n_material
     bps = bytes_per_site3(prec)
     step_bytes = bytes_per_step3(box, prec)
@@ -281,14 +312,14 @@ def time_box3(torch, stream, box, prec, steps, warm):
                    "material_sites": sites,
                    "precision": "fp32 populations and arithmetic, fp64 displacement" if prec == "fp32" else "fp64",
                    "lambda_over_mu": box.lam / box.mu, "tau": box.tau,
-                   "bench_step": "one D3Q19 time step of the whole box (density and step in one launch; "
+                   "bench_step": "one D3Q19 time step of the whole box (density and step; "
                                  "with cut links the step also forms the next step's rule values)",
                    "diverged": diverged, "wall_s": round(wall, 4)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic3(box, prec),
-                     "kernel": ("k3_links_ext + " if has_ext_links3(box) else "") + "k3_march",
+                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic3(box, prec, kernels),
+                     "kernel": " + ".join(kernels),
                      "bytes_per_site": bps, "bytes_per_step": step_bytes,
-                     "launches_per_step": 2 if has_ext_links3(box) else 1,
+                     "launches_per_step": len(kernels),
                      "avg_step_us": round(t_step * 1e6, 3),
                      "note": "achieved counts the step's algorithmic bytes over the time of all its launches "
                              "(traffic: measured bytes per step)"},
@@ -303,7 +334,7 @@ def run_3d(args, torch, dev, stream, n, kind="cube"):
     traction, periodic in y and z; kind "cavities", a porous solid periodic on
     every axis with (n/64)^3 pressurised spherical cavities (cut links of
     every q and normal).  fp32 populations, fp64 displacement, from rest.  One
-    bench step is one time step of the whole box (one launch); the rate counts
+    bench step is one time step of the whole box; the rate counts
     material sites."""
     from paper_2208_04088_amd import slbm
     steps = args.steps if args.steps_given else 1000
