@@ -4,6 +4,12 @@
 #include "slbm3.h"
 #include "step3_kernel.h"
 
+// How k3_march goes through a box and whether it takes its steps (march_of).
+struct March3 {
+    bool on = false;
+    int rows = 1, nch = 1, nyt = 1, depth = 1, mtiles = 1, slots = 256;
+};
+
 struct slbm3_s {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -51,19 +57,18 @@ struct slbm3_s {
     uint64_t geo_hash = 0;           // the geometry a checkpoint must match (mask and cut links, or the walls)
     int64_t n_links = 0;
     size_t link_bytes = 0;
+    March3 march;
 };
 
 namespace {
 
 using namespace slbm3_dev;
 
-bool march_box(const slbm3_s* h);
-
 // Which of the two lists of rule values belongs to the current state: with
 // k3_march the one of the state's buffer, so that a state is one place whatever
 // led there (a step from local populations, which reads none, writes in place
 // what the next step reads); without it the first.
-int lval_at(const slbm3_s* h) { return march_box(h) ? h->cur ^ (h->local ? 1 : 0) : 0; }
+int lval_at(const slbm3_s* h) { return h->march.on ? h->cur ^ (h->local ? 1 : 0) : 0; }
 
 template <typename real>
 Step3Args<real> make_args3(const slbm3_s* h, int src)
@@ -493,38 +498,6 @@ int launch3(slbm3_s* h, int what)
 
 int launch3_any(slbm3_s* h, int what);
 
-// Whether k3_march takes the next step.  Not a state that is read in place
-// (the first step after creation or initial fields), not a mask without cut
-// links, not walls whose Neumann data are extrapolated (they read a second
-// site) or that share one site.  And only boxes large enough: below, a workgroup's few planes in
-// series (2.6 us each in single, 5 us in double precision) take longer than
-// the two launches, whose every load is independent.  us per step, two
-// launches and one:
-//   fp32 slab  64^3 19 24   200x60x40 30 34   90x130x70 48 44   96^3 52 43   128^3 123 99   256^3 897 686
-//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 37 40   96^3 39 35   128^3 110 94   256^3 897 672
-//   fp64 slab  40^3 17 20   64^3 32 25        90x130x70 87 90   96^3 106 77  128^3 228 175
-//   fp64 per.  40^3 13 16   64^3 24 22        90x130x70 73 87   96^3 91 75   128^3 205 169   256^3 1669 1230
-// With cut links the series is longer (6 us a plane), and a row whose last
-// chunk is short pays for all of it (porous solids, n^3):
-//   fp32  100 55 84   120 108 99   128 122 104   130 151 163   150 225 249   160 241 235   180 374 361   256 964 752
-//   fp64  100 125 134  128 226 219  130 280 294  150 404 420   180 648 563   256 1777 1547
-bool march_box(const slbm3_s* h)
-{
-    if (h->geo) {
-        // a chunk's 64 lanes: how many of 16 hold sites
-        const long long lanes = 16LL * h->nx / (64 * ((h->nx + 63) / 64));
-        if (h->n_links == 0) return false;
-        return h->precision == SLBM_FP32 ? h->plane >= 4000000 || (h->plane >= 1500000 && lanes >= 14) : h->plane >= 2000000;
-    }
-    if (!h->px) {
-        if (h->nx < 2) return false;
-        for (int s = 0; s < 2; ++s)
-            if (h->norder == 1 && h->wkind[s] == SLBM_NEUMANN) return false;
-    }
-    return h->plane >= (h->px ? 850000 : (h->precision == SLBM_FP32 ? 800000 : 250000));
-}
-bool march3(const slbm3_s* h) { return !h->local && march_box(h); }
-
 // Planes a k3_march workgroup marches through, for `tiles` tiles of rows over
 // nz planes: a workgroup takes depth + 2 planes' time and a little to start,
 // and the chip runs `slots` of them at once, so the depth that needs the
@@ -542,15 +515,76 @@ int march_depth(long long tiles, int nz, int slots)
     return best;
 }
 
+// How k3_march goes through the box, and whether it takes its steps (but for
+// the first one from a state that is read in place: after creation or initial
+// fields).  Formed once, at creation.
+//
+// Not a mask without cut links, not walls whose Neumann data are extrapolated
+// (they read a second site) or that share one site.  And only boxes large
+// enough: below, a workgroup's few planes in series (2.6 us each in single, 5 us
+// in double precision) take longer than the two launches, whose every load is
+// independent.  us per step, two launches and one:
+//   fp32 slab  64^3 19 24   200x60x40 30 34   90x130x70 47 43   96^3 52 43   128^3 123 99   256^3 897 686
+//   fp32 per.  64^3 15 21   200x60x40 24 28   90x130x70 37 40   96^3 39 35   128^3 110 94   256^3 897 672
+//   fp64 slab  40^3 17 20   64^3 32 25        90x130x70 87 90   96^3 106 77  128^3 228 175
+//   fp64 per.  40^3 13 16   64^3 24 22        90x130x70 73 87   96^3 91 75   128^3 205 169   256^3 1669 1230
+// Nor boxes so thin that most of what the workgroups go through is halo, or most
+// of the chip waits in the last round of them: `useful` is the share of the row
+// planes of whole rounds that are stepped.  useful, two launches and one:
+//   fp32 slab  1024x1x1024 .31 48 80   1024x1024x1 .27 47 68   3000x17x17 .33 41 48   400x9x240 .33 43 52
+//              2048x2048x2 .40 449 471   1024x200x4 .42 40 38   1024x512x3 .48 75 77   1024x1024x4 .53 233 217
+//   fp64 slab  1024x1024x2 .36 212 235   1024x200x4 .35 72 84   1024x64x4 .33 26 28   3000x17x17 .41 80 85
+//              128x64x32 .40 29 24   500x30x17 .40 27 24   1024x1024x3 .45 317 316   1024x1024x4 .48 435 399
+// and two rows between walls (512x2x512 fp64 45 51, 700x2x700 97 106; periodic 41 33, 94 77).
+//
+// With cut links the series is longer (6 us a plane), and a row whose last
+// chunk is short pays for all of it (porous solids, n^3; `lanes` is the share of
+// the chunks' lanes that hold sites):
+//   fp32  100 54 76   120 107 99   128 123 103   130 151 160   140 186 195   150 222 246   160 241 234   170 318 329
+//         180 374 364   200 527 507   256 967 752
+//   fp64  100 123 132  120 194 181  128 226 220  130 277 276  136 307 324  140 332 349  144 349 339  150 405 399
+//         160 452 447  170 563 545  180 650 565  200 937 847  256 1778 1538
+// Fewer than four rows or planes leave its workgroups, one to a compute unit, too
+// few waves (a hole along the short axis): fp32 1024x2x1024 108 189, x3 162 209,
+// x4 223 229, x5 278 276, 1024x1024x3 163 184, x4 226 232, x6 335 313.
+March3 march_of(const slbm3_s* h)
+{
+    March3 m;
+    const bool single = h->precision == SLBM_FP32;
+    m.rows = std::min(kMarchWaves((int)h->esize) - 2, h->ny);
+    m.nch = (h->nx + 63) / 64;
+    m.nyt = (h->ny + m.rows - 1) / m.rows;
+    m.slots = single && !h->geo ? 512 : 256;
+    m.depth = march_depth((long long)m.nch * m.nyt, h->nz, m.slots);
+    m.mtiles = m.nch * m.nyt * ((h->nz + m.depth - 1) / m.depth);
+    const double rounds = (m.mtiles + m.slots - 1) / m.slots;
+    const double useful = (double)m.nch * h->ny * h->nz / (rounds * m.slots * (m.rows + 2) * (m.depth + 2));
+    if (useful < 0.39) return m;
+    if (h->geo) {
+        const double lanes = h->nx / (64.0 * m.nch);
+        if (h->n_links == 0 || h->ny < 4 || h->nz < 4) return m;
+        m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000));
+    } else if (h->px) {
+        m.on = h->plane >= 850000;
+    } else {
+        if (h->nx < 2 || h->ny < 3) return m;
+        for (int s = 0; s < 2; ++s)
+            if (h->norder == 1 && h->wkind[s] == SLBM_NEUMANN) return m;
+        m.on = h->plane >= (single ? 800000 : 250000);
+    }
+    return m;
+}
+bool march3(const slbm3_s* h) { return h->march.on && !h->local; }
+
 template <typename real, bool PX, bool GEO>
 int launch3_march(slbm3_s* h)
 {
     Step3Args<real> a = make_args3<real>(h, h->cur);
-    a.rows = std::min(kMarchWaves(sizeof(real)) - 2, h->ny);
-    a.nch = (h->nx + 63) / 64;
-    a.nyt = (h->ny + a.rows - 1) / a.rows;
-    a.depth = march_depth((long long)a.nch * a.nyt, h->nz, sizeof(real) == 4 && !GEO ? 512 : 256);
-    a.mtiles = a.nch * a.nyt * ((h->nz + a.depth - 1) / a.depth);
+    a.rows = h->march.rows;
+    a.nch = h->march.nch;
+    a.nyt = h->march.nyt;
+    a.depth = h->march.depth;
+    a.mtiles = h->march.mtiles;
     a.xgroup = 16;
     if (GEO && h->n_ext > 0)
         hipLaunchKernelGGL((k3_links_ext<real>), dim3((unsigned)((h->n_ext + 255) / 256)), dim3(256), 0, h->stream, a,
@@ -722,6 +756,7 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
             h->n_links = (int64_t)geo.recs.size();
             h->n_ext = (int64_t)geo.elink.size();
         }
+        h->march = march_of(h);
         DeviceGuard dg(h->device);
     #define TRY_OR_BAIL(expr)                                \
         do {                                                 \

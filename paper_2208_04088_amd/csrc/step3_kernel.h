@@ -16,7 +16,7 @@
 // SoA planes g[i][z][y][x], site offset (z ny + y) nx + x; consecutive planes
 // are `stride` elements apart, a little more than a plane, so that the 19
 // streams of a pull do not all start on the same HBM channel.  A step of a
-// large box is one launch, k3_march (march3 has the rule); of a small one two:
+// large box is one launch, k3_march (march_of has the rule); of a small one two:
 // k3_density (delta-rho of the pulled state, needed by the gradient stencil of
 // every neighbour) and k3_step (pull with the rules, moments, source term,
 // collision, U, store; with a general geometry also the next step's rule
