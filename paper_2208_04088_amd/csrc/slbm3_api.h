@@ -515,6 +515,45 @@ int march_depth(long long tiles, int nz, int slots)
     return best;
 }
 
+// Whether the cut links leave k3_march's workgroups about equally long.  A wave
+// takes a plane's links of its row 64 at a time, and the waves of the other rows
+// wait for it: 0.15 of a plane's time each.  A plane face along z puts 320 links
+// into one row of a tile, plane after plane, and the launch lasts as long as
+// those tiles.  The launch's time by that over its time with equal rows; us per
+// step, two launches and one (blocks of material in void):
+//   fp32  1024x8x1024 1.51 577 687   512x34x256 1.57 277 402   128x128x256 1.50 258 317   192^3 1.57 423 454
+//         256^3 1.57 1014 1228   1024x66x512 1.22 1987 2000
+//   fp64  1024x8x1024 1.57 1065 1748   128x128x256 1.58 483 650   192^3 1.37 784 866   256^3 1.26 1886 1945
+//         1024x66x512 1.18 3721 3445
+// (porous solids of every density and round holes: up to 1.16, one launch faster).
+bool even_links3(const slbm3_s* h, const Geo3& g, const March3& m)
+{
+    const int nseg = (h->nz + m.depth - 1) / m.depth;
+    double sum = 0, base = 0, most = 0;
+    for (int seg = 0; seg < nseg; ++seg)
+        for (int yt = 0; yt < m.nyt; ++yt)
+            for (int ch = 0; ch < m.nch; ++ch) {
+                const int z1 = std::min(h->nz, (seg + 1) * m.depth), y1 = std::min(h->ny, (yt + 1) * m.rows);
+                double wait = 0;
+                for (int z = seg * m.depth; z < z1; ++z) {
+                    int longest = 1, all = 0;
+                    for (int y = yt * m.rows; y < y1; ++y) {
+                        const size_t t = ((size_t)z * h->ny + y) * m.nch + ch;
+                        const int n = (g.rowrec[t + 1] - g.rowrec[t] + 63) / 64;
+                        longest = std::max(longest, n);
+                        all += n;
+                    }
+                    wait += longest - std::max(1.0, (double)all / m.rows);
+                }
+                const double planes = z1 - seg * m.depth + 3;
+                sum += planes + 0.15 * wait;
+                base += planes;
+                most = std::max(most, planes + 0.15 * wait);
+            }
+    const double mean = sum / m.mtiles, rounds = std::max(1.0, (double)m.mtiles / m.slots);
+    return rounds * mean + std::min(2.0, rounds) * (most - mean) <= 1.25 * rounds * base / m.mtiles;
+}
+
 // How k3_march goes through the box, and whether it takes its steps (but for
 // the first one from a state that is read in place: after creation or initial
 // fields).  Formed once, at creation.
@@ -547,7 +586,7 @@ int march_depth(long long tiles, int nz, int slots)
 // Fewer than four rows or planes leave its workgroups, one to a compute unit, too
 // few waves (a hole along the short axis): fp32 1024x2x1024 108 189, x3 162 209,
 // x4 223 229, x5 278 276, 1024x1024x3 163 184, x4 226 232, x6 335 313.
-March3 march_of(const slbm3_s* h)
+March3 march_of(const slbm3_s* h, const Geo3& g)
 {
     March3 m;
     const bool single = h->precision == SLBM_FP32;
@@ -563,7 +602,8 @@ March3 march_of(const slbm3_s* h)
     if (h->geo) {
         const double lanes = h->nx / (64.0 * m.nch);
         if (h->n_links == 0 || h->ny < 4 || h->nz < 4) return m;
-        m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000));
+        m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000)) &&
+               even_links3(h, g, m);
     } else if (h->px) {
         m.on = h->plane >= 850000;
     } else {
@@ -756,7 +796,7 @@ int slbm3_create(const slbm3_params* p, slbm3_handle* out)
             h->n_links = (int64_t)geo.recs.size();
             h->n_ext = (int64_t)geo.elink.size();
         }
-        h->march = march_of(h);
+        h->march = march_of(h, geo);
         DeviceGuard dg(h->device);
     #define TRY_OR_BAIL(expr)                                \
         do {                                                 \

@@ -42,6 +42,10 @@ def periodic(*d):
     return B.periodic_box3(*d, lam=0.04, force=(1e-7, 2e-7, 0))
 
 
+def block(nx, ny, nz):
+    return B.block_box3(nx, ny, nz, (1, 1, 1), (nx - 2, ny - 2, nz - 2), [0] * 6, PRESSED, lam=0.05, mu=0.05, tau=0.7)
+
+
 def cavity(*d):
     r = 0.3 * min(d)
     return B.sphere_box3(*d, [B.Sphere3(d[0] / 2 - 0.4, d[1] / 2 - 0.3, d[2] / 2 - 0.6, r, 0)], PRESSED, lam=0.05, mu=0.05,
@@ -61,6 +65,7 @@ def crack(nx, ny, nz):
     (periodic, (1024, 1024, 1), 2, 2), (slab, (1024, 1024, 2), 1, 2), (slab, (1024, 1024, 4), 1, 1),
     (slab, (400, 9, 240), 2, 1), (slab, (400, 8, 270), 1, 1),
     (cavity, (128, 128, 128), 1, 1), (cavity, (160, 160, 160), 1, 1), (crack, (1024, 1024, 3), 2, 2), (crack, (1024, 1024, 6), 1, 1),
+    (block, (1024, 8, 512), 2, 2), (block, (512, 34, 256), 2, 2), (block, (160, 160, 160), 2, 2),
 ])
 def test_launches_of_a_step(env, make, d, single, double):
     box = make(*d)
