@@ -602,7 +602,7 @@ March3 march_of(const slbm3_s* h, const Geo3& g)
     if (h->geo) {
         const double lanes = h->nx / (64.0 * m.nch);
         if (h->n_links == 0 || h->ny < 4 || h->nz < 4) return m;
-        m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000)) &&
+        m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000 && lanes >= 0.75)) &&
                even_links3(h, g, m);
     } else if (h->px) {
         m.on = h->plane >= 850000;

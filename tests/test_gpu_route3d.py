@@ -64,7 +64,8 @@ def crack(nx, ny, nz):
     (periodic, (700, 2, 700), 1, 1), (slab, (400, 3, 800), 1, 1), (slab, (1024, 1024, 1), 2, 2),
     (periodic, (1024, 1024, 1), 2, 2), (slab, (1024, 1024, 2), 1, 2), (slab, (1024, 1024, 4), 1, 1),
     (slab, (400, 9, 240), 2, 1), (slab, (400, 8, 270), 1, 1),
-    (cavity, (128, 128, 128), 1, 1), (cavity, (160, 160, 160), 1, 1), (crack, (1024, 1024, 3), 2, 2), (crack, (1024, 1024, 6), 1, 1),
+    (cavity, (128, 128, 128), 1, 1), (cavity, (136, 136, 136), 2, 2), (cavity, (144, 144, 144), 2, 1),
+    (cavity, (160, 160, 160), 1, 1), (crack, (1024, 1024, 3), 2, 2), (crack, (1024, 1024, 6), 1, 1),
     (block, (1024, 8, 512), 2, 2), (block, (512, 34, 256), 2, 2), (block, (160, 160, 160), 2, 2),
 ])
 def test_launches_of_a_step(env, make, d, single, double):
