@@ -200,8 +200,10 @@ int slbm_time(slbm_handle h, int64_t* step, double* t_user);
  * tile, 58 output columns; an odd step count ends with one single step).
  * seg_rows is at most 14 (10 with strip 58); 0 keeps the library's choice.
  * seg_rows 0 with strip 0, the state after slbm_create, leaves the whole
- * launch to the library: two steps per launch, rows by the plate's size, and up
- * to four per launch on a small plate (at most 256 tiles of 50 columns, 2 rows).
+ * launch to the library: two steps per launch, rows by the plate's size, up to
+ * four per launch on a small plate (at most 256 tiles of 50 columns, 2 rows), and
+ * one where the lists below cannot be had, or the plate has no cut links, and
+ * two would take longer.
  * For two steps per launch the library also lists, per tile, the plate's cut links in
  * the tile's reach (slbm_boundary_lists), so that the tile evaluates the
  * section 4 rules of all of them together; it allocates device memory for

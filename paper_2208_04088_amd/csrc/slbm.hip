@@ -595,21 +595,53 @@ hipError_t dev_alloc(slbm_s* h, void** p, size_t n);
 // Rows per tile of the two-step kernel for a requested number (0: default).
 int seg2_rows(int seg) { return std::max(1, std::min(seg > 0 ? seg : 6, kMaxTileRows2)); }
 
-// Rows per tile when the launch is left to the library, which then takes two
-// steps per launch: the fewest of 2, 4, 6, 8 that leave a workgroup a compute
-// unit (256), where a launch is one tile's latency, else the tallest tiles,
-// whose halo costs least.  us per step at 2 4 6 8 10 rows (one step per launch,
-// the default before, in brackets):
+// Rows per tile of the tile lists when the launch is left to the library, which
+// then takes two steps per launch: the fewest of 2, 4, 6, 8 that leave a workgroup
+// a compute unit (256), where a launch is one tile's latency, else the tallest
+// tiles, whose halo costs least.  us per step at 2 4 6 8 10 rows (one step per
+// launch, the default before, in brackets):
 //   fp32 80^2 3.6 3.9 3.9 4.1 4.3 (7.2)  320^2 7.0 4.5 4.7 4.3 4.5 (9.6)  701x354 9.6 7.1 6.2 6.2 5.5 (9.0)
 //        1024^2 29 18 15 15 13 (22)      2048^2 127 80 66 64 55 (100)
 //   fp64 80^2 4.2 4.4 4.8 5.0 5.3 (8.5)  200^2 7.4 4.5 4.8 5.0 5.3 (10.7) 701x354 19.6 13.5 11.7 10.7 10.1 (16.9)
 //        1024^2 60 36 29 26 25 (36)      2048^2 264 164 133 116 107 (172)
-int default_rows2(const slbm_s* h)
+int list_rows2(const slbm_s* h)
 {
     const long long strips = (h->nx + kStrip2 - 1) / kStrip2;
     for (int r = 2; r < kMaxTileRows2; r += 2)
         if (strips * ((h->ny + r - 1) / r) <= 256) return r;
     return kMaxTileRows2;
+}
+
+// The memory-side cache, with a little to spare, and what a step goes through
+// (both buffers and the displacement).
+constexpr long long kCacheBytes = 250000000;
+long long state_bytes_of(const slbm_s* h) { return h->plane * (18 * (long long)h->esize + 16); }
+
+// Rows per tile of the library's launch of two steps; 0: it takes one step per
+// launch.  The rows of the lists where there are any, and where a launch is one
+// tile's latency.  Without lists (no cut links, or too many in a tile, or of
+// too many groups, or no room) two steps save their traffic alone, against more
+// halo and, in single precision, registers spilled (6 rows best, 10 with 60 B a
+// lane): large states, and plates without cut links unless the narrower strips
+// or flat tiles cost more.  us per step, one step per launch and two (6 rows
+// in single, 10 in double precision):
+//   without cut links, periodic
+//     fp32  400^2 5.0 4.6   1024^2 19.0 18.7   2048^2 89 83   3000x40 5.2 4.6   116x4000 10.9 10.5 (2 strips of 58 and of 62)
+//           62x4000 6.3 9.5 (2 and 1)   124x4000 11.0 12.7 (3 and 2)   180x3000 11.6 13.0 (4 and 3)   100000x3 8.3 8.9
+//     fp64  400^2 6.8 6.7   1024^2 30.7 26.1   2048^2 162 104   124x4000 17.2 15.6   180x3000 18.4 16.3   62x4000 9.1 12.0
+//           rows of the plate: 100000x1 10.1 7.5   x2 11.4 8.0   20000x5 6.0 5.2 (at 10 rows 15.5, 16.1, 5.9)
+//   a hole, and more groups than the lists take
+//     fp32  600^2 12.0 12.3   900^2 18.9 21.7   1024^2 21.6 23.9   1600^2 (243 MB) 39 47   1700^2 73 54   2048^2 106 86
+//     fp64  600^2 21.1 20.1   900^2 31.2 34.1   1024^2 36.1 37.5   1250^2 (276 MB) 67 51   2048^2 188 137
+int default_rows2(const slbm_s* h)
+{
+    const int rows = list_rows2(h);
+    if (rows < kMaxTileRows2 || (h->rec.fit && h->rec.seg == rows)) return rows;
+    const bool single = h->precision == SLBM_FP32;
+    const int strips2 = (h->nx + kStrip2 - 1) / kStrip2, strips1 = (h->nx + 61) / 62;
+    if (single ? 10 * strips2 > 11 * strips1 || h->ny < 6 : 2 * strips2 > 3 * strips1) return 0;
+    if (h->n_links > 0 && state_bytes_of(h) <= kCacheBytes) return 0;
+    return std::min(single ? 6 : kMaxTileRows2, h->ny);
 }
 
 // Whether the launch is the library's choice, and the rows per tile of a
@@ -877,8 +909,7 @@ long long state_bytes(long long sites) { return sites * (long long)(18 * sizeof(
 // 24 mixed plates of a batch (fp32, 64 steps): 7817; 7651 7542 7554.
 TileOrder tile_order(int back, int grid, long long bytes)
 {
-    const long long cache = 250000000;
-    return {back, bytes <= cache ? 0 : (bytes <= 2 * cache ? grid / 2 : grid / 4)};
+    return {back, bytes <= kCacheBytes ? 0 : (bytes <= 2 * kCacheBytes ? grid / 2 : grid / 4)};
 }
 
 bool recording(hipStream_t stream);
@@ -890,7 +921,7 @@ void default_lists(slbm_s* h)
 {
     if (recording(h->stream)) return;
     try {
-        if (tile_records(h, default_rows2(h)) == SLBM_OK) return;
+        if (tile_records(h, list_rows2(h)) == SLBM_OK) return;
     } catch (const std::bad_alloc&) {
     }
     drop_tile_records(h);
@@ -925,7 +956,7 @@ template <typename real>
 void dispatch_step2(const slbm_s* h, const StepArgs<real>& a, int back)
 {
     const int grid = grid_for(a);
-    const TileOrder order = tile_order(back, grid, state_bytes<real>(h->plane));
+    const TileOrder order = tile_order(back, grid, state_bytes_of(h));
     const dim3 blk(64 * (a.seg + 6));
     constexpr int lo = k2_waves<real>(1), hi = k2_waves<real>(kMaxTileRows2);
     const bool per = h->px || h->py;
