@@ -1462,7 +1462,8 @@ int create_impl(const slbm_params* p, slbm_handle* out, Arena* arena = nullptr, 
 }  // namespace
 
 // slbm_displacement_device_noalloc takes plates of up to this many padded
-// sites (a 4096 x 4096 plate's).
+// sites (a 4096 x 4096 plate's): the readout needs no scratch, but the entry
+// point keeps the limit, and the message, of the scratch it once had.
 constexpr size_t kNoallocSites = (size_t)18874368;
 
 // ------------------------------------------------------------------ ABI
