@@ -1089,8 +1089,6 @@ int launch_readout(slbm_s* h, const ReadoutDst<T>& d)
     return SLBM_OK;
 }
 
-bool recording(hipStream_t stream);
-
 template <typename T>
 int readout(slbm_s* h, double* u, T* rho, T* j, T* P, T* sigma)
 {
