@@ -190,35 +190,51 @@ def has_ext_links3(box):
 
 
 def recorded_kernels(lib, stream, call):
-    """Kernels that `call` queues on the HIP stream `stream` (an address): it is
-    recorded, not run, so the handle that it steps is of no use afterwards."""
+    """Names (as compiled) of the kernels that `call` queues on the HIP stream
+    `stream` (an address), in order: it is recorded, not run, so the handle that
+    it steps is of no use afterwards."""
     import ctypes as C
-    graph, n = C.c_void_p(), C.c_size_t()
+
+    class Dim3(C.Structure):
+        _fields_ = [("x", C.c_uint32), ("y", C.c_uint32), ("z", C.c_uint32)]
+
+    class Node(C.Structure):                           # hipKernelNodeParams
+        _fields_ = [("block", Dim3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", Dim3),
+                    ("params", C.c_void_p), ("shared", C.c_uint)]
+
+    graph, n, stream = C.c_void_p(), C.c_size_t(), C.c_void_p(stream)
+    lib.hipKernelNameRefByPtr.restype = C.c_char_p
 
     def check(rc):
         if rc != 0:
             raise RuntimeError(f"HIP error {rc} while recording")
 
-    check(lib.hipStreamBeginCapture(C.c_void_p(stream), C.c_int(1)))         # 1: this thread's calls alone
+    check(lib.hipStreamBeginCapture(stream, C.c_int(1)))                     # 1: this thread's calls alone
     try:
         call()
     finally:
-        check(lib.hipStreamEndCapture(C.c_void_p(stream), C.byref(graph)))
+        check(lib.hipStreamEndCapture(stream, C.byref(graph)))
     check(lib.hipGraphGetNodes(graph, None, C.byref(n)))
+    nodes = (C.c_void_p * n.value)()
+    check(lib.hipGraphGetNodes(graph, nodes, C.byref(n)))
+    names = []
+    for x in nodes:
+        p = Node()
+        check(lib.hipGraphKernelNodeGetParams(C.c_void_p(x), C.byref(p)))
+        names.append(lib.hipKernelNameRefByPtr(C.c_void_p(p.func), stream).decode())
     check(lib.hipGraphDestroy(graph))
-    return n.value
-
-
-def kernels3(s, stream, box):
-    """Names of the kernels of one step of the box `s` (which ends here): one
-    more recorded step is that many more launches."""
-    from paper_2208_04088_amd import slbm3
-    many, few = (recorded_kernels(slbm3.lib(), stream, lambda: s.step(k)) for k in (6, 4))
-    per = (many - few) // 2
-    ext = ("k3_links_ext",) if has_ext_links3(box) else ()
-    names = ext + (("k3_march",) if per - len(ext) == 1 else ("k3_density", "k3_step"))
-    assert len(names) == per, (names, per)
     return names
+
+
+def kernels3(s, stream):
+    """The kernels of one step of the box `s` (which ends here), in order: those
+    of the last of a few recorded steps."""
+    import re
+    from paper_2208_04088_amd import slbm3
+    names = [re.search(r"k3_[a-z_]+", k).group(0) for k in recorded_kernels(slbm3.lib(), stream, lambda: s.step(4))]
+    last = names[-1]
+    start = max(i for i, k in enumerate(names[:-1]) if k == last)
+    return tuple(names[start + 1:])
 
 
 def measured_traffic3(box, prec, kernels):
@@ -298,7 +314,7 @@ def time_box3(torch, stream, box, prec, steps, warm):
     except slbm3.S.SlbmError:
         diverged = True
     assert diverged or np.isfinite(s.displacement()).all()
-    kernels = kernels3(s, stream.cuda_stream, box)
+    kernels = kernels3(s, stream.cuda_stream)
     sites = box.n_material
     bps = bytes_per_site3(prec)
     step_bytes = bytes_per_step3(box, prec)
