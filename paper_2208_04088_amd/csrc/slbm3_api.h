@@ -498,6 +498,28 @@ int launch3(slbm3_s* h, int what)
 
 int launch3_any(slbm3_s* h, int what);
 
+// What a step goes through: both buffers and the displacement.
+long long state_bytes3(const slbm3_s* h) { return h->plane * (2 * kQ * (long long)h->esize + 24); }
+
+// Whether k3_march stores past the caches: once the state exceeds the 256 MB
+// memory-side cache; below, the next launch finds what plain stores left in it.
+// Boxes with cut links are above it wherever k3_march takes them.  us per step of
+// slabs, streamed and plain:
+//   fp32  96^3 (155 MB) 54 43   112^3 (247 MB) 80 56   116^3 (274 MB) 81 80   128^3 99 102   160^3 196 204
+//   fp64  64^3 (85 MB) 27 25    90^3 (239 MB) 82 56    90x130x70 (268 MB) 90 93   96^3 77 82   128^3 175 181
+// Rows that are not whole lines (64 bytes) share theirs with the next, and a line
+// stored past the caches in two parts costs more than one; in single precision
+// plain stores win from some 450 MB:
+//   114x128x128 (329 MB) 100 102   120x150x150 (475 MB) 134 146   190x150x150 (752 MB) 235 224   114x192x192 (740 MB) 265 236
+//   180x152x152 (732 MB) 275 242   300x256x256 (3.5 GB) 1099 1027   255x256x256 1029 964
+// (double precision streams: 120x150x150 213 231, 300x256x256 1709 1759, 250x200x200 902 876).
+constexpr long long kRaggedBytes = 450000000;
+bool streamed3(const slbm3_s* h)
+{
+    const long long b = state_bytes3(h);
+    return b > kCacheBytes && !(h->precision == SLBM_FP32 && h->nx % 16 != 0 && b > kRaggedBytes);
+}
+
 // Planes a k3_march workgroup marches through, for `tiles` tiles of rows over
 // nz planes: a workgroup takes depth + 2 planes' time and a little to start,
 // and the chip runs `slots` of them at once, so the depth that needs the
@@ -599,8 +621,8 @@ March3 march_of(const slbm3_s* h, const Geo3& g)
     const double rounds = (m.mtiles + m.slots - 1) / m.slots;
     const double useful = (double)m.nch * h->ny * h->nz / (rounds * m.slots * (m.rows + 2) * (m.depth + 2));
     if (useful < 0.39) return m;
+    const double lanes = h->nx / (64.0 * m.nch);
     if (h->geo) {
-        const double lanes = h->nx / (64.0 * m.nch);
         if (h->n_links == 0 || h->ny < 4 || h->nz < 4) return m;
         m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000 && lanes >= 0.75)) &&
                even_links3(h, g, m);
@@ -634,14 +656,7 @@ int launch3_march(slbm3_s* h)
                            h->stream, a, (real*)h->wall[h->cur]);
     const unsigned unit = 8 * a.xgroup;
     const dim3 grid((a.mtiles + unit - 1) / unit * unit), blk(64 * (a.rows + 2));
-    // stores past the caches once the state (both buffers, U) exceeds the 256 MB
-    // memory-side cache; below, the next launch finds what plain stores left in
-    // it.  Boxes with cut links are above it wherever k3_march takes them.  us per
-    // step of slabs, streamed and plain:
-    //   fp32  96^3 (155 MB) 54 43   112^3 (247 MB) 80 56   116^3 (274 MB) 81 80   128^3 99 102   160^3 196 204
-    //   fp64  64^3 (85 MB) 27 25    90^3 (239 MB) 82 56    90x130x70 (268 MB) 90 93   96^3 77 82   128^3 175 181
-    const bool stream = GEO || h->plane * (long long)(2 * kQ * sizeof(real) + 24) > 250000000;
-    if (stream)
+    if (GEO || streamed3(h))
         hipLaunchKernelGGL((k3_march<real, PX, GEO, true>), grid, blk, 0, h->stream, a);
     else
         hipLaunchKernelGGL((k3_march<real, PX, GEO, GEO>), grid, blk, 0, h->stream, a);

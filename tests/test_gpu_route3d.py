@@ -72,3 +72,20 @@ def test_launches_of_a_step(env, make, d, single, double):
     box = make(*d)
     assert launches(env, box, "fp32") == single
     assert launches(env, box, "fp64") == double
+
+
+# k3_march's last template argument: its stores pass the caches by
+@pytest.mark.parametrize("d,single,double", [((96, 96, 96), False, True), ((120, 150, 140), True, True),
+                                             ((160, 160, 160), True, True), ((190, 150, 150), False, True),
+                                             ((50, 300, 300), False, True), ((52, 240, 240), False, True),
+                                             ((48, 300, 300), True, True)])
+def test_stores_of_the_one_launch_step(env, d, single, double):
+    torch, slbm3 = env
+    for box in (slab(*d), periodic(*d)):
+        for prec, streamed in (("fp32", single), ("fp64", double)):
+            stream = torch.cuda.Stream().cuda_stream
+            with slbm3.Solver3(box, prec, stream=stream) as s:
+                s.step(2)
+                s.sync()
+                name = recorded_kernels(slbm3.lib(), stream, lambda: s.step(1))[-1]
+            assert "k3_march" in name and ("Lb1EEE" in name) == streamed, (prec, name)
