@@ -597,14 +597,26 @@ bool even_links3(const slbm3_s* h, const Geo3& g, const March3& m)
 //   fp64 slab  1024x1024x2 .36 212 235   1024x200x4 .35 72 84   1024x64x4 .33 26 28   3000x17x17 .41 80 85
 //              128x64x32 .40 29 24   500x30x17 .40 27 24   1024x1024x3 .45 317 316   1024x1024x4 .48 435 399
 // and two rows between walls (512x2x512 fp64 45 51, 700x2x700 97 106; periodic 41 33, 94 77).
+// Nor, in single precision, boxes of several chunks whose rows are not whole lines
+// (64 bytes) and end in a short chunk: a chunk's 64 lanes cost the same however many
+// hold sites, and lines that two rows share are written in parts.  Up to the
+// caches' size, and again between where the two launches fall out of them and
+// where the parts cost more, one launch is still faster.  lanes (the share that
+// hold sites), state, two launches and one, slab and periodic:
+//   130x100x100 .68 229 MB 69 61, 56 51     66x150x150 .52 261 MB 90 111, 70 95     150x100x100 .78 264 MB 79 90, 68 84
+//   98x136x136 .77 319 MB 117 109, 105 101  136x120x120 .71 345 MB 126 115, 111 108  100x150x150 .78 396 MB 140 130, 129 121
+//   130x150x150 .68 515 MB 187 203, 173 194   90x200x200 .70 634 MB 227 261, 210 251   98x208x208 .77 746 MB 267 285, 259 275
+//   140x230x230 .73 1303 MB 468 495, 461 488  108x288x288 .84 1577 MB 526 547, 555 522  257x256x256 .80 983 1025, 1010 1012
+//   rows that fill their chunks  114x192x192 .89 740 MB 252 236, 247 222   250x200x200 .98 577 480, 600 468   255x256x256 988 964
+//   rows of whole lines  96x150x150 .75 133 114, 109 99   144x150x150 .75 198 187, 180 180   160^3 .83 234 197, 216 189
 //
 // With cut links the series is longer (6 us a plane), and a row whose last
-// chunk is short pays for all of it (porous solids, n^3; `lanes` is the share of
-// the chunks' lanes that hold sites):
+// chunk is short pays for all of it (porous solids, n^3):
 //   fp32  100 54 76   120 107 99   128 123 103   130 151 160   140 186 195   150 222 246   160 241 234   170 318 329
 //         180 374 364   200 527 507   256 967 752
+//         130x200x200 342 404   90x240x240 334 413   164 270 291   210x200x200 534 543   257x256x256 1072 1182
 //   fp64  100 123 132  120 194 181  128 226 220  130 277 276  136 307 324  140 332 349  144 349 339  150 405 399
-//         160 452 447  170 563 545  180 650 565  200 937 847  256 1778 1538
+//         160 452 447  170 563 545  180 650 565  200 937 847  256 1778 1538   70x260x260 631 684   130x200x200 627 628
 // Fewer than four rows or planes leave its workgroups, one to a compute unit, too
 // few waves (a hole along the short axis): fp32 1024x2x1024 108 189, x3 162 209,
 // x4 223 229, x5 278 276, 1024x1024x3 163 184, x4 226 232, x6 335 313.
@@ -622,8 +634,12 @@ March3 march_of(const slbm3_s* h, const Geo3& g)
     const double useful = (double)m.nch * h->ny * h->nz / (rounds * m.slots * (m.rows + 2) * (m.depth + 2));
     if (useful < 0.39) return m;
     const double lanes = h->nx / (64.0 * m.nch);
+    if (single && m.nch > 1 && h->nx % 16 != 0 && lanes < 0.87) {
+        const long long b = state_bytes3(h);
+        if (h->geo || (b > kCacheBytes && (b < 290000000 || b > kRaggedBytes))) return m;
+    }
     if (h->geo) {
-        if (h->n_links == 0 || h->ny < 4 || h->nz < 4) return m;
+        if (h->n_links == 0 || h->ny < 4 || h->nz < 4 || lanes < (single ? 0.0 : 0.6)) return m;
         m.on = (h->plane >= 4000000 || (single ? h->plane >= 1500000 && lanes >= 0.875 : h->plane >= 2000000 && lanes >= 0.75)) &&
                even_links3(h, g, m);
     } else if (h->px) {

@@ -66,6 +66,10 @@ def crack(nx, ny, nz):
     (slab, (400, 9, 240), 2, 1), (slab, (400, 8, 270), 1, 1),
     (cavity, (128, 128, 128), 1, 1), (cavity, (136, 136, 136), 2, 2), (cavity, (144, 144, 144), 2, 1),
     (cavity, (160, 160, 160), 1, 1), (crack, (1024, 1024, 3), 2, 2), (crack, (1024, 1024, 6), 1, 1),
+    (slab, (130, 100, 100), 1, 1), (slab, (66, 150, 150), 2, 1), (periodic, (150, 100, 100), 2, 1),
+    (periodic, (100, 150, 150), 1, 1), (slab, (96, 150, 150), 1, 1), (slab, (130, 200, 200), 2, 1),
+    (periodic, (90, 200, 200), 2, 1), (slab, (190, 150, 150), 1, 1), (slab, (50, 300, 300), 1, 1),
+    (cavity, (130, 200, 200), 2, 1), (cavity, (70, 260, 260), 2, 2), (cavity, (180, 180, 180), 1, 1),
     (block, (1024, 8, 512), 2, 2), (block, (512, 34, 256), 2, 2), (block, (160, 160, 160), 2, 2),
 ])
 def test_launches_of_a_step(env, make, d, single, double):
